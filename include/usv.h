@@ -184,7 +184,7 @@ usv_status usv_block_sparse_attn(const void* q, const void* k, const void* v,
  * the block range, compared lexicographically.  Measured on MI355X: per-row
  * budgets uniform in 8..64 at the merged 480p shape 12 % faster than index
  * order; uniform budgets at the 720p shape (59 of 1182 blocks, where a head's
- * K and V are ten times the L2) 20 % faster; uniform budgets at the 480p shape
+ * K and V are ten times the L2) 8 % faster; uniform budgets at the 480p shape
  * 1 % (there the sort costs what it gains).  It pays when the lists are ragged
  * or when a head's K and V are many times the L2.
  *
@@ -192,12 +192,14 @@ usv_status usv_block_sparse_attn(const void* q, const void* k, const void* v,
  *                         (b,h) takes; deterministic.  idx == NULL: by list
  *                         length (and block index) only.
  *   usv_block_sparse_attn_ordered   usv_block_sparse_attn with that table;
- *                         work_order == NULL is usv_block_sparse_attn.  The
- *                         output does not depend on the table as long as every
- *                         head's slice is a permutation of 0..nb-1 (entries are
- *                         clamped into range; a block named twice is computed
- *                         twice, a block never named is not written).  fp32
- *                         inputs ignore the table.
+ *                         work_order == NULL is usv_block_sparse_attn.  As long
+ *                         as every head's slice is a permutation of 0..nb-1, the
+ *                         output depends on the table at most in the rounding of
+ *                         its fp32 sums: a large launch begins the list of a
+ *                         slot where the other slots' sweeps are expected to
+ *                         be, and goes around.  (Entries are clamped into range;
+ *                         a block named twice is computed twice, a block never
+ *                         named is not written.)  fp32 inputs ignore the table.
  * idx        : NULL or [B, Hh, nb, kmax] int32 (device, read only), ascending lists
  *              as written by stage 2 (other lists only make the order less useful)
  * cnt        : [B, Hh, nb] int32 (device, read only), as written by stage 2
@@ -359,7 +361,7 @@ typedef struct {
   usv_strides out_strides; /* element strides of out; token == 0 means contiguous [B, Hh, Nv, d] */
   const int32_t* block_valid; /* NULL, or device [seq_len / 64] int32 from usv_cube_order_padded: see there */
   const int32_t* work_order;  /* NULL, or device [B, Hh, seq_len / 64] int32 from usv_attn_work_order: the attention
-                                 launch walks each head's query blocks in that order (same output) */
+                                 launch walks each head's query blocks in that order */
 } usv_raster;
 
 usv_status usv_cube_order(const usv_shape* shape, const usv_grid* grid, int32_t* order, void* stream);

@@ -290,9 +290,8 @@ usv_status attn_any(const void* q, const void* k, const void* v, const usv_shape
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (s.bf16) {
     const usv::FuseArgs fuse{coarse, static_cast<const uint16_t*>(gate_fine), static_cast<const uint16_t*>(gate_coarse)};
-    return hip_result(usv::launch_attn_bf16(q, k, v, s, idx, cnt, kmax, scale, out, out_dtype == USV_F32, lse, fuse, st,
-                                            work_order),
-                      "usv_block_sparse_attn launch");
+    const usv::AttnBf16Args args{q, k, v, s, idx, cnt, kmax, scale, out, lse, fuse, usv::RasterArgs{}, work_order};
+    return hip_result(usv::launch_attn_bf16(args, out_dtype == USV_F32, st), "usv_block_sparse_attn launch");
   }
   // fp32 inputs (the accuracy path; it takes the query blocks in index order whatever work_order says): attention,
   // then the fusion kernel in place
@@ -583,8 +582,8 @@ usv_status usv_block_sparse_attn_raster_fused(const void* q, const void* k, cons
   if (scale <= 0.f) scale = 1.0f / std::sqrt((float)s.d);
   const usv::FuseArgs fuse{coarse, static_cast<const uint16_t*>(gate_fine), static_cast<const uint16_t*>(gate_coarse)};
   if (view->work_order) USV_TRY(check_ptr(view->work_order, "work_order"));
-  return hip_result(usv::launch_attn_bf16_raster(q, k, v, s, ras, idx, cnt, kmax, scale, out, out_dtype == USV_F32, lse,
-                                                 fuse, static_cast<hipStream_t>(stream), view->work_order),
+  const usv::AttnBf16Args args{q, k, v, s, idx, cnt, kmax, scale, out, lse, fuse, ras, view->work_order};
+  return hip_result(usv::launch_attn_bf16(args, out_dtype == USV_F32, static_cast<hipStream_t>(stream)),
                     "usv_block_sparse_attn_raster launch");
 }
 

@@ -1,6 +1,9 @@
 // Stage 3, bf16 path: block-sparse flash attention on the gfx950 matrix cores
 // (masked-attention equation, paper Section 3.2; only listed K/V cubes are touched).
 //
+// This file: the dispatch, and the kernel for grids that do not fill the chip; the one for large grids is in
+// usv_attn_wide.hip.
+//
 // Work decomposition (one workgroup = 4 wavefronts = one 64-row query block):
 //   wave (qh, kh): query rows 32*qh .. +32, keys 32*kh .. +32 of every listed 64-key tile.
 //   Each wave runs an independent online softmax over its half of the keys; the two key halves
@@ -22,68 +25,23 @@
 // The 16x16x32 shape was chosen over 32x32x16 by measurement: the same flops draw less power, and
 // under this kernel the chip runs at its power limit, where less energy per tile is more clock.
 //
-// What bounds the kernel, measured on MI355X: a wavefront issues at most one instruction (of any
-// kind) every ~8 clocks, a tile's 32 MFMAs per wave occupy the matrix pipe for 512 clocks, and the
-// CU's vector-memory path moves 64 B/clk (a 64x64 tile needs 32 KiB of K and V: 512 clocks as
-// well).  With two workgroups per CU the chip then sits at its power limit
-// (it clocks this kernel at ~1.7 GHz of 2.4) and, for lists without locality, near what the
-// L2-miss path delivers (~7 TB/s), so every instruction and every byte moved costs clock.
-// The design goal is therefore few instructions per tile and two or three
-// workgroups per CU (waves per SIMD) that cover each other's issue gaps and waits:
+// What bounds it on a small grid is latency: four waves split each query block two ways in queries and two ways in keys, so
+// a workgroup is done in half the steps of the wide kernel, and its straight-line code is shorter (12 heads x 32 blocks,
+// 4 listed: 14.2 us against 18.4 us; 1 block: 5.5 against 6.4 us).
 //   - K/V tiles go global -> LDS directly (global_load_lds, 16 bytes per lane, no register
-//     staging, M0 set once per tile) through a ring of tile slots K(n), V(n), K(n+1), ... (3 as launched);
+//     staging, M0 set once per tile) through a ring of tile slots K(n), V(n), K(n+1);
 //     a slot is refilled as soon as the barrier after its last reader has passed;
 //   - the 16-byte chunks of a row are XOR-permuted on the way in (applied to the global address;
 //     the LDS side of the DMA is lane-linear) so that both the 16-byte K fragment reads and the
 //     transposing V reads are bank-conflict free;
 //   - softmax in the log2 domain; the running max is only raised when a row's tile max exceeds it
 //     by more than kRescaleSlack, so the O rescale is skipped on almost every tile.
-#include <type_traits>
-
-#include "usv_internal.h"
+#include "usv_attn_bf16.h"
 
 namespace usv {
 namespace {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
-typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-typedef __attribute__((__vector_size__(4 * sizeof(short)))) short short4v;
-typedef __attribute__((__vector_size__(8 * sizeof(short)))) short short8v;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-
-// Accumulators are kept four 16x16 tiles to a 16-register tuple and the MFMAs work on quarter q of it:
-// with one allocation unit per tuple the compiler updates the accumulators in place (given 64 separate
-// 4-register values it rotated them through fresh registers and copied all of them back on every tile).
-__device__ __forceinline__ f32x4 quarter(const f32x16& v, int q) {
-  switch (q) {
-    case 0: return __builtin_shufflevector(v, v, 0, 1, 2, 3);
-    case 1: return __builtin_shufflevector(v, v, 4, 5, 6, 7);
-    case 2: return __builtin_shufflevector(v, v, 8, 9, 10, 11);
-    default: return __builtin_shufflevector(v, v, 12, 13, 14, 15);
-  }
-}
-__device__ __forceinline__ void set_quarter(f32x16& v, int q, const f32x4& c) {
-  const f32x16 w = __builtin_shufflevector(c, c, 0, 1, 2, 3, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1);
-  switch (q) {
-    case 0: v = __builtin_shufflevector(v, w, 16, 17, 18, 19, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15); break;
-    case 1: v = __builtin_shufflevector(v, w, 0, 1, 2, 3, 16, 17, 18, 19, 8, 9, 10, 11, 12, 13, 14, 15); break;
-    case 2: v = __builtin_shufflevector(v, w, 0, 1, 2, 3, 4, 5, 6, 7, 16, 17, 18, 19, 12, 13, 14, 15); break;
-    default: v = __builtin_shufflevector(v, w, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 16, 17, 18, 19); break;
-  }
-}
-
 constexpr int kThreads = 256;
-constexpr float kRescaleSlack = 8.0f;  // log2 units
-// The probabilities are computed as 2^(logit - m - p_shift): the common factor 2^-p_shift cancels in
-// sum(p v) / sum(p), and it pushes every p below tau = 2^-(126 - p_shift) of the row's reference under
-// the fp32 normal range, where v_exp_f32 returns an exact 0.  Zero operands keep the matrix cores'
-// multipliers quiet, which matters because the chip is power-limited under this kernel (measured:
-// +3 % at tau = 2^-24, +10 % on dense lists at tau = 2^-16).  The dropped mass of a row is below
-// keys * tau of its largest term; the launcher picks tau so that this is at most 2^-12 (2.4e-4
-// relative, against an error budget of ~2.5e-3), i.e. tau = 2^-12 / (keys of the longest list).
-constexpr int kDropLog2 = 12;
 
 template <int D>
 struct Tile {
@@ -102,67 +60,6 @@ struct Tile {
   __device__ static int k_off(int row, int chunk) { return row * kRowBytes + ((chunk ^ k_swz(row)) << 4); }
   __device__ static int v_off(int row, int chunk) { return row * kRowBytes + ((chunk ^ v_swz(row)) << 4); }
 };
-
-__device__ __forceinline__ float4 load_bf16x4(const uint16_t* p) {
-  // (the gates of the fused second branch: read once, so a streaming read)
-  typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2;
-  const u32x2 ww = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
-  const uint2 w = make_uint2(ww[0], ww[1]);
-  return make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
-                     __uint_as_float(w.y & 0xffff0000u));
-}
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// v_permlane32_swap on two copies of x leaves (x of lane l % 32, x of lane l % 32 + 32) in both lanes:
-// one VALU op, no LDS round trip.
-__device__ __forceinline__ void both_halves(float x, float& lo, float& hi) {
-  const unsigned u = __float_as_uint(x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  lo = __uint_as_float(r[0]);
-  hi = __uint_as_float(r[1]);
-}
-
-// Max of the 8 accumulator values a lane holds for one query, in 4 instructions.  One assembly block:
-// v_max3 without the NaN-quieting moves the compiler adds around fmaxf (the inputs are never NaN).
-__device__ __forceinline__ float max8(float a0, float a1, float a2, float a3, float b0, float b1, float b2, float b3) {
-  float x, y;
-  asm("v_max3_f32 %0, %2, %3, %4\n\t"
-      "v_max3_f32 %1, %5, %6, %7\n\t"
-      "v_max3_f32 %0, %0, %8, %9\n\t"
-      "v_max_f32 %0, %0, %1"
-      : "=&v"(x), "=&v"(y)
-      : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(b0), "v"(b1), "v"(b2), "v"(b3));
-  return x;
-}
-
-// The four lanes c, c + 16, c + 32, c + 48 hold the keys of one query.  v_permlane16_swap on two copies
-// of x leaves (x of the even 16-lane row, x of the odd row) of each row pair in both rows, and
-// v_permlane32_swap does the same for the two wave halves: two VALU ops per step, no LDS round trip.
-__device__ __forceinline__ void row_pair(float x, float& even, float& odd) {
-  const unsigned u = __float_as_uint(x);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  even = __uint_as_float(r[0]);
-  odd = __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float max_over_groups(float x) {
-  float a, b;
-  row_pair(x, a, b);
-  x = fmaxf(a, b);
-  both_halves(x, a, b);
-  return fmaxf(a, b);
-}
-__device__ __forceinline__ float sum_over_groups(float x) {
-  float a, b;
-  row_pair(x, a, b);
-  x = a + b;
-  both_halves(x, a, b);
-  return a + b;
-}
-
-__device__ __forceinline__ unsigned lds_address(const void* p) {  // LDS byte address of a __shared__ pointer
-  return (unsigned)(uintptr_t)p;
-}
 
 // One wave's share of a tile, global -> LDS: N instructions of 16 bytes per lane.  Instruction `it`
 // reads gbase + voff[it] + 1024*it per lane and lands at lds_addr + 1024*it + 16*lane (the
@@ -197,15 +94,14 @@ __device__ __forceinline__ void dma_tile<2>(const void* gbase, const int (&voff)
       : "memory");
 }
 
-// SLOTS (odd) = tile slots of the LDS ring; a tile is requested LEAD = (SLOTS-1)/2 tiles before it
-// is used.  WGS = workgroups (= waves per SIMD) the register and LDS budget is sized for.
+// The LDS ring has kSlots tile slots; a tile is requested LEAD tiles before it is used.  Two workgroups per CU.
 // RASTER: Q, K, V and the output are in raster token order (any strides); `ras.order[p]` gives the
 // raster index of cube-major position p.  Every wave fetches the 16 order entries of the rows it
 // requests ahead of the tile (one more 4-byte-per-lane DMA per tile, into a small LDS ring that only
 // this wave reads), turns them into the per-lane global offsets of its DMA instructions, and the
 // epilogue stores each row at its raster position: no reordered copy of any tensor exists.
-template <int D, bool OUT_F32, int SLOTS, int WGS, bool RASTER>
-__global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __restrict__ q,
+template <int D, bool OUT_F32, bool RASTER>
+__global__ __launch_bounds__(kThreads, 2) void attn_bf16(const uint16_t* __restrict__ q,
                                                                 const uint16_t* __restrict__ k,
                                                                 const uint16_t* __restrict__ v,
                                                                 const int32_t* __restrict__ idx,
@@ -219,9 +115,8 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
   constexpr int KS = D / 32;  // MFMA k-steps of the QK^T product
   constexpr int DT = D / 16;  // 16-wide d sub-tiles of the output
   constexpr int kDma = T::kDmaPerWave;
-  constexpr int kSlots = SLOTS;
-  constexpr int LEAD = (SLOTS - 1) / 2;
-  static_assert(SLOTS % 2 == 1 && SLOTS >= 3, "odd ring: K items land on the slots V items left and vice versa");
+  constexpr int kSlots = 3;  // odd: K items land on the slots V items left and vice versa
+  constexpr int LEAD = 1;
   constexpr int XROWS = DT * 8 + 4;  // exchange rows per wave: O registers, m and l of its two queries per lane
   constexpr int OSTRIDE = D + 4;     // fp32 staging row stride (floats), bank-spread
   static_assert(XROWS * 64 >= 32 * OSTRIDE, "the staging rows of a query half overlay its exchange area");
@@ -348,7 +243,7 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
   load_valid();
   auto valid_at = [&](int n) { return __builtin_amdgcn_readlane(valid_v, n & 63); };
 
-  // ring item 2n = K(list[n]) -> slot (2n) % SLOTS, item 2n+1 = V(list[n]) -> slot (2n+1) % SLOTS;
+  // ring item 2n = K(list[n]) -> slot (2n) % kSlots, item 2n+1 = V(list[n]) -> slot (2n+1) % kSlots;
   // the first LEAD tiles are requested here
   if constexpr (RASTER) {
     // the order entries of the first LEAD + 2 tiles; the loop requests those of tile n + LEAD + 2
@@ -415,10 +310,6 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
 
   // per-lane LDS byte offsets of the fragment reads (loop invariant)
   // K fragment of key tile mt, k-step t: key row 32 kh + 16 mt + c16, chunk 4 t + G; +16 rows is a constant
-  // (both tables are XOR patterns: kfrag[t] = kfrag[0] ^ (t << 6) and vfrag[dt] = vfrag[0] ^ (dt << 5), because the
-  // swizzles only touch address bits that t and dt alone set.  The three-workgroup shape has no registers to
-  // spare and derives the entries with one v_xor per use; the other shapes keep them in registers.)
-  constexpr bool kLean = WGS >= 3;
   int kfrag[KS];
 #pragma unroll
   for (int t = 0; t < KS; ++t) kfrag[t] = T::k_off(kh * 32 + c16, 4 * t + G);
@@ -446,9 +337,9 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
   for (int t = 0; t < KS; ++t) asm volatile("" ::"v"(qf[0][t]), "v"(qf[1][t]));
   __syncthreads();
 
-  // One tile.  PHASE = n % SLOTS is a compile-time constant so that every LDS offset of the ring
+  // One tile.  PHASE = n % kSlots is a compile-time constant so that every LDS offset of the ring
   // folds into the instruction.  On entry K(n) is in LDS and visible to every wave and the slot of
-  // V(n-1) is free.  A freed slot of item e is refilled with item e + SLOTS.  STEADY (compile time)
+  // V(n-1) is free.  A freed slot of item e is refilled with item e + kSlots.  STEADY (compile time)
   // says that tile n+LEAD exists, which spares the main loop every end-of-list check.
   // blocks from this one on hold padded keys: the partial block (if Nv is not a multiple of 64) and, when the
   // tensors are padded by whole blocks, every block behind it.  A caller's list may name those too: all of
@@ -467,7 +358,7 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
       if (decltype(steady_c)::value || n + LEAD + 2 < n_list) issue_ord(jq[QD], n + LEAD + 2);
       if (steady) read_ord(n + LEAD);
     }
-    if (steady) issue_k(j_pre, freed_v);  // item 2n-1+SLOTS = K(n+LEAD)
+    if (steady) issue_k(j_pre, freed_v);  // item 2n-1+kSlots = K(n+LEAD)
 
     // ---- S^T = K Q^T over this wave's 32 keys x 32 queries: s[mt][nt] --------------------------
     f32x16 s;  // quarter 2 mt + nt = tile (mt, nt)
@@ -477,32 +368,26 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
       // fragments are read in batches and awaited once per batch: every s_waitcnt costs the
       // wave an issue slot, and the other waves of the SIMD cover the LDS latency
       const unsigned char* kb = smem + kslot * T::kBytes;
-      if constexpr (kLean) asm volatile("" : "+v"(kfrag[0]));  // keeps the XORs in the loop (hoisted, they are the table again)
-      constexpr int KB = WGS <= 2 ? KS : 1;  // k-steps per batch (register budget)
+      bf16x8 kf[KS][2];
 #pragma unroll
-      for (int t0 = 0; t0 < KS; t0 += KB) {
-        bf16x8 kf[KB][2];
+      for (int t = 0; t < KS; ++t)
 #pragma unroll
-        for (int t = 0; t < KB; ++t)
+        for (int mt = 0; mt < 2; ++mt)
+          kf[t][mt] = *reinterpret_cast<const bf16x8*>(kb + kfrag[t] + mt * 16 * T::kRowBytes);
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+      // the fences keep the batch together: reads, one wait, back-to-back MFMAs
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int mt = 0; mt < 2; ++mt)
-            kf[t][mt] = *reinterpret_cast<const bf16x8*>(kb + (kLean ? kfrag[0] ^ ((t0 + t) << 6) : kfrag[t0 + t]) +
-                                                         mt * 16 * T::kRowBytes);
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-        // the fences keep each batch together: reads, one wait, back-to-back MFMAs
-        __builtin_amdgcn_sched_barrier(0);
+      for (int t = 0; t < KS; ++t)
 #pragma unroll
-        for (int t = 0; t < KB; ++t)
+        for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-          for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-              set_quarter(s, 2 * mt + nt,
-                          __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][mt], qf[nt][t0 + t], quarter(s, 2 * mt + nt), 0, 0, 0));
-        __builtin_amdgcn_sched_barrier(0);
-      }
+          for (int nt = 0; nt < 2; ++nt)
+            set_quarter(s, 2 * mt + nt,
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][mt], qf[nt][t], quarter(s, 2 * mt + nt), 0, 0, 0));
+      __builtin_amdgcn_sched_barrier(0);
     }
-    // V(n) has landed; only the SLOTS-2 items requested after it may still be in flight (near the
+    // V(n) has landed; only the kSlots-2 items requested after it may still be in flight (near the
     // end of the list fewer are, so the last LEAD tiles simply wait for everything)
     // (raster mode: what this wave requested after V(n) is LEAD-1 whole tiles' worth of 2 kDma + 1
     // requests plus this tile's order and K requests)
@@ -512,7 +397,7 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
     else
       __builtin_amdgcn_s_waitcnt(0x0f70);
     __syncthreads();  // ... for every wave; and nobody reads K(n) any more
-    if (steady) issue_v(j_pre, kslot);  // item 2n+SLOTS = V(n+LEAD) takes K(n)'s slot
+    if (steady) issue_v(j_pre, kslot);  // item 2n+kSlots = V(n+LEAD) takes K(n)'s slot
     // block ids for the next iteration: shift the queue and append tile n+1+LEAD
     const int nk = nkq[0];
 #pragma unroll
@@ -597,30 +482,25 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
     // ---- O^T += V^T P^T: one MFMA per (d sub-tile, query tile), its 32 contraction slots = this wave's keys ----
     {
       const unsigned char* vb = smem + vslot * T::kBytes;
-      if constexpr (kLean) asm volatile("" : "+v"(vfrag[0]));
-      constexpr int VB = WGS <= 2 ? DT : 2;  // d sub-tiles per batch
+      bf16x8 vf[DT];
 #pragma unroll
-      for (int dt0 = 0; dt0 < DT; dt0 += VB) {
-        bf16x8 vf[VB];
-#pragma unroll
-        for (int dd = 0; dd < VB; ++dd) {
-          const unsigned char* p = vb + (kLean ? vfrag[0] ^ ((dt0 + dd) << 5) : vfrag[dt0 + dd]);
-          const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)p);
-          const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (short4v __attribute__((address_space(3)))*)(p + 16 * T::kRowBytes));
-          const short8v both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          __builtin_memcpy(&vf[dd], &both, sizeof(bf16x8));
-        }
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int dd = 0; dd < VB; ++dd)
-#pragma unroll
-          for (int nt = 0; nt < 2; ++nt)
-            set_quarter(o[nt][(dt0 + dd) >> 2], (dt0 + dd) & 3,
-                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dd], pf[nt], quarter(o[nt][(dt0 + dd) >> 2], (dt0 + dd) & 3), 0, 0, 0));
-        __builtin_amdgcn_sched_barrier(0);
+      for (int dt = 0; dt < DT; ++dt) {
+        const unsigned char* p = vb + vfrag[dt];
+        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)p);
+        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (short4v __attribute__((address_space(3)))*)(p + 16 * T::kRowBytes));
+        const short8v both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        __builtin_memcpy(&vf[dt], &both, sizeof(bf16x8));
       }
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+          set_quarter(o[nt][dt >> 2], dt & 3,
+                      __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pf[nt], quarter(o[nt][dt >> 2], dt & 3), 0, 0, 0));
+      __builtin_amdgcn_sched_barrier(0);
     }
 
     // pin each accumulator tuple to one 16-register unit once per tile (see quarter())
@@ -629,7 +509,7 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
 #pragma unroll
       for (int k = 0; k < OT; ++k) asm volatile("" : "+v"(o[nt][k]));
 
-    // K(n+1) has landed; again at most SLOTS-2 younger items are in flight
+    // K(n+1) has landed; again at most kSlots-2 younger items are in flight
     constexpr int kEndWait = RASTER ? (LEAD - 1) * (2 * kDma + 1) + kDma : (kSlots - 2) * kDma;
     if (RASTER ? decltype(steady_c)::value : steady)
       __builtin_amdgcn_s_waitcnt(0x0f70 | kEndWait);
@@ -641,31 +521,16 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
     using P0 = std::integral_constant<int, 0>;
     using P1 = std::integral_constant<int, 1>;
     using P2 = std::integral_constant<int, 2>;
-    using P3 = std::integral_constant<int, 3>;
-    using P4 = std::integral_constant<int, 4>;
     int n = 0;
     for (; n + kSlots + LEAD <= n_list; n += kSlots) {  // whole rounds of the ring, no end-of-list checks
       tile_step(P0{}, std::true_type{}, n);
       tile_step(P1{}, std::true_type{}, n + 1);
       tile_step(P2{}, std::true_type{}, n + 2);
-      if constexpr (kSlots >= 5) {
-        tile_step(P3{}, std::true_type{}, n + 3);
-        tile_step(P4{}, std::true_type{}, n + 4);
-      }
     }
-    // the last, partial round (n is a multiple of SLOTS here, so the phases line up)
+    // the last, partial round (n is a multiple of kSlots here, so the phases line up)
     if (n < n_list) tile_step(P0{}, std::false_type{}, n);
     if (n + 1 < n_list) tile_step(P1{}, std::false_type{}, n + 1);
     if (n + 2 < n_list) tile_step(P2{}, std::false_type{}, n + 2);
-    if constexpr (kSlots >= 5) {
-      if (n + 3 < n_list) tile_step(P3{}, std::false_type{}, n + 3);
-      if (n + 4 < n_list) tile_step(P4{}, std::false_type{}, n + 4);
-    }
-    // up to SLOTS + LEAD - 1 tiles can remain: LEAD - 1 more
-    static_assert(LEAD <= 2, "one extra tile after the partial round");
-    if constexpr (LEAD == 2) {
-      if (n + kSlots < n_list) tile_step(P0{}, std::false_type{}, n + kSlots);
-    }
   }
 
   // ---- merge the two key halves, stage the block row-major in LDS, store coalesced ----------
@@ -744,18 +609,10 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
       const int row = id / (D / 4), c4 = (id % (D / 4)) * 4;
       float4 val = *reinterpret_cast<const float4*>(stage + (row >> 5) * (XROWS * 64) + (row & 31) * OSTRIDE + c4);
       if (fuse.coarse && row < nq) {
-        // second branch folded into the store: out = gate_fine * attention + gate_coarse * cube-level row of this cube
-        const float4 cz = *reinterpret_cast<const float4*>(fuse.coarse + (head * nb + i) * (long long)D + c4);
-        float4 gf = make_float4(1.f, 1.f, 1.f, 1.f), gc = gf;
-        long long gate_off = blk_off + row * D + c4;  // in elements
+        long long gate_off = blk_off + row * D + c4;
         if constexpr (RASTER)  // the gates are raster tensors laid out like q
           gate_off = (ras_off + (long long)ras.order[i * kBlock + row] * ras.tok) / 2 + c4;
-        if (fuse.gate_fine) gf = load_bf16x4(fuse.gate_fine + gate_off);
-        if (fuse.gate_coarse) gc = load_bf16x4(fuse.gate_coarse + gate_off);
-        val.x = fmaf(gf.x, val.x, gc.x * cz.x);
-        val.y = fmaf(gf.y, val.y, gc.y * cz.y);
-        val.z = fmaf(gf.z, val.z, gc.z * cz.z);
-        val.w = fmaf(gf.w, val.w, gc.w * cz.w);
+        fuse4(val, fuse, (head * nb + i) * (long long)D + c4, gate_off);
       }
       void* dst;
       if constexpr (RASTER) {
@@ -763,94 +620,44 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
         dst = static_cast<unsigned char*>(out) + ras_out + (long long)ras.order[i * kBlock + row] * ras.o_tok +
               c4 * (OUT_F32 ? 4 : 2);
       } else {
-        dst = OUT_F32 ? static_cast<void*>(static_cast<float*>(out) + blk_off + row * D + c4)
-                      : static_cast<void*>(static_cast<uint16_t*>(out) + blk_off + row * D + c4);
+        dst = static_cast<unsigned char*>(out) + (blk_off + row * D + c4) * (OUT_F32 ? 4 : 2);
       }
-      // stream_out (the launcher's choice, the same for every workgroup): streaming stores.  The output is not read
-      // again by this launch, and written the ordinary way its lines push K/V tiles out of the L2.
-      if (OUT_F32) {
-        f32x4 vv = {val.x, val.y, val.z, val.w};
-        if (stream_out)
-          __builtin_nontemporal_store(vv, reinterpret_cast<f32x4*>(dst));
-        else
-          *reinterpret_cast<f32x4*>(dst) = vv;
-      } else {
-        bf16x4 pk;
-        pk[0] = (__bf16)val.x; pk[1] = (__bf16)val.y; pk[2] = (__bf16)val.z; pk[3] = (__bf16)val.w;
-        if (stream_out)
-          __builtin_nontemporal_store(pk, reinterpret_cast<bf16x4*>(dst));
-        else
-          *reinterpret_cast<bf16x4*>(dst) = pk;
-      }
+      store4<OUT_F32>(dst, val, stream_out);
     }
   }
 }
 
-template <int D, bool OUT_F32, int SLOTS, int WGS, bool RASTER = false>
-hipError_t run(const void* q, const void* k, const void* v, const Dims& s, const int32_t* idx, const int32_t* cnt,
-               int kmax, float scale, void* out, float* lse, const FuseArgs& fuse, hipStream_t st,
-               const RasterArgs& ras = RasterArgs{}, const int32_t* work_order = nullptr) {
+template <int D, bool OUT_F32, bool RASTER>
+hipError_t run(const AttnBf16Args& a, hipStream_t st) {
+  const Dims& s = a.s;
   const long long total = s.bh() * s.nb;
+  // The wide kernel puts four two-wave workgroups on a CU at d = 128 (six at d = 64), this one two of four waves, each
+  // twice as fast through its list, so 1024 (1536) or 512 query blocks make a round of the chip.  Below a full round of
+  // the wide kernel, and where it would leave half of its second one empty, this one is faster; measured, this one / wide:
+  //   d = 128, 25 listed: 512 blocks 38 / 54 us, 768: 58.6 / 58.5 (51 listed: 99 / 107), 1024: 69.7 / 66.2, 1536: 113 / 117
+  //   (51 listed: 202 / 216), 2048: 160 / 151; 8 listed: 768 blocks 27.5 / 28.7, 1024: 32.8 / 31.2, 1536: 47 / 52
+  //   d = 64 (half the matrix work per fetched byte and per exponential), 25 listed: 1024 blocks 41.4 / 42.0 us, 1536: 57.7 /
+  //   58.0, 2048: 74 / 85, 2560: 92 / 100, 5120: 213 / 213, 6144 (51 listed): 408 / 385
+  const bool wide = D == 128 ? (total > 768 && total <= 1024) || total > 1536 : total > 4608;
+  if (wide) return launch_attn_wide(a, OUT_F32, st);
   const int per_xcd = (int)((total + kNumXcd - 1) / kNumXcd);
-  const unsigned grid = (unsigned)per_xcd * kNumXcd;
-  const float sl2 = scale * kLog2e;
-  // tau = 2^-(kDropLog2 + ceil(log2(keys of the longest list))), p_shift = 126 + log2(tau), kept within [64, 110]
-  int bits = 0;
-  while ((1LL << bits) < (long long)kmax * kBlock) ++bits;
-  const float p_shift = (float)(126 - kDropLog2 - bits < 64 ? 64 : 126 - kDropLog2 - bits > 110 ? 110 : 126 - kDropLog2 - bits);
-  auto Q = static_cast<const uint16_t*>(q);
-  auto K = static_cast<const uint16_t*>(k);
-  auto V = static_cast<const uint16_t*>(v);
-  // Streaming output stores where the L2 has something to lose: measured -1 % at the 480p shape (a head's K and V:
-  // 16.8 MB), -2.7 % with ragged budgets at 16384 tokens, nothing on dense lists, but +4.4 % at the 720p shape
-  // (38.7 MB per head: the L2 serves a quarter of the tile requests there whatever the output does, and the launch
-  // runs at the limit of the fabric, which ordinary stores load more evenly).
-  const int stream_out = 2LL * s.nb * kBlock * D * 2 <= (32LL << 20);
-  attn_bf16<D, OUT_F32, SLOTS, WGS, RASTER><<<grid, kThreads, 0, st>>>(Q, K, V, idx, cnt, out, lse, s.nb, s.Nv, kmax, sl2,
-                                                                     p_shift, (int)total, per_xcd, fuse, ras, work_order,
-                                                                     stream_out);
+  attn_bf16<D, OUT_F32, RASTER><<<(unsigned)per_xcd * kNumXcd, kThreads, 0, st>>>(
+      static_cast<const uint16_t*>(a.q), static_cast<const uint16_t*>(a.k), static_cast<const uint16_t*>(a.v), a.idx, a.cnt,
+      a.out, a.lse, s.nb, s.Nv, a.kmax, a.scale * kLog2e, probability_shift(a.kmax), (int)total, per_xcd, a.fuse, a.ras,
+      a.work_order, stream_output(s));
   return hipGetLastError();
+}
+
+template <bool RASTER>
+hipError_t dispatch(const AttnBf16Args& a, bool out_f32, hipStream_t st) {
+  if (a.s.d == 128) return out_f32 ? run<128, true, RASTER>(a, st) : run<128, false, RASTER>(a, st);
+  return out_f32 ? run<64, true, RASTER>(a, st) : run<64, false, RASTER>(a, st);
 }
 
 }  // namespace
 
-hipError_t launch_attn_bf16(const void* q, const void* k, const void* v, const Dims& s, const int32_t* idx,
-                            const int32_t* cnt, int kmax, float scale, void* out, bool out_f32, float* lse,
-                            const FuseArgs& fuse, hipStream_t st, const int32_t* work_order) {
-  // Two launch shapes, both with a 3-slot ring (48 KiB at d = 128), chosen by measurement at the 480p shape:
-  //   sparse lists: 2 workgroups per CU with the whole register file between them, so that every fragment
-  //     of a tile is read in one batch (a 5-slot ring that requests tiles two iterations ahead was 1 % slower
-  //     at 51, 25 and ragged 8..64 blocks and at the 720p shape; 3 workgroups per CU with the small batches
-  //     their 168 registers allow was 19 % slower);
-  //   dense-like lists (at least half of the blocks kept, so neighbouring query blocks share most
-  //     tiles and L2 serves them): 3 workgroups per CU, for the extra wave per SIMD (2 % faster there).
-  const bool dense_like = 2 * (long long)kmax >= s.nb;
-#define USV_ATTN_CASE(DD, F32)                                                                         \
-  return dense_like ? run<DD, F32, 3, 3>(q, k, v, s, idx, cnt, kmax, scale, out, lse, fuse, st, RasterArgs{}, work_order) \
-                    : run<DD, F32, 3, 2>(q, k, v, s, idx, cnt, kmax, scale, out, lse, fuse, st, RasterArgs{}, work_order)
-  if (s.d == 128) {
-    if (out_f32) USV_ATTN_CASE(128, true);
-    USV_ATTN_CASE(128, false);
-  }
-  if (out_f32) USV_ATTN_CASE(64, true);
-  USV_ATTN_CASE(64, false);
-#undef USV_ATTN_CASE
-}
-
-// Raster-order tensors: the sparse shape (3-slot ring, 2 workgroups per CU) plus the order ring.
-hipError_t launch_attn_bf16_raster(const void* q, const void* k, const void* v, const Dims& s, const RasterArgs& ras,
-                                   const int32_t* idx, const int32_t* cnt, int kmax, float scale, void* out,
-                                   bool out_f32, float* lse, const FuseArgs& fuse, hipStream_t st,
-                                   const int32_t* work_order) {
-#define USV_RASTER_CASE(DD, F32) \
-  return run<DD, F32, 3, 2, true>(q, k, v, s, idx, cnt, kmax, scale, out, lse, fuse, st, ras, work_order)
-  if (s.d == 128) {
-    if (out_f32) USV_RASTER_CASE(128, true);
-    USV_RASTER_CASE(128, false);
-  }
-  if (out_f32) USV_RASTER_CASE(64, true);
-  USV_RASTER_CASE(64, false);
-#undef USV_RASTER_CASE
+hipError_t launch_attn_bf16(const AttnBf16Args& a, bool out_f32, hipStream_t st) {
+  return a.ras.order ? dispatch<true>(a, out_f32, st) : dispatch<false>(a, out_f32, st);
 }
 
 }  // namespace usv

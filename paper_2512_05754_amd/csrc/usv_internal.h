@@ -74,14 +74,22 @@ struct RasterArgs {
 // ras == nullptr: cube-major Q, K
 hipError_t launch_block_scores(const void* q, const void* k, const Dims& s, float* scores, float* ws,
                                hipStream_t st, const RasterArgs* ras = nullptr);
-hipError_t launch_attn_bf16_raster(const void* q, const void* k, const void* v, const Dims& s, const RasterArgs& ras,
-                                   const int32_t* idx, const int32_t* cnt, int kmax, float scale, void* out,
-                                   bool out_f32, float* lse, const FuseArgs& fuse, hipStream_t st,
-                                   const int32_t* work_order = nullptr);
+// ras.order == nullptr: cube-major tensors.
 // work_order == nullptr: workgroup slot s of a head takes query block s; otherwise block work_order[head * nb + s]
-hipError_t launch_attn_bf16(const void* q, const void* k, const void* v, const Dims& s, const int32_t* idx,
-                            const int32_t* cnt, int kmax, float scale, void* out, bool out_f32, float* lse,
-                            const FuseArgs& fuse, hipStream_t st, const int32_t* work_order = nullptr);
+struct AttnBf16Args {
+  const void *q, *k, *v;
+  Dims s;
+  const int32_t *idx, *cnt;
+  int kmax;
+  float scale;
+  void* out;
+  float* lse;
+  FuseArgs fuse;
+  RasterArgs ras;
+  const int32_t* work_order;
+};
+hipError_t launch_attn_bf16(const AttnBf16Args& a, bool out_f32, hipStream_t st);  // picks the kernel by the grid's size
+hipError_t launch_attn_wide(const AttnBf16Args& a, bool out_f32, hipStream_t st);  // the one for grids that fill the chip
 hipError_t launch_attn_work_order(const int32_t* idx, const int32_t* cnt, const Dims& s, int kmax, int32_t* work_order,
                                   hipStream_t st);  // idx == nullptr: by list length only
 

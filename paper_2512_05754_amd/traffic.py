@@ -24,10 +24,11 @@ ROOT = os.path.dirname(PKG_DIR)
 PATH = os.path.join(ROOT, "profiles", "traffic.json")
 
 # kernel sources behind each kind of entry (the entry name's prefix before ':' picks the kind)
+_ATTN = ("usv_attn_bf16.hip", "usv_attn_wide.hip", "usv_attn_bf16.h", "usv_internal.h")
 SOURCES = {
-    "attention": ("usv_attn_bf16.hip", "usv_internal.h"),
-    "raster": ("usv_attn_bf16.hip", "usv_internal.h"),
-    "cubes": ("usv_attn_bf16.hip", "usv_internal.h"),
+    "attention": _ATTN,
+    "raster": _ATTN,
+    "cubes": _ATTN,
     "reorder": ("usv_reorder.hip", "usv_internal.h"),
     "merge": ("usv_merge.hip", "usv_internal.h"),
 }

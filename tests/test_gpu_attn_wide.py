@@ -1,0 +1,57 @@
+"""The attention kernel for grids that fill the chip, at the edges of its ranges: the smallest grids it takes, lists around the
+64 entries one register holds, sweeps that start inside the list (later rounds of a launch), the deeper request ring, ragged
+and empty lists, lists in no order, both head dimensions.  Sampled query blocks against the oracle, at the bf16 bound."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as gu
+from paper_2512_05754_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# (batch, heads, blocks, head_dim, kmax, ragged): what the case is there for
+CASES = [
+    (1, 7, 110, 128, 18, False),    # 770 blocks: one round, every list starts at its first entry
+    (1, 8, 128, 128, 128, False),   # exactly one round, every block listed
+    (1, 22, 70, 128, 11, False),    # just above one and a half rounds; later lists start inside
+    (1, 4, 390, 128, 64, False),    # 64 entries: the whole list in one register
+    (1, 4, 390, 128, 65, False),    # ... and one more
+    (1, 2, 900, 128, 130, False),   # more than 128 entries, one head's K and V 29 MB: the deeper ring
+    (1, 3, 800, 128, 3, True),      # deeper ring, lists of 0 to 3 entries
+    (2, 12, 70, 128, 9, True),      # ragged, empty lists among them
+    (1, 47, 101, 64, 16, False),    # d = 64, four rounds
+    (1, 12, 400, 64, 66, True),     # d = 64, ragged, up to 66 entries
+]
+
+
+@pytest.mark.parametrize("B,Hh,nb,d,kmax,ragged", CASES)
+@pytest.mark.parametrize("ordered", [False, True])
+def test_wide_grids_against_the_oracle(usv, B, Hh, nb, d, kmax, ragged, ordered):
+    w = synth.Workload("wide", B, Hh, nb * 64 - 23, d, "bf16", 2.0, kmax, seed=7000 + nb + kmax)
+    Q, K, V = synth.gen_qkv(w)
+    q, k, v = gu.up(Q), gu.up(K), gu.up(V)
+    rng = np.random.default_rng(nb * 1000 + kmax)
+    cnt = rng.integers(0, kmax + 1, size=(B, Hh, nb)).astype(np.int32) if ragged else np.full((B, Hh, nb), kmax, np.int32)
+    scores = rng.random((B, Hh, nb, nb), dtype=np.float32)
+    idx = np.sort(np.argsort(scores, axis=-1)[..., :kmax], axis=-1).astype(np.int32)
+    idx[0, 0] = rng.permuted(idx[0, 0], axis=-1)  # one head's lists in no order
+    idx[np.arange(kmax) >= cnt[..., None]] = -1
+    wo = usv.attn_work_order(gu.up(cnt), kmax, idx=gu.up(idx)) if ordered else None
+    out, lse = usv.block_sparse_attn(q, k, v, gu.up(idx), gu.up(cnt), seq_valid=w.seq_valid, return_lse=True,
+                                     out_dtype=torch.float32, work_order=wo)
+    out16 = usv.block_sparse_attn(q, k, v, gu.up(idx), gu.up(cnt), seq_valid=w.seq_valid, work_order=wo)
+    gu.assert_bf16_store_is_rne(out16, out, "wide")
+    o_h, l_h = gu.down(out), gu.down(lse)
+    assert np.isfinite(o_h).all()
+    # blocks of the first, a middle and the last round of the first, a middle and the last XCD, and the partial block
+    flat = [int(x) for x in np.linspace(0, B * Hh * nb - 1, 17)] + [B * Hh * nb - 2]
+    for f in flat:
+        b, h, i = f // (Hh * nb), f // nb % Hh, f % nb
+        ref_o, ref_l = gu.oracle_attn_blocks(Q[b, h], K[b, h], V[b, h], idx[b, h], cnt[b, h], w.seq_valid, [i])[i]
+        what = f"head {b},{h} block {i} ({cnt[b, h, i]} listed)"
+        gu.assert_attn_close(o_h[b, h, i * 64:(i + 1) * 64], ref_o, "bf16", what)
+        live = np.isfinite(ref_l)
+        got = l_h[b, h, i * 64:(i + 1) * 64]
+        assert np.array_equal(np.isneginf(got), ~live), what
+        assert not live.any() or np.abs(got[live] - ref_l[live]).max() <= 2e-2, what
