@@ -14,7 +14,12 @@
 // operands as contiguous 16-byte pieces), in the second the step r takes, in half g, exactly the
 // key that accumulator register r of that half holds, so P^T needs no data movement at all.
 // K and V tiles are staged in LDS as fp32 (rows padded by 4 floats), single-buffered: the kernel is
-// bound by the fp32 matrix pipe (128 MFMAs of 64 clocks per wave and tile), not by the staging.
+// bound by the fp32 matrix pipe (128 MFMAs of 64 clocks per wave and tile), as long as a second workgroup
+// on the CU computes while one stages.  That takes 256 registers a wave: the partial accumulators of the first
+// product are formed and folded two at a time (2 heads, 32768 tokens, 51 of 512 blocks: 1.13 -> 0.94 ms = 117
+// TFLOP/s, against all four at once, 362 registers and one workgroup per CU; the same bits).
+#include <type_traits>
+
 #include "usv_internal.h"
 
 namespace usv {
@@ -31,7 +36,7 @@ __device__ __forceinline__ void both_halves(float x, float& lo, float& hi) {
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void attn_f32(const float* __restrict__ q, const float* __restrict__ k,
+__global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, const float* __restrict__ k,
                                                 const float* __restrict__ v, const int32_t* __restrict__ idx,
                                                 const int32_t* __restrict__ cnt, float* __restrict__ out,
                                                 float* __restrict__ lse, int nb, int Nv, int kmax, float scale_log2e) {
@@ -87,27 +92,41 @@ __global__ __launch_bounds__(256) void attn_f32(const float* __restrict__ q, con
     __syncthreads();
 
     // ---- S^T = K Q^T over this wave's 32 keys -------------------------------------------------
-    // Four accumulators, a quarter of the channel steps each, added at the end: the logits reach several
+    // Four partial sums, a quarter of the channel steps each, added pairwise: the logits reach several
     // hundred before scaling, and a single 64-step fp32 chain rounds them too coarsely for the 1e-5 bound.
     f32x16 s;
     {
-      f32x16 sp[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sp[a][r] = 0.f;
       const float* kr = Ks + (kh * 32 + col) * LD + g * HALF;
+      auto quarter = [&](auto a_c) {  // channel steps a * HALF / 4 .. of the product
+        constexpr int A = decltype(a_c)::value;
+        f32x16 p;
 #pragma unroll
-      for (int t = 0; t < HALF; t += 4) {
-        const int a = t / (HALF / 4);
-        const float4 kv = *reinterpret_cast<const float4*>(kr + t);
-        sp[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(kv.x, qf[t], sp[a], 0, 0, 0);
-        sp[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(kv.y, qf[t + 1], sp[a], 0, 0, 0);
-        sp[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(kv.z, qf[t + 2], sp[a], 0, 0, 0);
-        sp[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(kv.w, qf[t + 3], sp[a], 0, 0, 0);
-      }
+        for (int r = 0; r < 16; ++r) p[r] = 0.f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = (sp[0][r] + sp[1][r]) + (sp[2][r] + sp[3][r]);
+        for (int t = A * (HALF / 4); t < (A + 1) * (HALF / 4); t += 4) {
+          const float4 kv = *reinterpret_cast<const float4*>(kr + t);
+          p = __builtin_amdgcn_mfma_f32_32x32x2f32(kv.x, qf[t], p, 0, 0, 0);
+          p = __builtin_amdgcn_mfma_f32_32x32x2f32(kv.y, qf[t + 1], p, 0, 0, 0);
+          p = __builtin_amdgcn_mfma_f32_32x32x2f32(kv.z, qf[t + 2], p, 0, 0, 0);
+          p = __builtin_amdgcn_mfma_f32_32x32x2f32(kv.w, qf[t + 3], p, 0, 0, 0);
+        }
+        return p;
+      };
+      auto add = [](const f32x16& x, const f32x16& y) {
+        f32x16 z;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z[r] = x[r] + y[r];
+        return z;
+      };
+      using Q0 = std::integral_constant<int, 0>;
+      using Q1 = std::integral_constant<int, 1>;
+      using Q2 = std::integral_constant<int, 2>;
+      using Q3 = std::integral_constant<int, 3>;
+      f32x16 lo = quarter(Q0{});
+      lo = add(lo, quarter(Q1{}));
+      __builtin_amdgcn_sched_barrier(0);
+      f32x16 hi = quarter(Q2{});
+      s = add(lo, add(hi, quarter(Q3{})));
     }
     // register r of lane (col, g) is key 32 kh + 8 (r/4) + 4 g + (r%4) of the tile, query col
     const int nkeys = Nv - j * kBlock;  // valid keys of the tile (>= 64 except in the last, partial block)
