@@ -39,5 +39,6 @@ def __getattr__(name):
     if name in _BINDING_NAMES:
         from . import binding
 
-        return getattr(binding, name)
+        value = globals()[name] = getattr(binding, name)  # looked up once
+        return value
     raise AttributeError(name)

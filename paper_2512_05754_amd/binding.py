@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+from functools import lru_cache
 
 import torch
 
@@ -166,7 +167,17 @@ def _dev(t: torch.Tensor, name: str, dtype=None):
     return t.data_ptr()
 
 
-def _shape_of(x: torch.Tensor, seq_valid) -> UsvShape:
+# A small call is a few microseconds of kernels, so the marshalling counts: the argument structs of a shape are built once
+# (plain values, never written afterwards), and the stream handle is read without building a torch.cuda.Stream (0.2 instead
+# of 3 us).  Together with module attributes that are looked up once: three stages on 1024 tokens 29 -> 19.5 us on the host.
+@lru_cache(maxsize=1024)
+def _shape(batch, heads, seq_len, seq_valid, head_dim, dtype):
+    """(UsvShape, reference to it)."""
+    sh = UsvShape(batch, heads, seq_len, seq_valid, head_dim, BLOCK, dtype)
+    return sh, ctypes.byref(sh)
+
+
+def _shape_of(x: torch.Tensor, seq_valid):
     if x.dim() != 4:
         raise ValueError("Q/K/V must be [B, Hh, N, d]")
     if x.dtype == torch.bfloat16:
@@ -176,33 +187,42 @@ def _shape_of(x: torch.Tensor, seq_valid) -> UsvShape:
     else:
         raise TypeError(f"unsupported dtype {x.dtype}")
     B, Hh, N, d = x.shape
-    return UsvShape(B, Hh, N, N if seq_valid is None else int(seq_valid), d, BLOCK, dt)
+    return _shape(B, Hh, N, N if seq_valid is None else int(seq_valid), d, dt)
 
 
-def _stream() -> int:
+def _stream_public() -> int:
     return torch.cuda.current_stream().cuda_stream
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _stream_raw() -> int:
+    return _raw_stream(_current_device())
+
+
+_stream = _stream_public if _raw_stream is None or _current_device is None else _stream_raw
 
 
 def workspace_bytes(batch, heads, seq_len, seq_valid, head_dim, dtype) -> int:
     dt = USV_BF16 if dtype in (torch.bfloat16, "bf16") else USV_F32
-    sh = UsvShape(batch, heads, seq_len, seq_valid, head_dim, BLOCK, dt)
-    return int(lib().usv_workspace_bytes(ctypes.byref(sh)))
+    return int(lib().usv_workspace_bytes(_shape(batch, heads, seq_len, seq_valid, head_dim, dt)[1]))
 
 
 def block_scores(q, k, seq_valid=None, out=None, workspace=None):
     """usv_block_scores: pooled block scores [B, Hh, nb, nb] fp32 of Q, K [B, Hh, N, d]."""
-    sh = _shape_of(q, seq_valid)
+    sh, shp = _shape_of(q, seq_valid)
     if k.shape != q.shape or k.dtype != q.dtype:
         raise ValueError("k must match q in shape and dtype")
     nb = sh.seq_len // BLOCK
     if out is None:
         out = torch.empty((sh.batch, sh.heads, nb, nb), dtype=torch.float32, device=q.device)
-    need = int(lib().usv_workspace_bytes(ctypes.byref(sh)))
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(max(int(lib().usv_workspace_bytes(shp)), 16), dtype=torch.uint8, device=q.device)
     _check(
         lib().usv_block_scores(
-            _dev(q, "q"), _dev(k, "k"), ctypes.byref(sh), _dev(out, "scores", torch.float32),
+            _dev(q, "q"), _dev(k, "k"), shp, _dev(out, "scores", torch.float32),
             _dev(workspace, "workspace"), workspace.numel() * workspace.element_size(), _stream(),
         )
     )
@@ -211,13 +231,13 @@ def block_scores(q, k, seq_valid=None, out=None, workspace=None):
 
 def block_scores_static(q, k, out, seq_valid=None):
     """usv_block_scores_static: stage 1 without a workspace; `out` [B, Hh, nb, nb] fp32 is the caller's."""
-    sh = _shape_of(q, seq_valid)
+    sh, shp = _shape_of(q, seq_valid)
     if k.shape != q.shape or k.dtype != q.dtype:
         raise ValueError("k must match q in shape and dtype")
     nb = sh.seq_len // BLOCK
     if tuple(out.shape) != (sh.batch, sh.heads, nb, nb):
         raise ValueError("out must be [B, Hh, nb, nb]")
-    _check(lib().usv_block_scores_static(_dev(q, "q"), _dev(k, "k"), ctypes.byref(sh),
+    _check(lib().usv_block_scores_static(_dev(q, "q"), _dev(k, "k"), shp,
                                          _dev(out, "scores", torch.float32), _stream()))
     return out
 
@@ -233,7 +253,7 @@ def select_topk(scores, k=0, seq_valid=None, budgets=None, kmax=None, idx=None, 
         raise ValueError("scores must be [B, Hh, nb, nb]")
     B, Hh, nb, _ = scores.shape
     N = nb * BLOCK
-    sh = UsvShape(B, Hh, N, N if seq_valid is None else int(seq_valid), 0, BLOCK, USV_F32)
+    shp = _shape(B, Hh, N, N if seq_valid is None else int(seq_valid), 0, USV_F32)[1]
     if kmax is None:
         kmax = int(k)
     if idx is None:
@@ -241,7 +261,7 @@ def select_topk(scores, k=0, seq_valid=None, budgets=None, kmax=None, idx=None, 
     if cnt is None:
         cnt = torch.empty((B, Hh, nb), dtype=torch.int32, device=scores.device)
     bptr = None if budgets is None else _dev(budgets, "budgets", torch.int32)
-    args = (_dev(scores, "scores", torch.float32), ctypes.byref(sh), int(k), bptr, int(kmax))
+    args = (_dev(scores, "scores", torch.float32), shp, int(k), bptr, int(kmax))
     outs = (_dev(idx, "idx", torch.int32), _dev(cnt, "cnt", torch.int32), _stream())
     if force_local:
         _check(lib().usv_select_topk_ex(*args, TOPK_FORCE_LOCAL, *outs))
@@ -254,13 +274,13 @@ def attn_work_order(cnt, kmax, idx=None, out=None):
     """usv_attn_work_order: per head, the query blocks sorted by (list length descending, where the list lies
     [needs idx], block index) -> int32 [B, Hh, nb]."""
     B, Hh, nb = cnt.shape
-    sh = UsvShape(B, Hh, nb * BLOCK, nb * BLOCK, 0, BLOCK, USV_F32)
+    shp = _shape(B, Hh, nb * BLOCK, nb * BLOCK, 0, USV_F32)[1]
     if out is None:
         out = torch.empty((B, Hh, nb), dtype=torch.int32, device=cnt.device)
     if idx is not None and (tuple(idx.shape[:3]) != (B, Hh, nb) or idx.shape[3] != kmax):
         raise ValueError("idx must be [B, Hh, nb, kmax]")
     _check(lib().usv_attn_work_order(None if idx is None else _dev(idx, "idx", torch.int32), _dev(cnt, "cnt", torch.int32),
-                                     ctypes.byref(sh), int(kmax), _dev(out, "work_order", torch.int32), _stream()))
+                                     shp, int(kmax), _dev(out, "work_order", torch.int32), _stream()))
     return out
 
 
@@ -271,7 +291,7 @@ def block_sparse_attn(q, k, v, idx, cnt, seq_valid=None, scale=0.0, out=None, ls
     out_dtype: dtype of the result; defaults to q's dtype, torch.float32 is also allowed for bf16 inputs.
     coarse (+ optional gates): usv_block_sparse_attn_fused, out = gate_fine * attention + gate_coarse * coarse[cube].
     work_order (from attn_work_order): usv_block_sparse_attn_ordered, the launch walks the query blocks in that order."""
-    sh = _shape_of(q, seq_valid)
+    sh, shp = _shape_of(q, seq_valid)
     for name, t in (("k", k), ("v", v)):
         if t.shape != q.shape or t.dtype != q.dtype:
             raise ValueError(f"{name} must match q in shape and dtype")
@@ -290,7 +310,7 @@ def block_sparse_attn(q, k, v, idx, cnt, seq_valid=None, scale=0.0, out=None, ls
     odt = USV_F32 if out.dtype == torch.float32 else USV_BF16
     if lse is None and return_lse:
         lse = torch.empty((sh.batch, sh.heads, sh.seq_len), dtype=torch.float32, device=q.device)
-    head = (_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), ctypes.byref(sh), _dev(idx, "idx", torch.int32),
+    head = (_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), shp, _dev(idx, "idx", torch.int32),
             _dev(cnt, "cnt", torch.int32), int(kmax), float(scale))
     tail = (odt, _dev(out, "out"), None if lse is None else _dev(lse, "lse", torch.float32), _stream())
     if work_order is not None:
@@ -312,8 +332,16 @@ def block_sparse_attn(q, k, v, idx, cnt, seq_valid=None, scale=0.0, out=None, ls
     return (out, lse) if return_lse else out
 
 
-def _grid(grid, cube) -> UsvGrid:
-    return UsvGrid(*(int(x) for x in grid), *(int(x) for x in cube))
+@lru_cache(maxsize=1024)
+def _grid_of(T, H, W, ct, ch, cw):
+    return ctypes.byref(UsvGrid(T, H, W, ct, ch, cw))
+
+
+def _grid(grid, cube):
+    """Reference to the UsvGrid."""
+    T, H, W = grid
+    ct, ch, cw = cube
+    return _grid_of(int(T), int(H), int(W), int(ct), int(ch), int(cw))
 
 
 def cube_token_order(grid, cube=(4, 4, 4)):
@@ -322,8 +350,13 @@ def cube_token_order(grid, cube=(4, 4, 4)):
 
     g = _grid(grid, cube)
     order = np.full(max(int(grid[0]) * int(grid[1]) * int(grid[2]), 1), -1, dtype=np.int32)
-    _check(lib().usv_cube_token_order(ctypes.byref(g), order.ctypes.data_as(ctypes.c_void_p)))
+    _check(lib().usv_cube_token_order(g, order.ctypes.data_as(ctypes.c_void_p)))
     return order
+
+
+@lru_cache(maxsize=1024)
+def _strides(batch, head, token):
+    return UsvStrides(batch, head, token)
 
 
 def _raster(t: torch.Tensor, name: str):
@@ -332,7 +365,7 @@ def _raster(t: torch.Tensor, name: str):
         raise TypeError(f"{name} must be a GPU tensor (there is no CPU path)")
     if t.dim() != 4 or t.stride(3) != 1:
         raise ValueError(f"{name} must be [B, Hh, Nv, d] with contiguous channels")
-    return t.data_ptr(), UsvStrides(t.stride(0), t.stride(1), t.stride(2))
+    return t.data_ptr(), _strides(t.stride(0), t.stride(1), t.stride(2))
 
 
 def cube_gather(raster, grid, cube=(4, 4, 4), seq_len=None, out=None):
@@ -344,10 +377,10 @@ def cube_gather(raster, grid, cube=(4, 4, 4), seq_len=None, out=None):
         out = torch.empty((B, Hh, seq_len, d), dtype=raster.dtype, device=raster.device)
     if tuple(out.shape) != (B, Hh, seq_len, d) or out.dtype != raster.dtype:
         raise ValueError("out must be [B, Hh, seq_len, d] of the input dtype")
-    sh = _shape_of(out, Nv)
+    shp = _shape_of(out, Nv)[1]
     ptr, st = _raster(raster, "raster")
     g = _grid(grid, cube)
-    _check(lib().usv_cube_gather(ptr, ctypes.byref(st), ctypes.byref(sh), ctypes.byref(g), _dev(out, "cube"), _stream()))
+    _check(lib().usv_cube_gather(ptr, ctypes.byref(st), shp, g, _dev(out, "cube"), _stream()))
     return out
 
 
@@ -359,10 +392,10 @@ def cube_scatter(cube_major, grid, cube=(4, 4, 4), out=None):
         out = torch.empty((B, Hh, Nv, d), dtype=cube_major.dtype, device=cube_major.device)
     if tuple(out.shape) != (B, Hh, Nv, d) or out.dtype != cube_major.dtype:
         raise ValueError("out must be [B, Hh, T*H*W, d] of the input dtype")
-    sh = _shape_of(cube_major, Nv)
+    shp = _shape_of(cube_major, Nv)[1]
     ptr, st = _raster(out, "raster")
     g = _grid(grid, cube)
-    _check(lib().usv_cube_scatter(_dev(cube_major, "cube"), ctypes.byref(sh), ctypes.byref(g), ptr, ctypes.byref(st), _stream()))
+    _check(lib().usv_cube_scatter(_dev(cube_major, "cube"), shp, g, ptr, ctypes.byref(st), _stream()))
     return out
 
 
@@ -376,16 +409,15 @@ def _dt(t: torch.Tensor) -> int:
 
 def coarse_attn(scores, v, seq_valid=None, out=None, workspace=None):
     """usv_coarse_attn: cube-level attention output [B, Hh, nb, d] fp32 from the block scores and V."""
-    sh = _shape_of(v, seq_valid)
+    sh, shp = _shape_of(v, seq_valid)
     nb = sh.seq_len // BLOCK
     if tuple(scores.shape) != (sh.batch, sh.heads, nb, nb):
         raise ValueError("scores must be [B, Hh, nb, nb]")
     if out is None:
         out = torch.empty((sh.batch, sh.heads, nb, sh.head_dim), dtype=torch.float32, device=v.device)
-    need = int(lib().usv_coarse_workspace_bytes(ctypes.byref(sh)))
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=v.device)
-    _check(lib().usv_coarse_attn(_dev(scores, "scores", torch.float32), _dev(v, "v"), ctypes.byref(sh),
+        workspace = torch.empty(max(int(lib().usv_coarse_workspace_bytes(shp)), 16), dtype=torch.uint8, device=v.device)
+    _check(lib().usv_coarse_attn(_dev(scores, "scores", torch.float32), _dev(v, "v"), shp,
                                  _dev(out, "coarse", torch.float32), _dev(workspace, "workspace"),
                                  workspace.numel() * workspace.element_size(), _stream()))
     return out
@@ -399,7 +431,7 @@ def fuse_outputs(fine, coarse, gate_fine=None, gate_coarse=None, seq_valid=None,
     for g in gates:
         if g.shape != fine.shape or g.dtype != gdt:
             raise ValueError("gates must have fine's shape and one dtype")
-    sh = UsvShape(B, Hh, N, N if seq_valid is None else int(seq_valid), d, BLOCK, USV_F32 if gdt == torch.float32 else USV_BF16)
+    shp = _shape(B, Hh, N, N if seq_valid is None else int(seq_valid), d, USV_F32 if gdt == torch.float32 else USV_BF16)[1]
     if tuple(coarse.shape) != (B, Hh, N // BLOCK, d):
         raise ValueError("coarse must be [B, Hh, nb, d]")
     if out is None:
@@ -409,7 +441,7 @@ def fuse_outputs(fine, coarse, gate_fine=None, gate_coarse=None, seq_valid=None,
     _check(lib().usv_fuse_outputs(_dev(fine, "fine"), _dt(fine), _dev(coarse, "coarse", torch.float32),
                                   None if gate_fine is None else _dev(gate_fine, "gate_fine"),
                                   None if gate_coarse is None else _dev(gate_coarse, "gate_coarse"),
-                                  ctypes.byref(sh), _dt(out), _dev(out, "out"), _stream()))
+                                  shp, _dt(out), _dev(out, "out"), _stream()))
     return out
 
 
@@ -419,13 +451,12 @@ def attn_entropy(scores, seq_valid=None, out=None, workspace=None):
         raise ValueError("scores must be [B, Hh, nb, nb]")
     B, Hh, nb, _ = scores.shape
     N = nb * BLOCK
-    sh = UsvShape(B, Hh, N, N if seq_valid is None else int(seq_valid), 0, BLOCK, USV_F32)
+    shp = _shape(B, Hh, N, N if seq_valid is None else int(seq_valid), 0, USV_F32)[1]
     if out is None:
         out = torch.empty((B,), dtype=torch.float32, device=scores.device)
-    need = int(lib().usv_entropy_workspace_bytes(ctypes.byref(sh)))
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=scores.device)
-    _check(lib().usv_attn_entropy(_dev(scores, "scores", torch.float32), ctypes.byref(sh), _dev(out, "entropy", torch.float32),
+        workspace = torch.empty(max(int(lib().usv_entropy_workspace_bytes(shp)), 16), dtype=torch.uint8, device=scores.device)
+    _check(lib().usv_attn_entropy(_dev(scores, "scores", torch.float32), shp, _dev(out, "entropy", torch.float32),
                                   _dev(workspace, "workspace"), workspace.numel() * workspace.element_size(), _stream()))
     return out
 
@@ -441,28 +472,27 @@ def entropy_allocate(entropy, rho_bar, gamma=1.0, rho_min=0.0, rho_max=1.0):
     return rho
 
 
-def _merge_shape(B, Hh, d, dtype, grid, r, seq_len=None) -> UsvShape:
-    """Shape of the MERGED tensors: seq_valid = T*H*W - r rows, padded to seq_len (default: next multiple of 64)."""
+def _merge_shape(B, Hh, d, dtype, grid, r, seq_len=None):
+    """(UsvShape, reference to it) of the MERGED tensors: seq_valid = T*H*W - r rows, padded to seq_len (default: next multiple of 64)."""
     n_valid = int(grid[0]) * int(grid[1]) * int(grid[2]) - int(r)
     if seq_len is None:
         seq_len = -(-n_valid // BLOCK) * BLOCK
-    return UsvShape(B, Hh, int(seq_len), n_valid, d, BLOCK, USV_BF16 if dtype == torch.bfloat16 else USV_F32)
+    return _shape(B, Hh, int(seq_len), n_valid, d, USV_BF16 if dtype == torch.bfloat16 else USV_F32)
 
 
 def merge_similarity(k, grid, mblock, out=None, blk=None, workspace=None):
     """usv_merge_similarity: K [B, Hh, T*H*W, d] in raster order -> (u [B, T*H*W] fp32, -inf at destinations;
     blk [T*H*W] int32, the partition: block rank, bit 31 at destinations)."""
     B, Hh, N, d = k.shape
-    sh = _merge_shape(B, Hh, d, k.dtype, grid, 0)
+    shp = _merge_shape(B, Hh, d, k.dtype, grid, 0)[1]
     g = _grid(grid, mblock)
     if out is None:
         out = torch.empty((B, N), dtype=torch.float32, device=k.device)
     if blk is None:
         blk = torch.empty((N,), dtype=torch.int32, device=k.device)
-    need = int(lib().usv_merge_workspace_bytes(ctypes.byref(sh), ctypes.byref(g)))
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=k.device)
-    _check(lib().usv_merge_similarity(_dev(k, "k"), ctypes.byref(sh), ctypes.byref(g), _dev(out, "u", torch.float32),
+        workspace = torch.empty(max(int(lib().usv_merge_workspace_bytes(shp, g)), 16), dtype=torch.uint8, device=k.device)
+    _check(lib().usv_merge_similarity(_dev(k, "k"), shp, g, _dev(out, "u", torch.float32),
                                       _dev(blk, "blk", torch.int32), _dev(workspace, "workspace"), workspace.numel(), _stream()))
     return out, blk
 
@@ -471,9 +501,9 @@ MERGE_PLAN_WIDE_TOKENS = 8192  # from here on merge_plan brings a workspace by i
 
 
 def merge_plan_workspace_bytes(B, grid, mblock, r) -> int:
-    sh = _merge_shape(B, 1, 64, torch.float32, grid, r)
+    shp = _merge_shape(B, 1, 64, torch.float32, grid, r)[1]
     g = _grid(grid, mblock)
-    return int(lib().usv_merge_plan_workspace_bytes(ctypes.byref(sh), ctypes.byref(g)))
+    return int(lib().usv_merge_plan_workspace_bytes(shp, g))
 
 
 def merge_plan(u, blk, grid, mblock, r, row_of=None, src_of=None, workspace=None):
@@ -482,20 +512,20 @@ def merge_plan(u, blk, grid, mblock, r, row_of=None, src_of=None, workspace=None
     workspace: uint8 device tensor of merge_plan_workspace_bytes(...) -> the selection is spread over the chip; False ->
     one workgroup per batch element; None -> a workspace is allocated from MERGE_PLAN_WIDE_TOKENS tokens on."""
     B, N = u.shape
-    sh = _merge_shape(B, 1, 64, torch.float32, grid, r)
+    shp = _merge_shape(B, 1, 64, torch.float32, grid, r)[1]
     g = _grid(grid, mblock)
     if row_of is None:
         row_of = torch.empty((B, N), dtype=torch.int32, device=u.device)
     if src_of is None:
         src_of = torch.empty((B, max(N - int(r), 1)), dtype=torch.int32, device=u.device)[:, : N - int(r)]
     if workspace is None and N >= MERGE_PLAN_WIDE_TOKENS:
-        workspace = torch.empty(int(lib().usv_merge_plan_workspace_bytes(ctypes.byref(sh), ctypes.byref(g))), dtype=torch.uint8,
+        workspace = torch.empty(int(lib().usv_merge_plan_workspace_bytes(shp, g)), dtype=torch.uint8,
                                 device=u.device)
     if workspace is None or workspace is False:
         wptr, wbytes = None, 0
     else:
         wptr, wbytes = _dev(workspace, "workspace"), workspace.numel() * workspace.element_size()
-    _check(lib().usv_merge_plan(_dev(u, "u", torch.float32), _dev(blk, "blk", torch.int32), ctypes.byref(sh), ctypes.byref(g),
+    _check(lib().usv_merge_plan(_dev(u, "u", torch.float32), _dev(blk, "blk", torch.int32), shp, g,
                                 _dev(row_of, "row_of", torch.int32), _dev(src_of, "src_of", torch.int32), wptr, wbytes, _stream()))
     return row_of, src_of
 
@@ -503,11 +533,11 @@ def merge_plan(u, blk, grid, mblock, r, row_of=None, src_of=None, workspace=None
 def merge_apply(x, grid, mblock, row_of, src_of, seq_len=None, out=None):
     """usv_merge_apply: raster x [B, Hh, T*H*W, d] -> merged [B, Hh, seq_len, d] (padding rows zero)."""
     B, Hh, N, d = x.shape
-    sh = _merge_shape(B, Hh, d, x.dtype, grid, N - src_of.shape[1], seq_len)
+    sh, shp = _merge_shape(B, Hh, d, x.dtype, grid, N - src_of.shape[1], seq_len)
     g = _grid(grid, mblock)
     if out is None:
         out = torch.empty((B, Hh, sh.seq_len, d), dtype=x.dtype, device=x.device)
-    _check(lib().usv_merge_apply(_dev(x, "x"), ctypes.byref(sh), ctypes.byref(g), _dev(row_of, "row_of", torch.int32),
+    _check(lib().usv_merge_apply(_dev(x, "x"), shp, g, _dev(row_of, "row_of", torch.int32),
                                  _dev(src_of, "src_of", torch.int32), _dev(out, "out"), _stream()))
     return out
 
@@ -516,11 +546,11 @@ def unmerge_apply(y, grid, mblock, row_of, n_merged_rows, out=None):
     """usv_unmerge_apply: merged y [B, Hh, seq_len, d] (n_merged_rows real rows) -> raster [B, Hh, T*H*W, d]."""
     B, Hh, Np, d = y.shape
     N = row_of.shape[1]
-    sh = _merge_shape(B, Hh, d, y.dtype, grid, N - int(n_merged_rows), Np)
+    shp = _merge_shape(B, Hh, d, y.dtype, grid, N - int(n_merged_rows), Np)[1]
     g = _grid(grid, mblock)
     if out is None:
         out = torch.empty((B, Hh, N, d), dtype=y.dtype, device=y.device)
-    _check(lib().usv_unmerge_apply(_dev(y, "y"), ctypes.byref(sh), ctypes.byref(g), _dev(row_of, "row_of", torch.int32),
+    _check(lib().usv_unmerge_apply(_dev(y, "y"), shp, g, _dev(row_of, "row_of", torch.int32),
                                    _dev(out, "out"), _stream()))
     return out
 
@@ -532,21 +562,21 @@ def cube_order(grid, cube=(4, 4, 4), seq_len=None, device="cuda:0", out=None):
         seq_len = -(-Nv // BLOCK) * BLOCK
     if out is None:
         out = torch.empty((seq_len,), dtype=torch.int32, device=device)
-    sh = UsvShape(1, 1, int(seq_len), Nv, 0, BLOCK, USV_F32)
+    shp = _shape(1, 1, int(seq_len), Nv, 0, USV_F32)[1]
     g = _grid(grid, cube)
-    _check(lib().usv_cube_order(ctypes.byref(sh), ctypes.byref(g), _dev(out, "order", torch.int32), _stream()))
+    _check(lib().usv_cube_order(shp, g, _dev(out, "order", torch.int32), _stream()))
     return out
 
 
 def cube_order_padded(grid, cube=(4, 4, 4), device="cuda:0"):
     """usv_cube_order_padded: one cube per block, cut cubes padded -> (order int32 [64 * cubes], block_valid int32 [cubes])."""
     g = _grid(grid, cube)
-    n = int(lib().usv_cube_count(ctypes.byref(g)))
+    n = int(lib().usv_cube_count(g))
     if n == 0:
         raise ValueError("invalid grid / cube, or too many cubes")
     order = torch.empty((n * BLOCK,), dtype=torch.int32, device=device)
     valid = torch.empty((n,), dtype=torch.int32, device=device)
-    _check(lib().usv_cube_order_padded(ctypes.byref(g), _dev(order, "order", torch.int32),
+    _check(lib().usv_cube_order_padded(g, _dev(order, "order", torch.int32),
                                        _dev(valid, "block_valid", torch.int32), _stream()))
     return order, valid
 
@@ -563,14 +593,14 @@ def _view(order, st, ost, block_valid, work_order=None):
 
 def _raster_shape(x, order):
     B, Hh, Nv, d = x.shape
-    return UsvShape(B, Hh, order.numel(), Nv, d, BLOCK, USV_BF16 if x.dtype == torch.bfloat16 else USV_F32)
+    return _shape(B, Hh, order.numel(), Nv, d, USV_BF16 if x.dtype == torch.bfloat16 else USV_F32)
 
 
 def block_scores_raster(q, k, order, out=None, workspace=None, block_valid=None):
     """usv_block_scores_raster: q, k raster-ordered [B, Hh, Nv, d] (strided views allowed) -> scores [B, Hh, nb, nb].
 
     block_valid (with the order table of cube_order_padded): one cube per block, cut cubes padded."""
-    sh = _raster_shape(q, order)
+    sh, shp = _raster_shape(q, order)
     qp, st = _raster(q, "q")
     kp, st_k = _raster(k, "k")
     if (st_k.batch, st_k.head, st_k.token) != (st.batch, st.head, st.token) or k.dtype != q.dtype:
@@ -578,29 +608,27 @@ def block_scores_raster(q, k, order, out=None, workspace=None, block_valid=None)
     nb = sh.seq_len // BLOCK
     if out is None:
         out = torch.empty((sh.batch, sh.heads, nb, nb), dtype=torch.float32, device=q.device)
-    need = int(lib().usv_workspace_bytes(ctypes.byref(sh)))
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
-    view = _view(order, st, UsvStrides(0, 0, 0), block_valid)
-    _check(lib().usv_block_scores_raster(qp, kp, ctypes.byref(sh), ctypes.byref(view), _dev(out, "scores", torch.float32),
+        workspace = torch.empty(max(int(lib().usv_workspace_bytes(shp)), 16), dtype=torch.uint8, device=q.device)
+    view = _view(order, st, _strides(0, 0, 0), block_valid)
+    _check(lib().usv_block_scores_raster(qp, kp, shp, ctypes.byref(view), _dev(out, "scores", torch.float32),
                                          _dev(workspace, "workspace"), workspace.numel(), _stream()))
     return out
 
 
 def coarse_attn_raster(scores, v, order, out=None, workspace=None, block_valid=None):
     """usv_coarse_attn_raster: usv_coarse_attn with v in raster order [B, Hh, Nv, d] (strided views allowed)."""
-    sh = _raster_shape(v, order)
+    sh, shp = _raster_shape(v, order)
     vp_, st = _raster(v, "v")
     nb = sh.seq_len // BLOCK
     if tuple(scores.shape) != (sh.batch, sh.heads, nb, nb):
         raise ValueError("scores must be [B, Hh, nb, nb]")
     if out is None:
         out = torch.empty((sh.batch, sh.heads, nb, sh.head_dim), dtype=torch.float32, device=v.device)
-    need = int(lib().usv_coarse_workspace_bytes(ctypes.byref(sh)))
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=v.device)
-    view = _view(order, st, UsvStrides(0, 0, 0), block_valid)
-    _check(lib().usv_coarse_attn_raster(_dev(scores, "scores", torch.float32), vp_, ctypes.byref(sh), ctypes.byref(view),
+        workspace = torch.empty(max(int(lib().usv_coarse_workspace_bytes(shp)), 16), dtype=torch.uint8, device=v.device)
+    view = _view(order, st, _strides(0, 0, 0), block_valid)
+    _check(lib().usv_coarse_attn_raster(_dev(scores, "scores", torch.float32), vp_, shp, ctypes.byref(view),
                                         _dev(out, "coarse", torch.float32), _dev(workspace, "workspace"),
                                         workspace.numel() * workspace.element_size(), _stream()))
     return out
@@ -611,7 +639,7 @@ def block_sparse_attn_raster(q, k, v, order, idx, cnt, scale=0.0, out=None, out_
     """usv_block_sparse_attn_raster(_fused): raster-ordered q, k, v [B, Hh, Nv, d] -> out [B, Hh, Nv, d] in raster order.
 
     coarse (+ optional raster-order gates laid out like q): out = gate_fine * attention + gate_coarse * coarse[cube]."""
-    sh = _raster_shape(q, order)
+    sh, shp = _raster_shape(q, order)
     ptrs = []
     st = None
     for name, t in (("q", q), ("k", k), ("v", v)):
@@ -638,7 +666,7 @@ def block_sparse_attn_raster(q, k, v, order, idx, cnt, scale=0.0, out=None, out_
             raise ValueError(f"{name} must match q in shape, strides and dtype")
         gates.append(gp_)
     _check(lib().usv_block_sparse_attn_raster_fused(
-        *ptrs, ctypes.byref(sh), ctypes.byref(view), _dev(idx, "idx", torch.int32), _dev(cnt, "cnt", torch.int32),
+        *ptrs, shp, ctypes.byref(view), _dev(idx, "idx", torch.int32), _dev(cnt, "cnt", torch.int32),
         int(idx.shape[3]), float(scale), None if coarse is None else _dev(coarse, "coarse", torch.float32), gates[0],
         gates[1], _dt(out), op, None if lse is None else _dev(lse, "lse", torch.float32), _stream()))
     return (out, lse) if return_lse else out
