@@ -55,13 +55,15 @@ inline float probability_shift(int kmax) {
   return (float)(shift < 64 ? 64 : shift > 110 ? 110 : shift);
 }
 
+__device__ __forceinline__ float4 bf16_pair(unsigned x, unsigned y) {  // four bf16, two per register
+  return make_float4(__uint_as_float(x << 16), __uint_as_float(x & 0xffff0000u), __uint_as_float(y << 16),
+                     __uint_as_float(y & 0xffff0000u));
+}
 __device__ __forceinline__ float4 load_bf16x4(const uint16_t* p) {
   // (the gates of the fused second branch: read once, so a streaming read)
   typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2;
   const u32x2 ww = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
-  const uint2 w = make_uint2(ww[0], ww[1]);
-  return make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
-                     __uint_as_float(w.y & 0xffff0000u));
+  return bf16_pair(ww[0], ww[1]);
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -131,22 +133,39 @@ __device__ __forceinline__ void store4(void* dst, const float4& val, int stream)
     else *reinterpret_cast<bf16x4*>(dst) = pk;
   }
 }
+// Eight channels of one output row.
+template <bool OUT_F32>
+__device__ __forceinline__ void store8(void* dst, const float4 (&val)[2], int stream) {
+  if constexpr (OUT_F32) {
+    store4<true>(dst, val[0], stream);
+    store4<true>(static_cast<float*>(dst) + 4, val[1], stream);
+  } else {
+    bf16x8 pk;
+    pk[0] = (__bf16)val[0].x; pk[1] = (__bf16)val[0].y; pk[2] = (__bf16)val[0].z; pk[3] = (__bf16)val[0].w;
+    pk[4] = (__bf16)val[1].x; pk[5] = (__bf16)val[1].y; pk[6] = (__bf16)val[1].z; pk[7] = (__bf16)val[1].w;
+    if (stream) __builtin_nontemporal_store(pk, reinterpret_cast<bf16x8*>(dst));
+    else *reinterpret_cast<bf16x8*>(dst) = pk;
+  }
+}
 // Streaming output stores where the L2 has something to lose: measured -1 % at the 480p shape (a head's K and V:
 // 16.8 MB), -2.7 % with ragged budgets at 16384 tokens, nothing on dense lists, but +4.4 % at the 720p shape
 // (38.7 MB per head: the L2 serves a quarter of the tile requests there whatever the output does, and the launch
 // runs at the limit of the fabric, which ordinary stores load more evenly).
 inline int stream_output(const Dims& s) { return 4LL * s.nb * kBlock * s.d <= (32LL << 20); }
 
-// Second branch folded into the store: gate_fine * attention + gate_coarse * cube-level row.  gate_off in elements.
-__device__ __forceinline__ void fuse4(float4& val, const FuseArgs& fuse, long long coarse_off, long long gate_off) {
-  const float4 cz = *reinterpret_cast<const float4*>(fuse.coarse + coarse_off);
-  float4 gf = make_float4(1.f, 1.f, 1.f, 1.f), gc = gf;
-  if (fuse.gate_fine) gf = load_bf16x4(fuse.gate_fine + gate_off);
-  if (fuse.gate_coarse) gc = load_bf16x4(fuse.gate_coarse + gate_off);
+// Second branch folded into the store: gate_fine * attention + gate_coarse * cube-level row.
+__device__ __forceinline__ void fuse4(float4& val, const float4& gf, const float4& gc, const float4& cz) {
   val.x = fmaf(gf.x, val.x, gc.x * cz.x);
   val.y = fmaf(gf.y, val.y, gc.y * cz.y);
   val.z = fmaf(gf.z, val.z, gc.z * cz.z);
   val.w = fmaf(gf.w, val.w, gc.w * cz.w);
+}
+// gate_off in elements
+__device__ __forceinline__ void fuse4(float4& val, const FuseArgs& fuse, long long coarse_off, long long gate_off) {
+  float4 gf = make_float4(1.f, 1.f, 1.f, 1.f), gc = gf;
+  if (fuse.gate_fine) gf = load_bf16x4(fuse.gate_fine + gate_off);
+  if (fuse.gate_coarse) gc = load_bf16x4(fuse.gate_coarse + gate_off);
+  fuse4(val, gf, gc, *reinterpret_cast<const float4*>(fuse.coarse + coarse_off));
 }
 
 }  // namespace

@@ -592,31 +592,62 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
   __syncthreads();
   if (wave == 0) take(I0{});
   else take(I2{});
-  {
-    // 32 rows x D channels, 4 channels per lane per pass, consecutive lanes -> consecutive addresses (the rows this wave
-    // staged itself: no barrier)
+  const long long blk_off = head_off + (long long)i * kBlock * D;
+  // 32 rows x D channels, 4 (second branch: 8) channels per lane per pass, consecutive lanes -> consecutive addresses (the
+  // rows this wave staged itself: no barrier)
+  auto out_row = [&](int row) -> unsigned char* {
+    if constexpr (RASTER)
+      return static_cast<unsigned char*>(out) + ras_out + (long long)ras.order[i * kBlock + row] * ras.o_tok;
+    else
+      return static_cast<unsigned char*>(out) + (blk_off + row * D) * (OUT_F32 ? 4 : 2);
+  };
+  if (fuse.coarse) {
+    // Second branch.  Piece p = 64 it + lane: row p / (D / 8) of the wave's 32, channels c8 .. c8 + 7, the same channels in
+    // every pass.  All of the wave's gate rows are requested before the first store: left to the passes, each of them waited
+    // for its own two loads (12 heads, 32768 tokens, 51 of 512 blocks, both gates, the whole two-branch layer: 878 -> 822 us).
+    constexpr int PIECES8 = 32 * D / 8 / 64;
+    typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned gate8;
+    const int c8 = (lane % (D / 8)) * 8;
+    gate8 gf[PIECES8], gc[PIECES8];
+    float4 cz[2];
+#pragma unroll
+    for (int it = 0; it < PIECES8; ++it) {
+      const int row = 32 * wave + (it * 64 + lane) / (D / 8);
+      long long at = blk_off + row * D + c8;  // (padded rows are there to be read; a padding position's order entry is a valid token)
+      if constexpr (RASTER)  // the gates are raster tensors laid out like q
+        at = (ras_off + (long long)ras.order[i * kBlock + row] * ras.tok) / 2 + c8;
+      constexpr unsigned kOnes = 0x3f803f80u;  // an absent gate is 1
+      gf[it] = gc[it] = gate8{kOnes, kOnes, kOnes, kOnes};
+      if (fuse.gate_fine) gf[it] = __builtin_nontemporal_load(reinterpret_cast<const gate8*>(fuse.gate_fine + at));
+      if (fuse.gate_coarse) gc[it] = __builtin_nontemporal_load(reinterpret_cast<const gate8*>(fuse.gate_coarse + at));
+    }
+    {
+      const float* row = fuse.coarse + (head * nb + i) * (long long)D + c8;
+      cz[0] = reinterpret_cast<const float4*>(row)[0];
+      cz[1] = reinterpret_cast<const float4*>(row)[1];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int it = 0; it < PIECES8; ++it) {
+      const int rr = (it * 64 + lane) / (D / 8), row = 32 * wave + rr;
+      if (RASTER && row >= nq) continue;  // the raster tensor has no padded rows
+      float4 val[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        val[e] = *reinterpret_cast<const float4*>(other + rr * OSTRIDE + c8 + 4 * e);
+        if (row < nq) fuse4(val[e], bf16_pair(gf[it][2 * e], gf[it][2 * e + 1]), bf16_pair(gc[it][2 * e], gc[it][2 * e + 1]), cz[e]);
+      }
+      store8<OUT_F32>(out_row(row) + c8 * (OUT_F32 ? 4 : 2), val, stream_out);
+    }
+  } else {
     constexpr int PIECES = 32 * D / 4;
-    const long long blk_off = head_off + (long long)i * kBlock * D;
 #pragma unroll
     for (int it = 0; it < PIECES / 64; ++it) {
       const int id = it * 64 + lane;
       const int rr = id / (D / 4), row = 32 * wave + rr, c4 = (id % (D / 4)) * 4;
-      float4 val = *reinterpret_cast<const float4*>(other + rr * OSTRIDE + c4);
-      if (fuse.coarse && row < nq) {
-        long long gate_off = blk_off + row * D + c4;
-        if constexpr (RASTER)  // the gates are raster tensors laid out like q
-          gate_off = (ras_off + (long long)ras.order[i * kBlock + row] * ras.tok) / 2 + c4;
-        fuse4(val, fuse, (head * nb + i) * (long long)D + c4, gate_off);
-      }
-      void* dst;
-      if constexpr (RASTER) {
-        if (row >= nq) continue;  // the raster tensor has no padded rows
-        dst = static_cast<unsigned char*>(out) + ras_out + (long long)ras.order[i * kBlock + row] * ras.o_tok +
-              c4 * (OUT_F32 ? 4 : 2);
-      } else {
-        dst = static_cast<unsigned char*>(out) + (blk_off + row * D + c4) * (OUT_F32 ? 4 : 2);
-      }
-      store4<OUT_F32>(dst, val, stream_out);
+      if (RASTER && row >= nq) continue;
+      const float4 val = *reinterpret_cast<const float4*>(other + rr * OSTRIDE + c4);
+      store4<OUT_F32>(out_row(row) + c4 * (OUT_F32 ? 4 : 2), val, stream_out);
     }
   }
 }
