@@ -1,11 +1,42 @@
-// Stage 3, fp32 variant: block-sparse attention for fp32 Q/K/V in fp32 arithmetic throughout
+// Stage 3, fp32 variant: block-sparse attention for fp32 Q/K/V to fp32 accuracy
 // (masked-attention equation, paper Section 3.2).  This is the accuracy path (inputs that must
 // match an fp64 evaluation to 1e-5); the throughput path is the bf16 kernel.
 //
-// Same decomposition as the bf16 kernel: one workgroup = 4 wavefronts = one 64-row query block,
-// wave (qh, kh) = 32 queries x 32 keys of every listed 64-key tile, an online softmax per key
-// half, the two halves merged once at the end through LDS.  Both products run on the fp32 matrix
-// cores (v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation), on the transposes:
+// The fp32 matrix pipe bounds a kernel that feeds it fp32 operands (157 TFLOP/s; 2 heads, 32768 tokens, 51 of 512 blocks:
+// 944 us at 117 TFLOP/s).  So every operand is split into three bf16 parts instead: x = x0 + x1 + x2 with x0 the nearest bf16
+// to x, x1 the nearest to x - x0 and x2 the rest, which fits 8 bits: the split is exact (24 bits of fp32 = 3 x 8), and the
+// products of parts are exact in the bf16 matrix core's fp32 accumulation.  Of the nine products six are formed:
+//   x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0);
+// the three left out are below 2^-24 |x y| together (typically 2^-27, of either sign), under one rounding of the fp32
+// sum.  Six products at sixteen times the rate leave 3/8 of the matrix time.
+// Measured there: 944 -> 610 us (0.66 PFLOP of bf16 products at 1.08 PFLOP/s, the rate the bf16 attention kernels reach under
+// the chip's power limit: matrix pipes busy 48 % of the clocks at 1.93 GHz).  Error against a 64-bit evaluation (2-norm,
+// relative), fp32 operands / split: 4 of 16 blocks 1.95e-7 / 1.51e-7, 51 of 512 1.22e-6 / 1.10e-6, flat weights 7.8e-7 /
+// 4.5e-7, 300 of 512 6.9e-6 / 6.3e-6; lower in all of 16 settings (both head dimensions).
+// Splitting the V rows between the MFMAs of the first product and the next K rows between those of the second took as many
+// clocks and more power (645 us): the second workgroup already fills those gaps.
+//
+// attn_f32: one workgroup = 4 wavefronts = one 64-row query block; wave w owns query rows 16 w .. + 15 and sees every
+// key, 32 keys (half a listed block) per step, so nothing is merged at the end.  K and V rows are fetched into
+// registers one step ahead, split there by the whole workgroup and staged in LDS as three bf16 planes each; a
+// second workgroup on the CU computes meanwhile.  Products on the transposes as in usv_attn_wide.hip
+// (v_mfma_f32_16x16x32_bf16; lane = (c, G)): lane (c, G) holds query c, keys 16 mt + 4 G + r, and those eight values are, as
+// they stand, the contraction slots of the P^T operand.
+//
+// fp32_block: the same block with fp32 operands on the fp32 matrix cores, for what a split cannot carry: infinities and NaN
+// (inf - inf), values the rounding to bf16 takes past its largest, and results so small that the lower parts run out of
+// exponent.  All of these show in the row sum or in the result (NaN, infinite, below 2^-100), and the workgroup then
+// computes its block again this way.
+#include <type_traits>
+
+#include "usv_attn_bf16.h"
+
+namespace usv {
+namespace {
+
+// ---- fp32 operands ------------------------------------------------------------------------------
+// wave (qh, kh) = 32 queries x 32 keys of every listed 64-key tile, an online softmax per key half, the two halves merged
+// once at the end through LDS.  Both products run on v_mfma_f32_32x32x2_f32, on the transposes:
 //   S^T (32 keys x 32 queries) = K (A operand) x Q^T (B operand)
 //   O^T (32 d    x 32 queries) = V^T (A operand) x P^T (B operand)
 // so that one query sits in one lane column and max / sum / rescale are per-lane values.  An MFMA
@@ -13,42 +44,23 @@
 // agree: in the first product half g takes channels g*D/2 + t at step t (every lane reads its
 // operands as contiguous 16-byte pieces), in the second the step r takes, in half g, exactly the
 // key that accumulator register r of that half holds, so P^T needs no data movement at all.
-// K and V tiles are staged in LDS as fp32 (rows padded by 4 floats), single-buffered: the kernel is
-// bound by the fp32 matrix pipe (128 MFMAs of 64 clocks per wave and tile), as long as a second workgroup
-// on the CU computes while one stages.  That takes 256 registers a wave: the partial accumulators of the first
-// product are formed and folded two at a time (2 heads, 32768 tokens, 51 of 512 blocks: 1.13 -> 0.94 ms = 117
-// TFLOP/s, against all four at once, 362 registers and one workgroup per CU; the same bits).
-#include <type_traits>
-
-#include "usv_internal.h"
-
-namespace usv {
-namespace {
-
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-
-// Lanes l and l ^ 32 hold the two key quarters of one query: (value of the low lane, of the high lane) in both.
-__device__ __forceinline__ void both_halves(float x, float& lo, float& hi) {
-  const unsigned u = __float_as_uint(x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  lo = __uint_as_float(r[0]);
-  hi = __uint_as_float(r[1]);
-}
+// K and V tiles are staged in LDS as fp32 (rows padded by 4 floats), single-buffered.
+template <int D>
+constexpr int kF32Lds = 2 * kBlock * (D + 4) * (int)sizeof(float);
 
 template <int D>
-__global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, const float* __restrict__ k,
-                                                const float* __restrict__ v, const int32_t* __restrict__ idx,
-                                                const int32_t* __restrict__ cnt, float* __restrict__ out,
-                                                float* __restrict__ lse, int nb, int Nv, int kmax, float scale_log2e) {
+__device__ void fp32_block(unsigned char* smem, const float* __restrict__ q, const float* __restrict__ k,
+                           const float* __restrict__ v, const int32_t* __restrict__ idx, int n_list,
+                           float* __restrict__ out, float* __restrict__ lse, long long blk, int nb, int Nv, int kmax,
+                           float scale_log2e) {
   constexpr int LD = D + 4;      // LDS row stride in floats: 16-byte reads of consecutive rows spread over the banks
   constexpr int DSUB = D / 32;   // 32-wide d sub-tiles of the output
   constexpr int HALF = D / 2;    // channels per lane half in the first product
   constexpr int XROWS = DSUB * 16 + 2;  // exchange rows per wave: O registers, m, l
   static_assert(2 * XROWS * 64 == kBlock * LD, "the exchange area of the two query halves fills the K tile exactly");
-  __shared__ __attribute__((aligned(16))) float Ks[kBlock * LD];  // K tile; at the end the exchange area
-  __shared__ __attribute__((aligned(16))) float Vs[kBlock * LD];  // V tile; at the end the output staging rows
+  float* const Ks = reinterpret_cast<float*>(smem);  // K tile; at the end the exchange area
+  float* const Vs = Ks + kBlock * LD;                // V tile; at the end the output staging rows
 
-  const long long blk = blockIdx.x;  // (b*Hh + h) * nb + i
   const int i = (int)(blk % nb);
   const long long head = blk / nb;
   const long long head_off = head * (long long)nb * kBlock * D;
@@ -56,7 +68,6 @@ __global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qh = wave & 1, kh = wave >> 1;
   const int col = lane & 31, g = lane >> 5;
-  const int n_list = min(max(cnt[blk], 0), kmax);  // device contents are not trusted with addresses
 
   // Q fragments: lane (col, g) holds channels g*HALF .. +HALF of query row 32 qh + col
   float qf[HALF];
@@ -228,16 +239,279 @@ __global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, 
   }
 }
 
+// ---- operands in three bf16 parts ---------------------------------------------------------------
+struct Split {  // eight values: x = p[0] + p[1] + p[2], exactly
+  bf16x8 p[3];
+};
+__device__ __forceinline__ Split split8(const float (&x)[8]) {
+  // pairs throughout: one conversion rounds and packs two values, a shift and a mask take them apart again
+  Split s;
+  float r[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) r[e] = x[e];
+#pragma unroll
+  for (int part = 0; part < 3; ++part) {
+    unsigned w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+      const f32x2 pair = {r[2 * e], r[2 * e + 1]};
+      w[e] = __builtin_bit_cast(unsigned, __builtin_convertvector(pair, bf16x2));  // to nearest even
+      if (part < 2) {  // (exact)
+        r[2 * e] -= __uint_as_float(w[e] << 16);
+        r[2 * e + 1] -= __uint_as_float(w[e] & 0xffff0000u);
+      }
+    }
+    typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
+    s.p[part] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+  }
+  return s;
+}
+
+__device__ __forceinline__ f32x4 mfma(const bf16x8& a, const bf16x8& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+template <int D>
+__global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, const float* __restrict__ k,
+                                                   const float* __restrict__ v, const int32_t* __restrict__ idx,
+                                                   const int32_t* __restrict__ cnt, float* __restrict__ out,
+                                                   float* __restrict__ lse, int nb, int Nv, int kmax, float scale_log2e,
+                                                   int total, int per_xcd) {
+  constexpr int KS = D / 32, DT = D / 16;      // channel steps of the first product, 16-channel tiles of the second
+  constexpr int kKeys = 32;                    // keys per step
+  constexpr int kRow = D * 2;                  // bytes of a key's row in a plane
+  constexpr int kPlane = kKeys * kRow;         // one part of K or V
+  constexpr int CH = D / 8;                    // 16-byte chunks per row
+  constexpr int PIECES = kKeys * CH / 256;     // chunks (eight channels) of K, and of V, that a thread fetches and splits
+  constexpr int LD = D + 4;                    // row stride of the output staging rows
+  constexpr int kLds = kF32Lds<D> > 6 * kPlane ? kF32Lds<D> : 6 * kPlane;
+  static_assert(kBlock * LD * (int)sizeof(float) <= kLds, "the output rows overlay the planes");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
+  __shared__ int redo[4];
+
+  const int work = xcd_contiguous_id(blockIdx.x, per_xcd);  // neighbouring query blocks share K and V in an XCD's L2
+  if (work >= total) return;  // whole workgroup leaves before any barrier
+  const long long blk = work;  // (b*Hh + h) * nb + i
+  const int i = work % nb;
+  const long long head = work / nb;
+  const long long head_off = head * (long long)nb * kBlock * D;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c16 = lane & 15, G = lane >> 4;
+  const int n_list = min(max(cnt[blk], 0), kmax);  // device contents are not trusted with addresses
+  const int32_t* list = idx + blk * kmax;
+
+  // Position of chunk c of row r inside a plane.  The 16 rows of a K fragment read, and the 8 rows of half of a transposing V
+  // read (32 bytes each), fall on different banks.
+  auto k_at = [](int r, int c) { return D == 128 ? r * kRow + ((c ^ (r & 15)) << 4) : r * kRow + ((c ^ ((r >> 1) & 7)) << 4); };
+  auto v_at = [](int r, int c) {
+    return D == 128 ? r * kRow + ((c ^ ((r & 7) << 1)) << 4) : r * kRow + ((c ^ (((r >> 1) & 3) << 1)) << 4);
+  };
+
+  // The rows of a step on their way from memory: this thread's pieces, piece u = row (256 u + tid) / CH, chunk (tid % CH)
+  float4 kraw[PIECES][2], vraw[PIECES][2];
+  auto fetch = [&](int j, int half) {
+    const long long at = head_off + ((long long)j * kBlock + half * kKeys) * D;
+#pragma unroll
+    for (int u = 0; u < PIECES; ++u) {
+      const long long off = at + (long long)(256 * u + tid) * 8;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        kraw[u][e] = reinterpret_cast<const float4*>(k + off)[e];
+        vraw[u][e] = reinterpret_cast<const float4*>(v + off)[e];
+      }
+    }
+  };
+  auto block_at = [&](int n) { return min(max(list[n], 0), nb - 1); };
+
+  int j = n_list > 0 ? block_at(0) : 0;
+  if (n_list > 0) fetch(j, 0);
+
+  // Q^T fragments: query row 16 wave + c16, channels 32 t + 8 G .. + 8
+  Split qf[KS];
+  {
+    const float* qp = q + head_off + (long long)(i * kBlock + wave * 16 + c16) * D + G * 8;
+#pragma unroll
+    for (int t = 0; t < KS; ++t) {
+      float x[8];
+      *reinterpret_cast<float4*>(x) = reinterpret_cast<const float4*>(qp + 32 * t)[0];
+      *reinterpret_cast<float4*>(x + 4) = reinterpret_cast<const float4*>(qp + 32 * t)[1];
+      qf[t] = split8(x);
+    }
+  }
+  // channel 16 dt + 4 G + r of query c16: the leading products and the small ones in sums of their own (in one sum every small
+  // product would round the whole of it)
+  f32x4 o[DT], o5[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) o[dt] = o5[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, m_ref = 0.f;  // reference maximum (log2 domain), identical in the four lanes of a query; 0 in its place before the first live key
+  float l = 0.f;        // this lane's partial row sum
+
+  const unsigned char* const ks = smem;
+  const unsigned char* const vs = smem + 3 * kPlane;
+
+  for (int st = 0; st < 2 * n_list; ++st) {
+    const int half = st & 1;
+    const int nkeys = Nv - j * kBlock - half * kKeys;  // valid keys of this half (below 32 only at the end of the sequence)
+    __syncthreads();  // the previous step's planes are fully consumed
+#pragma unroll
+    for (int u = 0; u < PIECES; ++u) {
+      const int e = 256 * u + tid, row = e / CH, c = e % CH;
+      float x[8];
+      *reinterpret_cast<float4*>(x) = kraw[u][0];
+      *reinterpret_cast<float4*>(x + 4) = kraw[u][1];
+      const Split a = split8(x);
+#pragma unroll
+      for (int part = 0; part < 3; ++part) *reinterpret_cast<bf16x8*>(smem + part * kPlane + k_at(row, c)) = a.p[part];
+      *reinterpret_cast<float4*>(x) = vraw[u][0];
+      *reinterpret_cast<float4*>(x + 4) = vraw[u][1];
+      if (nkeys < kKeys) {  // padded rows may hold any finite value, also one that rounds to infinity: their p is 0
+#pragma unroll
+        for (int y = 0; y < 8; ++y) x[y] = row < nkeys ? x[y] : 0.f;
+      }
+      const Split b = split8(x);
+#pragma unroll
+      for (int part = 0; part < 3; ++part)
+        *reinterpret_cast<bf16x8*>(smem + (3 + part) * kPlane + v_at(row, c)) = b.p[part];
+    }
+    if (half) j = block_at(min((st >> 1) + 1, n_list - 1));
+    if (st + 1 < 2 * n_list) fetch(j, half ^ 1);
+    __syncthreads();
+
+    // ---- S^T = K Q^T: the leading product and the five small ones in sums of their own ----
+    f32x4 s[2], t5[2];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) s[mt] = t5[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 a[2][3];  // the fragments of this product and, on their way from LDS, of the next
+    auto read_k = [&](int f) {  // fragment f = 2 t + mt
+#pragma unroll
+      for (int part = 0; part < 3; ++part)
+        a[f & 1][part] = *reinterpret_cast<const bf16x8*>(ks + part * kPlane + k_at(16 * (f & 1) + c16, 4 * (f >> 1) + G));
+    };
+    read_k(0);
+#pragma unroll
+    for (int f = 0; f < 2 * KS; ++f) {
+      if (f + 1 < 2 * KS) read_k(f + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      const bf16x8(&x)[3] = a[f & 1];
+      const bf16x8(&y)[3] = qf[f >> 1].p;
+      f32x4& big = s[f & 1];
+      f32x4& small = t5[f & 1];
+      small = mfma(x[2], y[0], small);
+      small = mfma(x[0], y[2], small);
+      small = mfma(x[1], y[1], small);
+      small = mfma(x[1], y[0], small);
+      small = mfma(x[0], y[1], small);
+      big = mfma(x[0], y[0], big);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    float x[8];  // key 16 (e / 4) + 4 G + e % 4 of the step, query c16
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = s[e >> 2][e & 3] + t5[e >> 2][e & 3];
+    if (nkeys < kKeys) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = 16 * (e >> 2) + 4 * G + (e & 3) < nkeys ? x[e] : -INFINITY;
+    }
+
+    // ---- online softmax (log2 domain, lazily raised reference maximum: p stays below 2^slack, which fp32 does not feel) ----
+    float mx = x[0];
+#pragma unroll
+    for (int e = 1; e < 8; ++e) mx = fmaxf(mx, x[e]);
+    if (__any(mx * scale_log2e - m > kRescaleSlack)) {  // wave-uniform; always taken on the first step with a live key
+      const float m_new = fmaxf(m, max_over_groups(mx) * scale_log2e);
+      m_ref = m_new == -INFINITY ? 0.f : m_new;  // every key so far masked: all p are exp2(-inf) = 0
+      const float alpha = fast_exp2(m - m_ref);  // m = -inf -> 0
+      m = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[dt][r] *= alpha, o5[dt][r] *= alpha;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      x[e] = fast_exp2(fmaf(x[e], scale_log2e, -m_ref));
+      l += x[e];
+    }
+    const Split pf = split8(x);
+
+    // ---- O^T += V^T P^T ----
+    auto read_v = [&](int dt) {
+#pragma unroll
+      for (int part = 0; part < 3; ++part) {
+        // rows 4 G + (0..3) and 16 + 4 G + (0..3); the 16 lanes of a group address 4 rows x 16 channels
+        const int row = 4 * G + (c16 >> 2);
+        const unsigned char* at = vs + part * kPlane + v_at(row, 2 * dt + ((c16 >> 1) & 1)) + (c16 & 1) * 8;
+        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)at);
+        const short4v hi =
+            __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)(at + 16 * kRow));
+        a[dt & 1][part] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      }
+    };
+    read_v(0);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      if (dt + 1 < DT) read_v(dt + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      const bf16x8(&y)[3] = a[dt & 1];
+      o5[dt] = mfma(y[2], pf.p[0], o5[dt]);
+      o5[dt] = mfma(y[0], pf.p[2], o5[dt]);
+      o5[dt] = mfma(y[1], pf.p[1], o5[dt]);
+      o5[dt] = mfma(y[1], pf.p[0], o5[dt]);
+      o5[dt] = mfma(y[0], pf.p[1], o5[dt]);
+      o[dt] = mfma(y[0], pf.p[0], o[dt]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  // ---- stage the rows row-major, store coalesced ----
+  __syncthreads();  // every wave is done with the last planes
+  const float lt = sum_over_groups(l);
+  const int token = i * kBlock + wave * 16 + c16;
+  const bool mine = token < Nv && n_list > 0;
+  const bool live = mine && lt > 0.f;  // lt == 0: every listed key is padding
+  const float inv = live ? 1.f / lt : 0.f;
+  bool bad = mine && !(lt < INFINITY);
+  float* stage = reinterpret_cast<float*>(smem) + (wave * 16 + c16) * LD;
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) {
+    float y[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      y[r] = live ? (o[dt][r] + o5[dt][r]) * inv : 0.f;
+      const float a = fabsf(y[r]);
+      bad |= !(a < INFINITY) || (a < 0x1p-100f && a > 0.f);
+    }
+    *reinterpret_cast<float4*>(stage + 16 * dt + 4 * G) = make_float4(y[0], y[1], y[2], y[3]);
+  }
+  const int any_bad = __any(bad);
+  if (lane == 0) redo[wave] = any_bad;
+  __syncthreads();
+  if (redo[0] | redo[1] | redo[2] | redo[3]) {
+    fp32_block<D>(smem, q, k, v, idx, n_list, out, lse, blk, nb, Nv, kmax, scale_log2e);
+    return;
+  }
+  if (lse && G == 0) lse[head * (long long)nb * kBlock + token] = live ? (m + __log2f(lt)) * kLn2 : -INFINITY;
+  float* ob = out + head_off + (long long)i * kBlock * D;
+#pragma unroll
+  for (int e = tid; e < kBlock * (D / 4); e += 256) {
+    const int row = e / (D / 4), c = (e % (D / 4)) * 4;
+    *reinterpret_cast<float4*>(ob + row * D + c) = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(smem) + row * LD + c);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_attn_f32(const float* q, const float* k, const float* v, const Dims& s, const int32_t* idx,
                            const int32_t* cnt, int kmax, float scale, float* out, float* lse, hipStream_t st) {
-  const unsigned grid = (unsigned)(s.bh() * s.nb);
+  const int total = (int)(s.bh() * s.nb), per_xcd = (total + kNumXcd - 1) / kNumXcd;
+  const unsigned grid = (unsigned)per_xcd * kNumXcd;
   const float sl2 = scale * kLog2e;
   if (s.d == 128)
-    attn_f32<128><<<grid, 256, 0, st>>>(q, k, v, idx, cnt, out, lse, s.nb, s.Nv, kmax, sl2);
+    attn_f32<128><<<grid, 256, 0, st>>>(q, k, v, idx, cnt, out, lse, s.nb, s.Nv, kmax, sl2, total, per_xcd);
   else
-    attn_f32<64><<<grid, 256, 0, st>>>(q, k, v, idx, cnt, out, lse, s.nb, s.Nv, kmax, sl2);
+    attn_f32<64><<<grid, 256, 0, st>>>(q, k, v, idx, cnt, out, lse, s.nb, s.Nv, kmax, sl2, total, per_xcd);
   return hipGetLastError();
 }
 

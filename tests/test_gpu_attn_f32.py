@@ -1,0 +1,68 @@
+"""The fp32 attention kernel where splitting its operands into bf16 parts could go wrong: infinities, NaN, values beyond the largest
+bf16, values whose lower parts run out of exponent, padding of any finite value, halves of a block without a valid key."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+FLT_MAX = np.float32(3.4028234e38)
+
+
+def edit(what, Q, K, V, Nv):
+    if what == "inf in v": V[0, 0, 70, 5] = np.inf
+    if what == "nan in v": V[0, 0, 70, 5] = np.nan
+    if what == "nan in q": Q[0, 1, 3, 5] = np.nan
+    if what == "-inf logit":  # weight 0, not NaN
+        Q[0, 0, :, 3] = np.abs(Q[0, 0, :, 3]) + 0.1
+        K[0, 0, 70, 3] = -np.inf
+    # Rounds to infinity as bf16 (above 3.396e38).  Not FLT_MAX itself: the largest weight is 2^(x - round(x)), |x| < 64 here, so it
+    # may be 1 + 2^-19, and the sum before the division overflowed on fp32 operands too; 3.4e38 leaves 8e-4.
+    if what == "beyond bf16": V[0, 0, 70, 5] = 3.4e38
+    if what == "tiny v": V[..., 7] *= 1e-33
+    if what == "tiny v, lower parts subnormal": V[..., 7] *= 1e-36
+    if what == "huge padding": Q[:, :, Nv:], K[:, :, Nv:], V[:, :, Nv:] = FLT_MAX, FLT_MAX, -FLT_MAX
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tail", [0, 44, 62, 32])  # padded rows of the last block: none, its second half empty, two keys, half
+@pytest.mark.parametrize("what", ["plain", "inf in v", "nan in v", "nan in q", "-inf logit", "beyond bf16", "tiny v",
+                                  "tiny v, lower parts subnormal", "huge padding"])
+def test_f32_attention_special_values(usv, d, tail, what):
+    nb, Nv = 5, 5 * 64 - tail
+    rng = np.random.default_rng(d + tail)
+    Q, K, V = (rng.standard_normal((1, 2, nb * 64, d), dtype=np.float32) for _ in range(3))
+    edit(what, Q, K, V, Nv)
+    lists = [[0, 1, 2, 3, 4], [4], [1, 4], [], [3, 2, 1]]
+    idx = np.full((1, 2, nb, nb), -1, np.int32)
+    cnt = np.zeros((1, 2, nb), np.int32)
+    for i, js in enumerate(lists):
+        idx[:, :, i, :len(js)], cnt[:, :, i] = js, len(js)
+    out, lse = usv.block_sparse_attn(gu.up(Q), gu.up(K), gu.up(V), gu.up(idx), gu.up(cnt), seq_valid=Nv, return_lse=True)
+    o, l = gu.down(out), gu.down(lse)
+    with np.errstate(all="ignore"):
+        for h in range(2):
+            for i, js in enumerate(lists):
+                got, rows = o[0, h, i * 64:(i + 1) * 64], max(0, min(64, Nv - i * 64))
+                assert (got[rows:] == 0).all()
+                keys = np.concatenate([np.arange(j * 64, min(j * 64 + 64, Nv)) for j in js]) if js else np.zeros(0, int)
+                if not len(keys):
+                    assert (got == 0).all() and np.isneginf(l[0, h, i * 64:(i + 1) * 64]).all()
+                    continue
+                S = Q[0, h, i * 64:i * 64 + rows].astype(np.float64) @ K[0, h, keys].astype(np.float64).T / np.sqrt(d)
+                P = np.exp(S - S.max(axis=1, keepdims=True))
+                ref = (P / P.sum(axis=1, keepdims=True)) @ V[0, h, keys].astype(np.float64)
+                if what == "nan in q":  # a row without a row sum is written as zeros
+                    bad = np.isnan(S).any(axis=1)
+                    assert (got[:rows][bad] == 0).all()
+                    got, ref, rows = got[:rows][~bad], ref[~bad], int((~bad).sum())
+                got = got[:rows].astype(np.float64)
+                assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref)), (what, h, i)
+                # fp32 rounding of the inputs' products over at most 320 keys: 1e-5 of what the channel's values average
+                fin = np.isfinite(ref)
+                scale = np.abs(np.where(np.isfinite(V[0, h, keys]), V[0, h, keys], 0)).astype(np.float64).mean(axis=0)
+                err = np.abs(np.where(fin, got - ref, 0))
+                # (values of 1e-36 leave results a few of whose last bits lie under the fp32 normal range)
+                assert (err <= 1e-5 * scale + 2.0 ** -126 * 1e-5 + 2.0 ** -149).all(), (what, h, i, (err / scale).max())
