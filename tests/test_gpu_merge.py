@@ -189,3 +189,18 @@ def test_merge_plan_large_token_counts(usv, grid, mb):
         rr, rs = orc.merge_plan(u, grid, mb, r)
         np.testing.assert_array_equal(row_of.cpu().numpy(), rr)
         np.testing.assert_array_equal(src_of.cpu().numpy(), rs)
+
+
+@pytest.mark.parametrize("grid", [(1, 1, 1), (2, 2, 2), (3, 5, 7), (2, 3, 17), (5, 4, 10)], ids=str)
+@pytest.mark.parametrize("d,dtype", [(64, "f32"), (128, "f32"), (64, "bf16"), (128, "bf16")])
+@pytest.mark.parametrize("Hh", [1, 12, 13])  # heads are summed twelve at a time, then one by one
+def test_similarity_of_2x2x2_blocks(usv, grid, d, dtype, Hh):
+    """The one-kernel form for 2x2x2 merge blocks: cut blocks on every axis, one to four blocks per workgroup with and without a rest."""
+    N = grid[0] * grid[1] * grid[2]
+    rng = np.random.default_rng([62, *grid, d, Hh])
+    K = make(rng, (2, Hh, N, d), dtype, smooth=rng.standard_normal((2, 1, N, d)).astype(np.float32))
+    K[1, :, 0] = 0  # a destination whose descriptor is zero: similarity 0, not NaN
+    u, blk = usv.merge_similarity(gu.up(K), grid, (2, 2, 2))
+    assert np.array_equal(gu.down(blk), expected_blk(grid, (2, 2, 2)))
+    ref = orc.merge_similarity(synth.as_f32(K), grid, (2, 2, 2))
+    gu.assert_f32_close(gu.down(u), ref, f"{grid} d={d} {dtype} heads={Hh}")
