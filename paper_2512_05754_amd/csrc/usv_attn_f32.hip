@@ -16,8 +16,9 @@
 // Splitting the V rows between the MFMAs of the first product and the next K rows between those of the second took as many
 // clocks and more power (645 us): the second workgroup already fills those gaps.
 //
-// attn_f32: one workgroup = 4 wavefronts = one 64-row query block; wave w owns query rows 16 w .. + 15 and sees every
-// key, 32 keys (half a listed block) per step, so nothing is merged at the end.  K and V rows are fetched into
+// attn_f32: one workgroup = 4 KH wavefronts = one 64-row query block; wave w owns query rows 16 (w % 4) .. + 15.  KH = 1: 32 keys
+// (half a listed block) per step, every wave sees them all and nothing is merged at the end.  KH = 2 (small grids, see the
+// launcher): a whole block per step, waves 0..3 take its first half and waves 4..7 its second, merged once through LDS.  K and V rows are fetched into
 // registers one step ahead, split there by the whole workgroup and staged in LDS as three bf16 planes each; a
 // second workgroup on the CU computes meanwhile.  Products on the transposes as in usv_attn_wide.hip
 // (v_mfma_f32_16x16x32_bf16; lane = (c, G)): lane (c, G) holds query c, keys 16 mt + 4 G + r, and those eight values are, as
@@ -48,8 +49,8 @@ namespace {
 template <int D>
 constexpr int kF32Lds = 2 * kBlock * (D + 4) * (int)sizeof(float);
 
-template <int D>
-__device__ void fp32_block(unsigned char* smem, const float* __restrict__ q, const float* __restrict__ k,
+template <int D>  // (inlined: a call would need scratch memory)
+__device__ __forceinline__ void fp32_block(unsigned char* smem, const float* __restrict__ q, const float* __restrict__ k,
                            const float* __restrict__ v, const int32_t* __restrict__ idx, int n_list,
                            float* __restrict__ out, float* __restrict__ lse, long long blk, int nb, int Nv, int kmax,
                            float scale_log2e) {
@@ -64,7 +65,7 @@ __device__ void fp32_block(unsigned char* smem, const float* __restrict__ q, con
   const int i = (int)(blk % nb);
   const long long head = blk / nb;
   const long long head_off = head * (long long)nb * kBlock * D;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x & 255, lane = tid & 63;  // (a second set of four waves does the same work, to the same places)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qh = wave & 1, kh = wave >> 1;
   const int col = lane & 31, g = lane >> 5;
@@ -272,21 +273,24 @@ __device__ __forceinline__ f32x4 mfma(const bf16x8& a, const bf16x8& b, const f3
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-template <int D>
-__global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, const float* __restrict__ k,
+template <int D, int KH>
+__global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict__ q, const float* __restrict__ k,
                                                    const float* __restrict__ v, const int32_t* __restrict__ idx,
                                                    const int32_t* __restrict__ cnt, float* __restrict__ out,
                                                    float* __restrict__ lse, int nb, int Nv, int kmax, float scale_log2e,
                                                    int total, int per_xcd) {
   constexpr int KS = D / 32, DT = D / 16;      // channel steps of the first product, 16-channel tiles of the second
-  constexpr int kKeys = 32;                    // keys per step
+  constexpr int kThreads = 256 * KH;
+  constexpr int kKeys = 32 * KH;               // keys per step
   constexpr int kRow = D * 2;                  // bytes of a key's row in a plane
   constexpr int kPlane = kKeys * kRow;         // one part of K or V
   constexpr int CH = D / 8;                    // 16-byte chunks per row
-  constexpr int PIECES = kKeys * CH / 256;     // chunks (eight channels) of K, and of V, that a thread fetches and splits
+  constexpr int PIECES = kKeys * CH / kThreads;     // chunks (eight channels) of K, and of V, that a thread fetches and splits
   constexpr int LD = D + 4;                    // row stride of the output staging rows
   constexpr int kLds = kF32Lds<D> > 6 * kPlane ? kF32Lds<D> : 6 * kPlane;
-  static_assert(kBlock * LD * (int)sizeof(float) <= kLds, "the output rows overlay the planes");
+  constexpr int XROWS = DT * 4 + 2;            // exchange rows of 64 floats per wave: O, reference and sum
+  constexpr int kExchange = KH == 2 ? 4 * XROWS * 64 : 0;  // floats
+  static_assert((kExchange + kBlock * LD) * (int)sizeof(float) <= kLds, "exchange area and output rows overlay the planes");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
   __shared__ int redo[4];
 
@@ -298,6 +302,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, 
   const long long head_off = head * (long long)nb * kBlock * D;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qw = wave & 3, kh = wave >> 2;  // query rows 16 qw .., keys 32 kh .. of a step
   const int c16 = lane & 15, G = lane >> 4;
   const int n_list = min(max(cnt[blk], 0), kmax);  // device contents are not trusted with addresses
   const int32_t* list = idx + blk * kmax;
@@ -309,13 +314,13 @@ __global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, 
     return D == 128 ? r * kRow + ((c ^ ((r & 7) << 1)) << 4) : r * kRow + ((c ^ (((r >> 1) & 3) << 1)) << 4);
   };
 
-  // The rows of a step on their way from memory: this thread's pieces, piece u = row (256 u + tid) / CH, chunk (tid % CH)
+  // The rows of a step on their way from memory: this thread's pieces, piece u = row (kThreads u + tid) / CH, chunk (tid % CH)
   float4 kraw[PIECES][2], vraw[PIECES][2];
   auto fetch = [&](int j, int half) {
-    const long long at = head_off + ((long long)j * kBlock + half * kKeys) * D;
+    const long long at = head_off + ((long long)j * kBlock + half * 32) * D;
 #pragma unroll
     for (int u = 0; u < PIECES; ++u) {
-      const long long off = at + (long long)(256 * u + tid) * 8;
+      const long long off = at + (long long)(kThreads * u + tid) * 8;
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
         kraw[u][e] = reinterpret_cast<const float4*>(k + off)[e];
@@ -328,10 +333,10 @@ __global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, 
   int j = n_list > 0 ? block_at(0) : 0;
   if (n_list > 0) fetch(j, 0);
 
-  // Q^T fragments: query row 16 wave + c16, channels 32 t + 8 G .. + 8
+  // Q^T fragments: query row 16 qw + c16, channels 32 t + 8 G .. + 8
   Split qf[KS];
   {
-    const float* qp = q + head_off + (long long)(i * kBlock + wave * 16 + c16) * D + G * 8;
+    const float* qp = q + head_off + (long long)(i * kBlock + qw * 16 + c16) * D + G * 8;
 #pragma unroll
     for (int t = 0; t < KS; ++t) {
       float x[8];
@@ -351,13 +356,14 @@ __global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, 
   const unsigned char* const ks = smem;
   const unsigned char* const vs = smem + 3 * kPlane;
 
-  for (int st = 0; st < 2 * n_list; ++st) {
-    const int half = st & 1;
-    const int nkeys = Nv - j * kBlock - half * kKeys;  // valid keys of this half (below 32 only at the end of the sequence)
+  constexpr int kSteps = 2 / KH;  // steps per listed block
+  for (int st = 0; st < kSteps * n_list; ++st) {
+    const int half = st % kSteps;
+    const int nkeys = Nv - j * kBlock - half * 32;  // valid keys of this step (below kKeys only at the end of the sequence)
     __syncthreads();  // the previous step's planes are fully consumed
 #pragma unroll
     for (int u = 0; u < PIECES; ++u) {
-      const int e = 256 * u + tid, row = e / CH, c = e % CH;
+      const int e = kThreads * u + tid, row = e / CH, c = e % CH;
       float x[8];
       *reinterpret_cast<float4*>(x) = kraw[u][0];
       *reinterpret_cast<float4*>(x + 4) = kraw[u][1];
@@ -375,8 +381,8 @@ __global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, 
       for (int part = 0; part < 3; ++part)
         *reinterpret_cast<bf16x8*>(smem + (3 + part) * kPlane + v_at(row, c)) = b.p[part];
     }
-    if (half) j = block_at(min((st >> 1) + 1, n_list - 1));
-    if (st + 1 < 2 * n_list) fetch(j, half ^ 1);
+    if (half == kSteps - 1) j = block_at(min(st / kSteps + 1, n_list - 1));
+    if (st + 1 < kSteps * n_list) fetch(j, (st + 1) % kSteps);
     __syncthreads();
 
     // ---- S^T = K Q^T: the leading product and the five small ones in sums of their own ----
@@ -387,7 +393,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, 
     auto read_k = [&](int f) {  // fragment f = 2 t + mt
 #pragma unroll
       for (int part = 0; part < 3; ++part)
-        a[f & 1][part] = *reinterpret_cast<const bf16x8*>(ks + part * kPlane + k_at(16 * (f & 1) + c16, 4 * (f >> 1) + G));
+        a[f & 1][part] = *reinterpret_cast<const bf16x8*>(ks + part * kPlane + k_at(32 * kh + 16 * (f & 1) + c16, 4 * (f >> 1) + G));
     };
     read_k(0);
 #pragma unroll
@@ -411,7 +417,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, 
     for (int e = 0; e < 8; ++e) x[e] = s[e >> 2][e & 3] + t5[e >> 2][e & 3];
     if (nkeys < kKeys) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = 16 * (e >> 2) + 4 * G + (e & 3) < nkeys ? x[e] : -INFINITY;
+      for (int e = 0; e < 8; ++e) x[e] = 32 * kh + 16 * (e >> 2) + 4 * G + (e & 3) < nkeys ? x[e] : -INFINITY;
     }
 
     // ---- online softmax (log2 domain, lazily raised reference maximum: p stays below 2^slack, which fp32 does not feel) ----
@@ -441,7 +447,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, 
 #pragma unroll
       for (int part = 0; part < 3; ++part) {
         // rows 4 G + (0..3) and 16 + 4 G + (0..3); the 16 lanes of a group address 4 rows x 16 channels
-        const int row = 4 * G + (c16 >> 2);
+        const int row = 32 * kh + 4 * G + (c16 >> 2);
         const unsigned char* at = vs + part * kPlane + v_at(row, 2 * dt + ((c16 >> 1) & 1)) + (c16 & 1) * 8;
         const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)at);
         const short4v hi =
@@ -465,39 +471,68 @@ __global__ __launch_bounds__(256, 2) void attn_f32(const float* __restrict__ q, 
     }
   }
 
-  // ---- stage the rows row-major, store coalesced ----
+  // ---- merge the key halves, stage the rows row-major, store coalesced ----
   __syncthreads();  // every wave is done with the last planes
-  const float lt = sum_over_groups(l);
-  const int token = i * kBlock + wave * 16 + c16;
-  const bool mine = token < Nv && n_list > 0;
+  float lt = sum_over_groups(l);
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[dt][r] += o5[dt][r];
+  if constexpr (KH == 2) {
+    float* xch = reinterpret_cast<float*>(smem) + qw * XROWS * 64 + lane;
+    if (kh == 1) {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) xch[(dt * 4 + r) * 64] = o[dt][r];
+      xch[(DT * 4) * 64] = m;
+      xch[(DT * 4 + 1) * 64] = lt;
+    }
+    __syncthreads();
+    if (kh == 0) {
+      const float m1 = xch[(DT * 4) * 64], l1 = xch[(DT * 4 + 1) * 64];
+      const float mm = fmaxf(m, m1);
+      const float ref = mm == -INFINITY ? 0.f : mm;
+      const float a0 = fast_exp2(m - ref), a1 = fast_exp2(m1 - ref);
+      lt = lt * a0 + l1 * a1;
+      m = mm;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[dt][r] = o[dt][r] * a0 + xch[(dt * 4 + r) * 64] * a1;
+    }
+  }
+  float* const rows = reinterpret_cast<float*>(smem) + kExchange;
+  const int token = i * kBlock + qw * 16 + c16;
+  const bool mine = token < Nv && n_list > 0 && kh == 0;
   const bool live = mine && lt > 0.f;  // lt == 0: every listed key is padding
   const float inv = live ? 1.f / lt : 0.f;
   bool bad = mine && !(lt < INFINITY);
-  float* stage = reinterpret_cast<float*>(smem) + (wave * 16 + c16) * LD;
+  float* stage = rows + (qw * 16 + c16) * LD;
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
     float y[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      y[r] = live ? (o[dt][r] + o5[dt][r]) * inv : 0.f;
+      y[r] = live ? o[dt][r] * inv : 0.f;
       const float a = fabsf(y[r]);
       bad |= !(a < INFINITY) || (a < 0x1p-100f && a > 0.f);
     }
-    *reinterpret_cast<float4*>(stage + 16 * dt + 4 * G) = make_float4(y[0], y[1], y[2], y[3]);
+    if (kh == 0) *reinterpret_cast<float4*>(stage + 16 * dt + 4 * G) = make_float4(y[0], y[1], y[2], y[3]);
   }
   const int any_bad = __any(bad);
-  if (lane == 0) redo[wave] = any_bad;
+  if (lane == 0 && kh == 0) redo[qw] = any_bad;
   __syncthreads();
   if (redo[0] | redo[1] | redo[2] | redo[3]) {
     fp32_block<D>(smem, q, k, v, idx, n_list, out, lse, blk, nb, Nv, kmax, scale_log2e);
     return;
   }
-  if (lse && G == 0) lse[head * (long long)nb * kBlock + token] = live ? (m + __log2f(lt)) * kLn2 : -INFINITY;
+  if (lse && G == 0 && kh == 0) lse[head * (long long)nb * kBlock + token] = live ? (m + __log2f(lt)) * kLn2 : -INFINITY;
   float* ob = out + head_off + (long long)i * kBlock * D;
 #pragma unroll
-  for (int e = tid; e < kBlock * (D / 4); e += 256) {
+  for (int e = tid; e < kBlock * (D / 4); e += kThreads) {
     const int row = e / (D / 4), c = (e % (D / 4)) * 4;
-    *reinterpret_cast<float4*>(ob + row * D + c) = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(smem) + row * LD + c);
+    *reinterpret_cast<float4*>(ob + row * D + c) = *reinterpret_cast<const float4*>(rows + row * LD + c);
   }
 }
 
@@ -508,10 +543,18 @@ hipError_t launch_attn_f32(const float* q, const float* k, const float* v, const
   const int total = (int)(s.bh() * s.nb), per_xcd = (total + kNumXcd - 1) / kNumXcd;
   const unsigned grid = (unsigned)per_xcd * kNumXcd;
   const float sl2 = scale * kLog2e;
-  if (s.d == 128)
-    attn_f32<128><<<grid, 256, 0, st>>>(q, k, v, idx, cnt, out, lse, s.nb, s.Nv, kmax, sl2, total, per_xcd);
-  else
-    attn_f32<64><<<grid, 256, 0, st>>>(q, k, v, idx, cnt, out, lse, s.nb, s.Nv, kmax, sl2, total, per_xcd);
+  auto launch = [&](auto d_c, auto kh_c) {
+    constexpr int KH = decltype(kh_c)::value;
+    attn_f32<decltype(d_c)::value, KH><<<grid, 256 * KH, 0, st>>>(q, k, v, idx, cnt, out, lse, s.nb, s.Nv, kmax, sl2, total, per_xcd);
+  };
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  // Up to one workgroup per CU, eight waves that take both halves of a block at once; beyond, four waves, so that a CU holds a
+  // second workgroup to compute while one stages.  KH = 1 / 2, 20 listed: d = 64, 128 blocks 50.2 / 37.1 us, 256: 50.6 / 38.7, 320:
+  // 68.6 / 70.6, 512: 72.8 / 73.7; d = 128, 128 blocks 87 / 64 us, 256: 88 / 69, 320: 117 / 126, 512: 127 / 135.
+  const bool few = total <= 256;
+  if (s.d == 128) few ? launch(std::integral_constant<int, 128>{}, I2{}) : launch(std::integral_constant<int, 128>{}, I1{});
+  else few ? launch(std::integral_constant<int, 64>{}, I2{}) : launch(std::integral_constant<int, 64>{}, I1{});
   return hipGetLastError();
 }
 

@@ -30,20 +30,21 @@ def edit(what, Q, K, V, Nv):
 @pytest.mark.parametrize("tail", [0, 44, 62, 32])  # padded rows of the last block: none, its second half empty, two keys, half
 @pytest.mark.parametrize("what", ["plain", "inf in v", "nan in v", "nan in q", "-inf logit", "beyond bf16", "tiny v",
                                   "tiny v, lower parts subnormal", "huge padding"])
-def test_f32_attention_special_values(usv, d, tail, what):
+@pytest.mark.parametrize("Hh", [2, 52])  # 10 query blocks: eight waves each; 260, just past one per CU: four waves each
+def test_f32_attention_special_values(usv, d, tail, what, Hh):
     nb, Nv = 5, 5 * 64 - tail
     rng = np.random.default_rng(d + tail)
-    Q, K, V = (rng.standard_normal((1, 2, nb * 64, d), dtype=np.float32) for _ in range(3))
+    Q, K, V = (rng.standard_normal((1, Hh, nb * 64, d), dtype=np.float32) for _ in range(3))
     edit(what, Q, K, V, Nv)
     lists = [[0, 1, 2, 3, 4], [4], [1, 4], [], [3, 2, 1]]
-    idx = np.full((1, 2, nb, nb), -1, np.int32)
-    cnt = np.zeros((1, 2, nb), np.int32)
+    idx = np.full((1, Hh, nb, nb), -1, np.int32)
+    cnt = np.zeros((1, Hh, nb), np.int32)
     for i, js in enumerate(lists):
         idx[:, :, i, :len(js)], cnt[:, :, i] = js, len(js)
     out, lse = usv.block_sparse_attn(gu.up(Q), gu.up(K), gu.up(V), gu.up(idx), gu.up(cnt), seq_valid=Nv, return_lse=True)
     o, l = gu.down(out), gu.down(lse)
     with np.errstate(all="ignore"):
-        for h in range(2):
+        for h in (0, 1, Hh - 1):
             for i, js in enumerate(lists):
                 got, rows = o[0, h, i * 64:(i + 1) * 64], max(0, min(64, Nv - i * 64))
                 assert (got[rows:] == 0).all()
