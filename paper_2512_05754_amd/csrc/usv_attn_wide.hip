@@ -45,6 +45,7 @@ namespace {
 
 constexpr int NW = 2;        // waves per workgroup
 constexpr int kItem = 4096;  // one item of the ring: 32 keys x 64 channels
+constexpr float kNoKey = 3.4028234e38f;  // reference of a row that has seen no key yet
 
 // One item, global -> LDS: instruction r lands at lds + 1024 r + 16 * lane.  Inline assembly so that the compiler does not
 // pair the DMA with a conservative "wait for all memory" before the next LDS read of ANOTHER item; completion is
@@ -291,11 +292,12 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[nt][x][r] = 0.f;
   // Per query tile (this lane's four queries).  nm = -(reference maximum) - p_shift in the log2 domain, identical in the four
-  // lanes of its query, 1e30 while no key has been seen (2^(s + 1e30) is never evaluated: the first live key raises it);
-  // l = this lane's partial row sum (its 8 keys per step).
+  // lanes of its query, kNoKey while no key has been seen (the first live key raises it, whatever its logit: with the largest
+  // float here no finite logit is beyond it, and a masked one still gives 2^-inf = 0); l = this lane's partial row sum (its 8
+  // keys per step).
   float nm[4], l[4];
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) nm[nt] = 1e30f, l[nt] = 0.f;
+  for (int nt = 0; nt < 4; ++nt) nm[nt] = kNoKey, l[nt] = 0.f;
   const float raise_at = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(kRescaleSlack - p_shift)));
 
   // Lane bases of the fragment reads; what else an address needs is an immediate or one XOR.
@@ -420,7 +422,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) {
         const float nm_new = fminf(nm[nt], -max_over_groups(mx[nt]) * scale_log2e - p_shift);
-        const float alpha = fast_exp2(nm_new - nm[nt]);  // nm = 1e30 -> 0
+        const float alpha = fast_exp2(nm_new - nm[nt]);  // nm = kNoKey -> 0
         nm[nt] = nm_new;
         l[nt] *= alpha;
 #pragma unroll

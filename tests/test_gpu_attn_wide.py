@@ -55,3 +55,30 @@ def test_wide_grids_against_the_oracle(usv, B, Hh, nb, d, kmax, ragged, ordered)
         got = l_h[b, h, i * 64:(i + 1) * 64]
         assert np.array_equal(np.isneginf(got), ~live), what
         assert not live.any() or np.abs(got[live] - ref_l[live]).max() <= 2e-2, what
+
+
+@pytest.mark.parametrize("d,Hh", [(128, 8), (128, 98), (64, 8), (64, 300)])  # 128 and 1568, 128 and 4800 query blocks
+def test_hugely_negative_logits_are_still_a_softmax(usv, d, Hh):
+    """Logits of -2^113 sqrt(d) (bf16 inputs reach them), all alike in a row: every listed key has the same weight, so a row is
+    the mean of its keys' V, whatever the size of the logits; both kernels, the reference raised from nothing on the first tile.
+    (Powers of two, so that the scaled logits are exact and their differences are 0 in any arithmetic.)"""
+    nb, kmax, Nv = 16, 3, 16 * 64 - 5
+    rng = np.random.default_rng(d + Hh)
+    v = rng.standard_normal((1, Hh, nb * 64, d), dtype=np.float32)
+    V = synth.f32_to_bf16_bits(v)
+    v = synth.as_f32(V).astype(np.float64)
+    q = torch.full((1, Hh, nb * 64, d), 2.0 ** 57, dtype=torch.bfloat16, device=gu.DEV)
+    k = torch.full((1, Hh, nb * 64, d), -2.0 ** 56, dtype=torch.bfloat16, device=gu.DEV)
+    idx = np.sort(np.argsort(rng.random((1, Hh, nb, nb)), axis=-1)[..., :kmax], axis=-1).astype(np.int32)
+    cnt = np.full((1, Hh, nb), kmax, np.int32)
+    out, lse = usv.block_sparse_attn(q, k, gu.up(V), gu.up(idx), gu.up(cnt), seq_valid=Nv, return_lse=True, out_dtype=torch.float32)
+    o, l = gu.down(out), gu.down(lse)
+    logit = float(q[0, 0, 0, 0]) * float(k[0, 0, 0, 0]) * np.sqrt(d)  # d terms / sqrt(d)
+    for h in (0, Hh // 2, Hh - 1):
+        for i in (0, 7, nb - 1):
+            keys = np.concatenate([np.arange(j * 64, min(j * 64 + 64, Nv)) for j in idx[0, h, i]])
+            rows = slice(i * 64, min(i * 64 + 64, Nv))
+            want = np.broadcast_to(v[0, h, keys].mean(axis=0), o[0, h, rows].shape)
+            # equal weights are exact in bf16: what is left is the fp32 sum of 192 values
+            np.testing.assert_allclose(o[0, h, rows], want, rtol=0, atol=192 * 2.0 ** -24 * 4)
+            np.testing.assert_allclose(l[0, h, rows], logit, rtol=1e-6)
