@@ -4,8 +4,10 @@
 //
 // The fp32 matrix pipe bounds a kernel that feeds it fp32 operands (157 TFLOP/s; 2 heads, 32768 tokens, 51 of 512 blocks:
 // 944 us at 117 TFLOP/s).  So every operand is split into three bf16 parts instead: x = x0 + x1 + x2 with x0 the nearest bf16
-// to x, x1 the nearest to x - x0 and x2 the rest, which fits 8 bits: the split is exact (24 bits of fp32 = 3 x 8), and the
-// products of parts are exact in the bf16 matrix core's fp32 accumulation.  Of the nine products six are formed:
+// to x, x1 the nearest to x - x0 and x2 the rest, which fits 8 bits: the split is exact (24 bits of fp32 = 3 x 8) as long as x2
+// has a place in bf16, that is for |x| >= 2^-110 and 0; and the products of parts are exact in the bf16 matrix core's fp32
+// accumulation.  (Splitting fp32 operands so is a published method: Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", 2019.)  Of the nine products six are formed:
 //   x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0);
 // the three left out are below 2^-24 |x y| together (typically 2^-27, of either sign), under one rounding of the fp32
 // sum.  Six products at sixteen times the rate leave 3/8 of the matrix time.
@@ -25,9 +27,10 @@
 // they stand, the contraction slots of the P^T operand.
 //
 // fp32_block: the same block with fp32 operands on the fp32 matrix cores, for what a split cannot carry: infinities and NaN
-// (inf - inf), values the rounding to bf16 takes past its largest, and results so small that the lower parts run out of
-// exponent.  All of these show in the row sum or in the result (NaN, infinite, below 2^-100), and the workgroup then
-// computes its block again this way.
+// (inf - inf), values the rounding to bf16 takes past its largest, and lower parts that run out of exponent where that matters.
+// The first two show in the row sum or in the result; for the third the workgroup keeps the largest magnitudes it has split
+// (four instructions per eight values: 632 -> 642 us there) and looks at the size of its results: the bounds stand at kTiny.  Such a workgroup computes its
+// block again this way.
 #include <type_traits>
 
 #include "usv_attn_bf16.h"
@@ -241,7 +244,7 @@ __device__ __forceinline__ void fp32_block(unsigned char* smem, const float* __r
 }
 
 // ---- operands in three bf16 parts ---------------------------------------------------------------
-struct Split {  // eight values: x = p[0] + p[1] + p[2], exactly
+struct Split {  // eight values: x = p[0] + p[1] + p[2], exactly from 2^-110 on
   bf16x8 p[3];
 };
 __device__ __forceinline__ Split split8(const float (&x)[8]) {
@@ -269,6 +272,23 @@ __device__ __forceinline__ Split split8(const float (&x)[8]) {
   return s;
 }
 
+// acc = the largest of |x[0..7]| and acc, NaN left out.  (assembly: without the moves that quiet a NaN ahead of every fmaxf)
+__device__ __forceinline__ void largest8(float& acc, const float (&x)[8]) {
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(acc) : "v"(x[e]), "v"(x[e + 1]));
+}
+
+// What three parts cannot carry.  A part below 2^-133 has no place in bf16 (and below 2^-126 it need not keep its last bits), so
+// an operand is good to 2^-24 of itself or to 2^-125, whichever is more, and so is a product.  That is too little where
+//  - a Q or K beside it is larger than 2^80 / scale: up to there the logits move by less than 2^-36;
+//  - a result is below 2^-80, or below 2^-80 of the largest |V| of its channels (a small p against a large V): down to there
+//    2^18 keys' errors of 2^-125 stay under 2^-26 of it.  A result of exactly 0 is below both, but V may well be 0 there: it
+//    counts if those channels hold nothing but values below 2^-80, or if a look through the listed rows of V (only then) finds a
+//    subnormal value.
+// Overflows, infinities and NaN make the row sum or the result infinite or NaN.
+constexpr float kTiny = 0x1p-80f;
+constexpr float kQkLimit = 0x1p80f;
+
 __device__ __forceinline__ f32x4 mfma(const bf16x8& a, const bf16x8& b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -278,7 +298,7 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
                                                    const float* __restrict__ v, const int32_t* __restrict__ idx,
                                                    const int32_t* __restrict__ cnt, float* __restrict__ out,
                                                    float* __restrict__ lse, int nb, int Nv, int kmax, float scale_log2e,
-                                                   int total, int per_xcd) {
+                                                   float qk_limit, int total, int per_xcd) {
   constexpr int KS = D / 32, DT = D / 16;      // channel steps of the first product, 16-channel tiles of the second
   constexpr int kThreads = 256 * KH;
   constexpr int kKeys = 32 * KH;               // keys per step
@@ -292,7 +312,9 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
   constexpr int kExchange = KH == 2 ? 4 * XROWS * 64 : 0;  // floats
   static_assert((kExchange + kBlock * LD) * (int)sizeof(float) <= kLds, "exchange area and output rows overlay the planes");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
-  __shared__ int redo[4];
+  __shared__ int redo[4 * KH];
+  __shared__ unsigned v_top[CH];  // largest |V| that was staged, per 8 channels (bits of the float)
+  __shared__ int subnormal_v;
 
   const int work = xcd_contiguous_id(blockIdx.x, per_xcd);  // neighbouring query blocks share K and V in an XCD's L2
   if (work >= total) return;  // whole workgroup leaves before any barrier
@@ -335,6 +357,7 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
 
   // Q^T fragments: query row 16 qw + c16, channels 32 t + 8 G .. + 8
   Split qf[KS];
+  float q_top = 0.f, k_top = 0.f, v_max = 0.f;  // largest magnitudes this lane splits (a thread's pieces share their channels)
   {
     const float* qp = q + head_off + (long long)(i * kBlock + qw * 16 + c16) * D + G * 8;
 #pragma unroll
@@ -342,6 +365,7 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
       float x[8];
       *reinterpret_cast<float4*>(x) = reinterpret_cast<const float4*>(qp + 32 * t)[0];
       *reinterpret_cast<float4*>(x + 4) = reinterpret_cast<const float4*>(qp + 32 * t)[1];
+      largest8(q_top, x);
       qf[t] = split8(x);
     }
   }
@@ -355,6 +379,8 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
 
   const unsigned char* const ks = smem;
   const unsigned char* const vs = smem + 3 * kPlane;
+  if (tid < CH) v_top[tid] = 0;  // (the barriers of the loop stand between this and the first maximum)
+  if (tid == 0) subnormal_v = 0;
 
   constexpr int kSteps = 2 / KH;  // steps per listed block
   for (int st = 0; st < kSteps * n_list; ++st) {
@@ -367,6 +393,7 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
       float x[8];
       *reinterpret_cast<float4*>(x) = kraw[u][0];
       *reinterpret_cast<float4*>(x + 4) = kraw[u][1];
+      largest8(k_top, x);
       const Split a = split8(x);
 #pragma unroll
       for (int part = 0; part < 3; ++part) *reinterpret_cast<bf16x8*>(smem + part * kPlane + k_at(row, c)) = a.p[part];
@@ -376,6 +403,7 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
 #pragma unroll
         for (int y = 0; y < 8; ++y) x[y] = row < nkeys ? x[y] : 0.f;
       }
+      largest8(v_max, x);
       const Split b = split8(x);
 #pragma unroll
       for (int part = 0; part < 3; ++part)
@@ -472,7 +500,10 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
   }
 
   // ---- merge the key halves, stage the rows row-major, store coalesced ----
-  __syncthreads();  // every wave is done with the last planes
+  v_max = max_over_groups(v_max);
+  if (CH == 8) v_max = fmaxf(v_max, __shfl_xor(v_max, 8));
+  if (n_list > 0 && lane < CH) atomicMax(&v_top[lane], __float_as_uint(v_max));  // (not negative: the bits order as the floats do)
+  __syncthreads();  // every wave is done with the last planes; v_top is complete
   float lt = sum_over_groups(l);
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
@@ -507,23 +538,53 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
   const bool mine = token < Nv && n_list > 0 && kh == 0;
   const bool live = mine && lt > 0.f;  // lt == 0: every listed key is padding
   const float inv = live ? 1.f / lt : 0.f;
-  bool bad = mine && !(lt < INFINITY);
+  bool bad = (mine && (!(lt < INFINITY) || q_top >= qk_limit)) || k_top >= qk_limit;
+  bool small = false, zero = false;
+  float finite = 0.f;  // NaN as soon as a result is not finite
   float* stage = rows + (qw * 16 + c16) * LD;
+  auto least = [&](float top) { return fmaxf(kTiny, top * kTiny); };
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
     float y[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       y[r] = live ? o[dt][r] * inv : 0.f;
-      const float a = fabsf(y[r]);
-      bad |= !(a < INFINITY) || (a < 0x1p-100f && a > 0.f);
+      finite = fmaf(y[r], 0.f, finite);
     }
+    small |= fminf(fminf(fabsf(y[0]), fabsf(y[1])), fminf(fabsf(y[2]), fabsf(y[3]))) < least(__uint_as_float(v_top[2 * dt + (G >> 1)]));
     if (kh == 0) *reinterpret_cast<float4*>(stage + 16 * dt + 4 * G) = make_float4(y[0], y[1], y[2], y[3]);
   }
-  const int any_bad = __any(bad);
-  if (lane == 0 && kh == 0) redo[qw] = any_bad;
+  bad |= finite != 0.f;
+  if (__any(live && small)) {
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const float top = __uint_as_float(v_top[2 * dt + (G >> 1)]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float a = fabsf(o[dt][r] * inv);
+        bad |= live && a < least(top) && (a > 0.f || (top > 0.f && top < kTiny));
+        zero |= live && a == 0.f && top > 0.f;
+      }
+    }
+  }
+  const int any_bad = __any(bad), any_zero = __any(zero);
+  if (lane == 0) redo[wave] = any_bad | any_zero << 1;
   __syncthreads();
-  if (redo[0] | redo[1] | redo[2] | redo[3]) {
+  int again = 0;
+#pragma unroll
+  for (int w = 0; w < 4 * KH; ++w) again |= redo[w];
+  if (again == 2) {  // a result of 0 beside other values: is V 0 there, or too small to be split?
+    bool sub = false;
+    for (int n = 0; n < n_list; ++n) {
+      const int jn = block_at(n), rows_n = min(kBlock, Nv - jn * kBlock);
+      const unsigned* vn = reinterpret_cast<const unsigned*>(v + head_off + (long long)jn * kBlock * D);
+      for (int e = tid; e < rows_n * D; e += kThreads) sub |= (vn[e] & 0x7fffffffu) - 1u < 0x007fffffu;
+    }
+    if (__any(sub) && lane == 0) subnormal_v = 1;
+    __syncthreads();
+    again = subnormal_v;
+  }
+  if (again) {
     fp32_block<D>(smem, q, k, v, idx, n_list, out, lse, blk, nb, Nv, kmax, scale_log2e);
     return;
   }
@@ -545,7 +606,8 @@ hipError_t launch_attn_f32(const float* q, const float* k, const float* v, const
   const float sl2 = scale * kLog2e;
   auto launch = [&](auto d_c, auto kh_c) {
     constexpr int KH = decltype(kh_c)::value;
-    attn_f32<decltype(d_c)::value, KH><<<grid, 256 * KH, 0, st>>>(q, k, v, idx, cnt, out, lse, s.nb, s.Nv, kmax, sl2, total, per_xcd);
+    attn_f32<decltype(d_c)::value, KH><<<grid, 256 * KH, 0, st>>>(q, k, v, idx, cnt, out, lse, s.nb, s.Nv, kmax, sl2,
+                                                                kQkLimit / fmaxf(scale, 1.f), total, per_xcd);
   };
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;

@@ -1,5 +1,6 @@
 """The fp32 attention kernel where splitting its operands into bf16 parts could go wrong: infinities, NaN, values beyond the largest
-bf16, values whose lower parts run out of exponent, padding of any finite value, halves of a block without a valid key."""
+bf16, values whose lower parts run out of exponent (in V, and in one of Q and K with the other as large; weights that do so
+beside values as large), padding of any finite value, halves of a block without a valid key."""
 import numpy as np
 import pytest
 import torch
@@ -23,13 +24,28 @@ def edit(what, Q, K, V, Nv):
     if what == "beyond bf16": V[0, 0, 70, 5] = 3.4e38
     if what == "tiny v": V[..., 7] *= 1e-33
     if what == "tiny v, lower parts subnormal": V[..., 7] *= 1e-36
+    if what == "subnormal v": V[..., 7] *= 1e-41
+    if what == "zero v": V[..., 7] = 0
+    if what == "huge q, tiny k":  # logits as of "plain"; the lower parts of k have no place in bf16
+        Q *= np.float32(2.0 ** 118)
+        K *= np.float32(2.0 ** -118)
+    if what == "tiny q, huge k":
+        Q *= np.float32(2.0 ** -120)
+        K *= np.float32(2.0 ** 120)
+    if what == "tiny weight, huge v":  # weights of about 2^-123 against values of 2^127
+        Q *= np.float32(0.1)
+        Q[..., 3] = 8
+        K[..., 3] = 0
+        K[:, :, 70, 3] = -85.5 * np.sqrt(Q.shape[-1]) / 8
+        V[:, :, 70, 5] = 2.0 ** 127
     if what == "huge padding": Q[:, :, Nv:], K[:, :, Nv:], V[:, :, Nv:] = FLT_MAX, FLT_MAX, -FLT_MAX
 
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("tail", [0, 44, 62, 32])  # padded rows of the last block: none, its second half empty, two keys, half
 @pytest.mark.parametrize("what", ["plain", "inf in v", "nan in v", "nan in q", "-inf logit", "beyond bf16", "tiny v",
-                                  "tiny v, lower parts subnormal", "huge padding"])
+                                  "tiny v, lower parts subnormal", "subnormal v", "zero v", "huge q, tiny k", "tiny q, huge k",
+                                  "tiny weight, huge v", "huge padding"])
 @pytest.mark.parametrize("Hh", [2, 52])  # 10 query blocks: eight waves each; 260, just past one per CU: four waves each
 def test_f32_attention_special_values(usv, d, tail, what, Hh):
     nb, Nv = 5, 5 * 64 - tail
@@ -65,5 +81,12 @@ def test_f32_attention_special_values(usv, d, tail, what, Hh):
                 fin = np.isfinite(ref)
                 scale = np.abs(np.where(np.isfinite(V[0, h, keys]), V[0, h, keys], 0)).astype(np.float64).mean(axis=0)
                 err = np.abs(np.where(fin, got - ref, 0))
+                if what == "tiny weight, huge v":
+                    # in channel 5 stands this one key's weight times 2^127.  Its product q k of about 970 rounds by 2^-15 in each of at
+                    # most 32 sums of a partial sum, times log2(e) / sqrt(d) < 2^-2.4; the exponent of 123 by 2^-18 twice
+                    rel = (32 * 2.0 ** -17.4 + 2 * 2.0 ** -18) * np.log(2)
+                    own = (P / P.sum(axis=1, keepdims=True))[:, keys == 70].sum(axis=1) * 2.0 ** 127
+                    assert (err[:, 5] <= rel * own + 1e-6).all(), (h, i, (err[:, 5] / own).max())
+                    err[:, 5] = 0
                 # (values of 1e-36 leave results a few of whose last bits lie under the fp32 normal range)
-                assert (err <= 1e-5 * scale + 2.0 ** -126 * 1e-5 + 2.0 ** -149).all(), (what, h, i, (err / scale).max())
+                assert (err <= 1e-5 * scale + 2.0 ** -126 * 1e-5 + 2.0 ** -149).all(), (what, h, i, (err / np.maximum(scale, 1e-45)).max())
