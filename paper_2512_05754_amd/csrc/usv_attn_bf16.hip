@@ -94,14 +94,15 @@ __device__ __forceinline__ void dma_tile<2>(const void* gbase, const int (&voff)
       : "memory");
 }
 
-// The LDS ring has kSlots tile slots; a tile is requested LEAD tiles before it is used.  Two workgroups per CU.
+// The LDS ring has kSlots tile slots; a tile is requested LEAD tiles before it is used.  WGS: workgroups per CU (= waves per
+// SIMD) that the register budget is sized for.
 // RASTER: Q, K, V and the output are in raster token order (any strides); `ras.order[p]` gives the
 // raster index of cube-major position p.  Every wave fetches the 16 order entries of the rows it
 // requests ahead of the tile (one more 4-byte-per-lane DMA per tile, into a small LDS ring that only
 // this wave reads), turns them into the per-lane global offsets of its DMA instructions, and the
 // epilogue stores each row at its raster position: no reordered copy of any tensor exists.
-template <int D, bool OUT_F32, bool RASTER>
-__global__ __launch_bounds__(kThreads, 2) void attn_bf16(const uint16_t* __restrict__ q,
+template <int D, bool OUT_F32, int WGS, bool RASTER>
+__global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __restrict__ q,
                                                                 const uint16_t* __restrict__ k,
                                                                 const uint16_t* __restrict__ v,
                                                                 const int32_t* __restrict__ idx,
@@ -310,6 +311,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16(const uint16_t* __restr
 
   // per-lane LDS byte offsets of the fragment reads (loop invariant)
   // K fragment of key tile mt, k-step t: key row 32 kh + 16 mt + c16, chunk 4 t + G; +16 rows is a constant
+  // (both tables are XOR patterns: kfrag[t] = kfrag[0] ^ (t << 6) and vfrag[dt] = vfrag[0] ^ (dt << 5), because the
+  // swizzles only touch address bits that t and dt alone set.  With three workgroups per CU there are no registers to
+  // spare and the entries are derived with one v_xor per use; with two they stay in registers.)
+  constexpr bool kLean = WGS >= 3;
   int kfrag[KS];
 #pragma unroll
   for (int t = 0; t < KS; ++t) kfrag[t] = T::k_off(kh * 32 + c16, 4 * t + G);
@@ -368,24 +373,30 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16(const uint16_t* __restr
       // fragments are read in batches and awaited once per batch: every s_waitcnt costs the
       // wave an issue slot, and the other waves of the SIMD cover the LDS latency
       const unsigned char* kb = smem + kslot * T::kBytes;
-      bf16x8 kf[KS][2];
+      if constexpr (kLean) asm volatile("" : "+v"(kfrag[0]));  // keeps the XORs in the loop (hoisted, they are the table again)
+      constexpr int KB = kLean ? 1 : KS;  // k-steps per batch (register budget)
 #pragma unroll
-      for (int t = 0; t < KS; ++t)
+      for (int t0 = 0; t0 < KS; t0 += KB) {
+        bf16x8 kf[KB][2];
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-          kf[t][mt] = *reinterpret_cast<const bf16x8*>(kb + kfrag[t] + mt * 16 * T::kRowBytes);
-      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-      // the fences keep the batch together: reads, one wait, back-to-back MFMAs
-      __builtin_amdgcn_sched_barrier(0);
+        for (int t = 0; t < KB; ++t)
 #pragma unroll
-      for (int t = 0; t < KS; ++t)
+          for (int mt = 0; mt < 2; ++mt)
+            kf[t][mt] = *reinterpret_cast<const bf16x8*>(kb + (kLean ? kfrag[0] ^ ((t0 + t) << 6) : kfrag[t0 + t]) +
+                                                         mt * 16 * T::kRowBytes);
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+        // the fences keep each batch together: reads, one wait, back-to-back MFMAs
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int t = 0; t < KB; ++t)
 #pragma unroll
-          for (int nt = 0; nt < 2; ++nt)
-            set_quarter(s, 2 * mt + nt,
-                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][mt], qf[nt][t], quarter(s, 2 * mt + nt), 0, 0, 0));
-      __builtin_amdgcn_sched_barrier(0);
+          for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+              set_quarter(s, 2 * mt + nt,
+                          __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][mt], qf[nt][t0 + t], quarter(s, 2 * mt + nt), 0, 0, 0));
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     // V(n) has landed; only the kSlots-2 items requested after it may still be in flight (near the
     // end of the list fewer are, so the last LEAD tiles simply wait for everything)
@@ -482,25 +493,30 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16(const uint16_t* __restr
     // ---- O^T += V^T P^T: one MFMA per (d sub-tile, query tile), its 32 contraction slots = this wave's keys ----
     {
       const unsigned char* vb = smem + vslot * T::kBytes;
-      bf16x8 vf[DT];
+      if constexpr (kLean) asm volatile("" : "+v"(vfrag[0]));
+      constexpr int VB = kLean ? 2 : DT;  // d sub-tiles per batch
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        const unsigned char* p = vb + vfrag[dt];
-        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)p);
-        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (short4v __attribute__((address_space(3)))*)(p + 16 * T::kRowBytes));
-        const short8v both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        __builtin_memcpy(&vf[dt], &both, sizeof(bf16x8));
+      for (int dt0 = 0; dt0 < DT; dt0 += VB) {
+        bf16x8 vf[VB];
+#pragma unroll
+        for (int dd = 0; dd < VB; ++dd) {
+          const unsigned char* p = vb + (kLean ? vfrag[0] ^ ((dt0 + dd) << 5) : vfrag[dt0 + dd]);
+          const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)p);
+          const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (short4v __attribute__((address_space(3)))*)(p + 16 * T::kRowBytes));
+          const short8v both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+          __builtin_memcpy(&vf[dd], &both, sizeof(bf16x8));
+        }
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int dd = 0; dd < VB; ++dd)
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt)
+            set_quarter(o[nt][(dt0 + dd) >> 2], (dt0 + dd) & 3,
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dd], pf[nt], quarter(o[nt][(dt0 + dd) >> 2], (dt0 + dd) & 3), 0, 0, 0));
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-          set_quarter(o[nt][dt >> 2], dt & 3,
-                      __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pf[nt], quarter(o[nt][dt >> 2], dt & 3), 0, 0, 0));
-      __builtin_amdgcn_sched_barrier(0);
     }
 
     // pin each accumulator tuple to one 16-register unit once per tile (see quarter())
@@ -641,10 +657,20 @@ hipError_t run(const AttnBf16Args& a, hipStream_t st) {
   const bool wide = D == 128 ? (total > 768 && total <= 1024) || total > 1536 : total > 4608;
   if (wide) return launch_attn_wide(a, OUT_F32, st);
   const int per_xcd = (int)((total + kNumXcd - 1) / kNumXcd);
-  attn_bf16<D, OUT_F32, RASTER><<<(unsigned)per_xcd * kNumXcd, kThreads, 0, st>>>(
-      static_cast<const uint16_t*>(a.q), static_cast<const uint16_t*>(a.k), static_cast<const uint16_t*>(a.v), a.idx, a.cnt,
-      a.out, a.lse, s.nb, s.Nv, a.kmax, a.scale * kLog2e, probability_shift(a.kmax), (int)total, per_xcd, a.fuse, a.ras,
-      a.work_order, stream_output(s));
+  auto launch = [&](auto wgs_c) {
+    attn_bf16<D, OUT_F32, decltype(wgs_c)::value, RASTER><<<(unsigned)per_xcd * kNumXcd, kThreads, 0, st>>>(
+        static_cast<const uint16_t*>(a.q), static_cast<const uint16_t*>(a.k), static_cast<const uint16_t*>(a.v), a.idx, a.cnt,
+        a.out, a.lse, s.nb, s.Nv, a.kmax, a.scale * kLog2e, probability_shift(a.kmax), (int)total, per_xcd, a.fuse, a.ras,
+        a.work_order, stream_output(s));
+  };
+  // Two workgroups per CU, with registers for every fragment of a tile at once.  Three where the L2 serves the tiles anyway (at
+  // least half of the blocks listed) and there are more query blocks than two per CU hold: the third pays for the smaller batches its
+  // registers allow.  Two / three, d = 128, all blocks listed: 640 query blocks 137 / 125 us, 768: 166 / 157, 1280: 424 / 413; half
+  // of them: 74 / 68, 90 / 85, 222 / 215.  (Up to 512 query blocks two are no slower, at d = 64 2 % faster, and raster mode has no
+  // registers for a third.)
+  constexpr bool kCanThree = D == 128 && !RASTER;
+  if (kCanThree && 2LL * a.kmax >= s.nb && total > 512) launch(std::integral_constant<int, kCanThree ? 3 : 2>{});
+  else launch(std::integral_constant<int, 2>{});
   return hipGetLastError();
 }
 

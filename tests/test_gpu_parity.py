@@ -288,8 +288,8 @@ def test_keep_all_equals_dense_attention(usv, dtype, d):
 
 @pytest.mark.parametrize("nb,k", [(200, 70), (200, 67), (140, 100), (130, 129), (330, 64), (330, 65)])
 def test_long_lists_cross_the_index_reload_boundary(usv, nb, k):
-    """Lists longer than 64 entries (the kernel keeps 64 block ids in a register and reloads), in both
-    launch shapes (k < nb/2: deep ring; k >= nb/2: three workgroups per CU), with a padded last block."""
+    """Lists longer than 64 entries (the kernel keeps 64 block ids in a register and reloads), short against the number of
+    blocks and dense, with a padded last block (at most 330 query blocks: two workgroups per CU)."""
     w = Workload(f"long_{nb}_{k}", 1, 1, nb * 64 - 11, 128, "bf16", 2.0, k, seed=71 + nb + k)
     (Q, K, V), S, idx, cnt, out, lse = run_pipeline(usv, w, out_dtype=torch.float32)
     ridx, rcnt = orc.select_topk(S, w.keep, w.seq_valid)
@@ -300,30 +300,34 @@ def test_long_lists_cross_the_index_reload_boundary(usv, nb, k):
     gu.assert_attn_close(got, np.stack([ref[i][0] for i in blocks]), "bf16", w.name)
 
 
-@pytest.mark.parametrize("nb,kmax,d", [(64, 24, 128), (64, 24, 64), (24, 24, 128), (40, 40, 64)],
-                         ids=["sparse_shape_d128", "sparse_shape_d64", "dense_shape_d128", "dense_shape_d64"])
-def test_every_list_length_in_both_launch_shapes(usv, nb, kmax, d):
-    """Query cube i gets a list of i % (kmax + 1) blocks: every length from 0 to kmax, i.e. every phase of the
-    K/V ring and every shape of its last, partial round, in the sparse launch shape (kmax < nb/2: five slots)
-    and in the dense-like one (three slots)."""
-    w = Workload("lengths", 1, 2, nb * 64 - 11, d, "bf16", 2.0, kmax, seed=300 + nb + d)
+@pytest.mark.parametrize("nb,kmax,d,Hh", [(64, 24, 128, 2), (64, 24, 64, 2), (24, 24, 128, 2), (40, 40, 64, 2), (24, 24, 128, 22),
+                                          (30, 15, 128, 18), (24, 24, 128, 40), (24, 24, 64, 200)],
+                         ids=["few_d128", "few_d64", "few_dense_d128", "few_dense_d64", "three_per_cu", "three_per_cu_half",
+                              "wide_d128", "wide_d64"])
+def test_every_list_length_in_every_launch_shape(usv, nb, kmax, d, Hh):
+    """Query cube i gets a list of i % (kmax + 1) blocks (starting elsewhere in every head): every length from 0 to kmax, i.e.
+    every phase of the K/V ring and every shape of its last, partial round, with two workgroups per CU (few query blocks), with
+    three (dense lists on more than 512 query blocks, d = 128), and in the kernel for grids that fill the chip."""
+    w = Workload("lengths", 1, Hh, nb * 64 - 11, d, "bf16", 2.0, kmax, seed=300 + nb + d)
     rng = np.random.default_rng(nb * 7 + kmax + d)
     Q, K, V = synth.gen_qkv(w)
     nbv = (w.seq_valid + 63) // 64
-    idx = np.full((1, 2, nb, kmax), -1, dtype=np.int32)
-    cnt = np.zeros((1, 2, nb), dtype=np.int32)
-    for h in range(2):
+    idx = np.full((1, Hh, nb, kmax), -1, dtype=np.int32)
+    cnt = np.zeros((1, Hh, nb), dtype=np.int32)
+    for h in range(Hh):
         for i in range(nb):
             c = (i + 3 * h) % (kmax + 1)
             idx[0, h, i, :c] = np.sort(rng.choice(nbv, size=c, replace=False))
             cnt[0, h, i] = c
     out, lse = usv.block_sparse_attn(gu.up(Q), gu.up(K), gu.up(V), gu.up(idx), gu.up(cnt), seq_valid=w.seq_valid,
                                      return_lse=True, out_dtype=torch.float32)
-    O, L = orc.block_sparse_attn(synth.as_f32(Q), synth.as_f32(K), synth.as_f32(V), idx, cnt, w.seq_valid)
-    gu.assert_attn_close(gu.down(out), O, "bf16", f"nb {nb} kmax {kmax}")
+    some = sorted({0, 1, Hh // 2, Hh - 1})  # (heads; Hh = 2: both)
+    O, L = orc.block_sparse_attn(*(synth.as_f32(x[:, some]) for x in (Q, K, V)), idx[:, some], cnt[:, some], w.seq_valid)
+    gu.assert_attn_close(gu.down(out)[:, some], O, "bf16", f"nb {nb} kmax {kmax}")
     live = np.isfinite(L)
-    assert np.array_equal(np.isneginf(gu.down(lse)), ~live)
-    assert np.abs(gu.down(lse)[live] - L[live]).max() <= 2e-2
+    got = gu.down(lse)[:, some]
+    assert np.array_equal(np.isneginf(got), ~live)
+    assert np.abs(got[live] - L[live]).max() <= 2e-2
 
 
 def test_online_softmax_survives_large_logit_offsets(usv):
