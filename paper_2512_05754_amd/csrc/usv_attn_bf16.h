@@ -160,12 +160,14 @@ __device__ __forceinline__ void fuse4(float4& val, const float4& gf, const float
   val.z = fmaf(gf.z, val.z, gc.z * cz.z);
   val.w = fmaf(gf.w, val.w, gc.w * cz.w);
 }
-// gate_off in elements
+// gate_off in elements.  The cube-level row is requested first: behind the gates, whose loads are awaited where they branch, it
+// is one more round trip per pass (768 query blocks, 6 listed, both gates 38.7 -> 41.5 us).
 __device__ __forceinline__ void fuse4(float4& val, const FuseArgs& fuse, long long coarse_off, long long gate_off) {
+  const float4 cz = *reinterpret_cast<const float4*>(fuse.coarse + coarse_off);
   float4 gf = make_float4(1.f, 1.f, 1.f, 1.f), gc = gf;
   if (fuse.gate_fine) gf = load_bf16x4(fuse.gate_fine + gate_off);
   if (fuse.gate_coarse) gc = load_bf16x4(fuse.gate_coarse + gate_off);
-  fuse4(val, gf, gc, *reinterpret_cast<const float4*>(fuse.coarse + coarse_off));
+  fuse4(val, gf, gc, cz);
 }
 
 }  // namespace
