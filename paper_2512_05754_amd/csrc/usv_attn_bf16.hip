@@ -643,19 +643,50 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
   }
 }
 
-template <int D, bool OUT_F32, bool RASTER>
-hipError_t run(const AttnBf16Args& a, hipStream_t st) {
+// Which kernel takes a launch.  All times this kernel / wide.
+inline bool wide_is_faster(const AttnBf16Args& a) {
   const Dims& s = a.s;
   const long long total = s.bh() * s.nb;
   // The wide kernel puts four two-wave workgroups on a CU at d = 128 (six at d = 64), this one two of four waves, each
   // twice as fast through its list, so 1024 (1536) or 512 query blocks make a round of the chip.  Below a full round of
-  // the wide kernel, and where it would leave half of its second one empty, this one is faster; measured, this one / wide:
+  // the wide kernel, and where it would leave half of its second one empty, this one is faster:
   //   d = 128, 25 listed: 512 blocks 38 / 54 us, 768: 58.6 / 58.5 (51 listed: 99 / 107), 1024: 69.7 / 66.2, 1536: 113 / 117
   //   (51 listed: 202 / 216), 2048: 160 / 151; 8 listed: 768 blocks 27.5 / 28.7, 1024: 32.8 / 31.2, 1536: 47 / 52
   //   d = 64 (half the matrix work per fetched byte and per exponential), 25 listed: 1024 blocks 41.4 / 42.0 us, 1536: 57.7 /
-  //   58.0, 2048: 74 / 85, 2560: 92 / 100, 5120: 213 / 213, 6144 (51 listed): 408 / 385
-  const bool wide = D == 128 ? (total > 768 && total <= 1024) || total > 1536 : total > 4608;
-  if (wide) return launch_attn_wide(a, OUT_F32, st);
+  //   58.0, 2048: 74 / 85, 2560: 92 / 100, 5120: 213 / 213 (128: 747 / 774), 6144 (51 listed): 408 / 385; heads of more than 640 blocks
+  //   gain from the start of the sweep: 1182 blocks x 4, 71 listed 537 / 447
+  //   raster order (the wide kernel's address arithmetic is the longer one): 2048 query blocks, 26 listed 152 / 162
+  // Heads beyond the L2 of an XCD (below: from 17.5 MiB of K and V on): twice as many sweeps run together in the wide kernel, and
+  // from some list length on they drift apart further than the start of a sweep can foresee (its rule is in usv_attn_wide.hip).
+  // Times in ms; k = kmax.
+  const long long k = a.kmax, nb = s.nb;
+  if (s.d == 64) {
+    // 1700 blocks x 6 heads: k = 272 4.75 / 3.57, 340 4.09 / 4.62; with a work order 136 2.35 / 1.79, 204 2.45 / 2.64, 340 3.92 / 3.99
+    const bool drifts = nb > 1280 && 4 * k < nb && (a.work_order ? 10 : 6) * k > nb;
+    return total > (nb > 640 ? 4608 : 5376) && !drifts;
+  }
+  if (total <= 768 || (total > 1024 && total <= (a.ras.order ? 2048 : 1536))) return false;
+  // In its single full round every list runs at once, half as fast: a work order puts the longest lists of a short head on the
+  // same CUs (8 heads x 128 blocks, lists of 16..128 blocks 165 / 183 us, 24 x 40, 5..40: 65 / 73; 2 x 512, 64..512: 916 / 810).
+  if (total <= 1024 && a.work_order && nb <= 128) return false;
+  if (nb <= 560) return true;
+  if (a.work_order) {
+    // 600 blocks x 40 heads, k = 96 5.43 / 4.99; 680 x 40, 109 6.75 / 8.40; 768 x 12, 61 1.38 / 1.48, 123 2.48 / 2.86; 1182 x 3, 59
+    // 0.62 / 0.68 but x 40, 59 8.06 / 7.62; 1182 x 4, 95 1.12 / 1.35; 768 x 12, 154 3.05 / 2.83; 1182 x 6, 236 3.60 / 4.54, 390 5.72 / 5.74
+    if (6 * k <= nb) return nb <= 640 || (k <= 64 && (24 * k <= nb || (16 * k <= nb && total > 12000)));
+    return nb <= 1024 || 3 * k >= nb;
+  }
+  // 600 x 24, 96 3.85 / 3.13; 680 x 40, 82 6.63 / 6.08; 768 x 12, 61 1.83 / 1.49, 92 1.99 / 2.17, 154 3.11 / 4.11, 253 4.86 / 4.59;
+  // 1182 x 4, 142 2.30 / 2.02 but x 12, 142 5.11 / 5.95; 1182 x 6, 236 3.71 / 4.98; 1700 x 2, 714 5.41 / 6.25
+  if (5 * k >= 2 * nb) return nb <= 1280;
+  return 6 * k <= nb && (nb <= 640 || k <= 84 || (nb > 1024 && total <= 7168));
+}
+
+template <int D, bool OUT_F32, bool RASTER>
+hipError_t run(const AttnBf16Args& a, hipStream_t st) {
+  const Dims& s = a.s;
+  const long long total = s.bh() * s.nb;
+  if (wide_is_faster(a)) return launch_attn_wide(a, OUT_F32, st);
   const int per_xcd = (int)((total + kNumXcd - 1) / kNumXcd);
   auto launch = [&](auto wgs_c) {
     attn_bf16<D, OUT_F32, decltype(wgs_c)::value, RASTER><<<(unsigned)per_xcd * kNumXcd, kThreads, 0, st>>>(

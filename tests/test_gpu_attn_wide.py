@@ -17,11 +17,14 @@ CASES = [
     (1, 22, 70, 128, 11, False),    # just above one and a half rounds; later lists start inside
     (1, 4, 390, 128, 64, False),    # 64 entries: the whole list in one register
     (1, 4, 390, 128, 65, False),    # ... and one more
-    (1, 2, 900, 128, 130, False),   # more than 128 entries, one head's K and V 29 MB: the deeper ring
+    (1, 2, 900, 128, 130, False),   # more than 128 entries, one head's K and V 29 MB (stays with the kernel for small grids)
+    (1, 2, 1100, 128, 130, False),  # ... 36 MB: the deeper ring (in index order)
+    (1, 2, 900, 128, 380, False),   # the deeper ring, six registers of entries, with and without a work order
     (1, 3, 800, 128, 3, True),      # deeper ring, lists of 0 to 3 entries
     (2, 12, 70, 128, 9, True),      # ragged, empty lists among them
-    (1, 47, 101, 64, 16, False),    # d = 64, four rounds
-    (1, 12, 400, 64, 66, True),     # d = 64, ragged, up to 66 entries
+    (1, 54, 101, 64, 16, False),    # d = 64, four rounds
+    (1, 14, 400, 64, 66, True),     # d = 64, ragged, up to 66 entries
+    (1, 7, 670, 64, 20, False),     # d = 64, a head of more than 640 blocks
 ]
 
 
@@ -57,7 +60,36 @@ def test_wide_grids_against_the_oracle(usv, B, Hh, nb, d, kmax, ragged, ordered)
         assert not live.any() or np.abs(got[live] - ref_l[live]).max() <= 2e-2, what
 
 
-@pytest.mark.parametrize("d,Hh", [(128, 8), (128, 98), (64, 8), (64, 300)])  # 128 and 1568, 128 and 4800 query blocks
+# Grids that fill the chip and stay with the kernel for small ones all the same: its sweeps start at the first entry, so the
+# result does not depend on the order the query blocks are walked in, bit for bit.
+@pytest.mark.parametrize("B,Hh,nb,d,kmax", [
+    (1, 4, 650, 128, 100),    # a head beyond the L2, lists that drift apart
+    (1, 3, 660, 128, 66),     # ... with a work order, lists past 64 entries
+    (2, 12, 41, 128, 20),     # one full round, ragged, a short head with a work order
+    (1, 2, 1200, 128, 300),   # 1/6 to 1/3 of the blocks of a larger head, with and without
+    (1, 4, 1300, 64, 180),    # d = 64, with a work order
+])
+def test_calls_that_stay_with_the_small_grids_kernel(usv, B, Hh, nb, d, kmax):
+    w = synth.Workload("stay", B, Hh, nb * 64 - 31, d, "bf16", 2.0, kmax, seed=nb + kmax)
+    Q, K, V = synth.gen_qkv(w)
+    q, k, v = gu.up(Q), gu.up(K), gu.up(V)
+    rng = np.random.default_rng(nb)
+    cnt = rng.integers(kmax // 4, kmax + 1, size=(B, Hh, nb)).astype(np.int32)
+    idx = np.sort(np.argsort(rng.random((B, Hh, nb, nb), dtype=np.float32), axis=-1)[..., :kmax], axis=-1).astype(np.int32)
+    i_g, c_g = gu.up(idx), gu.up(cnt)
+    run = lambda wo: gu.down(usv.block_sparse_attn(q, k, v, i_g, c_g, seq_valid=w.seq_valid, out_dtype=torch.float32, work_order=wo))
+    wo = usv.attn_work_order(c_g, kmax, idx=i_g)
+    ordered, mixed = run(wo), run(gu.up(np.stack([[rng.permutation(nb) for _ in range(Hh)] for _ in range(B)]).astype(np.int32)))
+    assert np.array_equal(ordered, mixed)
+    plain = run(None)
+    for f in np.linspace(0, B * Hh * nb - 1, 9).astype(int):
+        b, h, i = f // (Hh * nb), f // nb % Hh, f % nb
+        ref, _ = gu.oracle_attn_blocks(Q[b, h], K[b, h], V[b, h], idx[b, h], cnt[b, h], w.seq_valid, [i])[i]
+        for o in (ordered, plain):
+            gu.assert_attn_close(o[b, h, i * 64:(i + 1) * 64], ref, "bf16", f"head {b},{h} block {i} ({cnt[b, h, i]} listed)")
+
+
+@pytest.mark.parametrize("d,Hh", [(128, 8), (128, 98), (64, 8), (64, 340)])  # 128 and 1568, 128 and 5440 query blocks
 def test_hugely_negative_logits_are_still_a_softmax(usv, d, Hh):
     """Logits of -2^113 sqrt(d) (bf16 inputs reach them), all alike in a row: every listed key has the same weight, so a row is
     the mean of its keys' V, whatever the size of the logits; both kernels, the reference raised from nothing on the first tile.

@@ -301,7 +301,7 @@ def test_long_lists_cross_the_index_reload_boundary(usv, nb, k):
 
 
 @pytest.mark.parametrize("nb,kmax,d,Hh", [(64, 24, 128, 2), (64, 24, 64, 2), (24, 24, 128, 2), (40, 40, 64, 2), (24, 24, 128, 22),
-                                          (30, 15, 128, 18), (24, 24, 128, 40), (24, 24, 64, 200)],
+                                          (30, 15, 128, 18), (24, 24, 128, 40), (24, 24, 64, 230)],
                          ids=["few_d128", "few_d64", "few_dense_d128", "few_dense_d64", "three_per_cu", "three_per_cu_half",
                               "wide_d128", "wide_d64"])
 def test_every_list_length_in_every_launch_shape(usv, nb, kmax, d, Hh):
