@@ -35,10 +35,15 @@ _BINDING_NAMES = (
 )
 
 
-def __getattr__(name):
-    if name in _BINDING_NAMES:
-        from . import binding
+_binding = None
 
-        value = globals()[name] = getattr(binding, name)  # looked up once
-        return value
+
+def __getattr__(name):
+    global _binding
+    if name in _BINDING_NAMES:
+        if _binding is None:  # (kept: an import statement on every call costs more than the rest of the lookup)
+            from . import binding
+
+            _binding = binding
+        return getattr(_binding, name)
     raise AttributeError(name)

@@ -41,6 +41,17 @@ def test_header_is_plain_c(tmp_path):
     assert res.returncode == 0, res.stderr
 
 
+def test_package_names_follow_the_binding_module(monkeypatch):
+    """paper_2512_05754_amd.f is binding.f at the time of the call, also after an earlier use (a replaced function is seen)."""
+    import paper_2512_05754_amd as usv
+
+    assert usv.block_scores is binding.block_scores
+    monkeypatch.setattr(binding, "block_scores", lambda: "replaced")
+    assert usv.block_scores() == "replaced"
+    monkeypatch.undo()
+    assert usv.block_scores is binding.block_scores
+
+
 def shape(**kw):
     base = dict(batch=1, heads=2, seq_len=1024, seq_valid=1024, head_dim=64, block=64, dtype=binding.USV_F32)
     base.update(kw)
