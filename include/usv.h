@@ -162,9 +162,20 @@ usv_status usv_select_topk_ex(const float* scores, const usv_shape* shape, int32
  *           scaled logits over the row's allowed keys; -inf where out is 0.
  * bf16 inputs: QK^T and PV run on bf16 MFMA with fp32 accumulation and an fp32
  * online softmax; the probabilities are rounded to bf16 before PV and the row
- * sums are taken over the rounded values.
- * fp32 inputs: both products on the fp32 matrix cores (fp32 operands and
- * accumulation), fp32 softmax: within 1e-5 relative of an fp64 evaluation.
+ * sums are taken over the rounded values.  The same call gives the same bits
+ * every time.  What a row's weights are rounded against (a reference that the
+ * first keys of its list set) depends on where in the list the launch begins:
+ * a large bf16 launch (from 769 query blocks in B * Hh * nb on) may begin
+ * elsewhere than at the first entry, at a place that follows from the row's
+ * slot in the launch.  There the same list in another batch, head or work-order
+ * slot, or under another kmax, may give a result that differs by that rounding:
+ * each weight by at most 2^-7 of itself between the two, which is 2e-4 to 1e-3
+ * of the result's 2-norm on video-like inputs, as much as the result's own
+ * error.  Smaller launches and fp32 inputs begin at the first entry.
+ * fp32 inputs: both products to fp32 accuracy (operands in three bf16 parts,
+ * the six leading products summed in fp32; on the fp32 matrix cores where a
+ * part would run out of range), fp32 softmax: within 1e-5 relative of an fp64
+ * evaluation.
  */
 usv_status usv_block_sparse_attn(const void* q, const void* k, const void* v,
                                  const usv_shape* shape, const int32_t* idx, const int32_t* cnt,
@@ -194,12 +205,13 @@ usv_status usv_block_sparse_attn(const void* q, const void* k, const void* v,
  *   usv_block_sparse_attn_ordered   usv_block_sparse_attn with that table;
  *                         work_order == NULL is usv_block_sparse_attn.  As long
  *                         as every head's slice is a permutation of 0..nb-1, the
- *                         output depends on the table at most in the rounding of
- *                         its fp32 sums: a large launch begins the list of a
- *                         slot where the other slots' sweeps are expected to
- *                         be, and goes around.  (Entries are clamped into range;
- *                         a block named twice is computed twice, a block never
- *                         named is not written.)  fp32 inputs ignore the table.
+ *                         output does not depend on the table, except that a
+ *                         large bf16 launch may begin a list where its slot says
+ *                         (see usv_block_sparse_attn): two tables then give
+ *                         results that differ by the rounding of the weights to
+ *                         bf16.  (Entries are clamped into range; a block named
+ *                         twice is computed twice, a block never named is not
+ *                         written.)  fp32 inputs ignore the table.
  * idx        : NULL or [B, Hh, nb, kmax] int32 (device, read only), ascending lists
  *              as written by stage 2 (other lists only make the order less useful)
  * cnt        : [B, Hh, nb] int32 (device, read only), as written by stage 2

@@ -1,6 +1,7 @@
 """The attention kernel for grids that fill the chip, at the edges of its ranges: the smallest grids it takes, lists around the
 64 entries one register holds, sweeps that start inside the list (later rounds of a launch), the deeper request ring, ragged
-and empty lists, lists in no order, both head dimensions.  Sampled query blocks against the oracle, at the bf16 bound."""
+and empty lists, lists in no order, both head dimensions.  Sampled query blocks against the oracle, at the bf16 bound; what
+calls of this size promise about their bits; the second branch folded into the store; raster order."""
 import numpy as np
 import pytest
 import torch
@@ -58,6 +59,63 @@ def test_wide_grids_against_the_oracle(usv, B, Hh, nb, d, kmax, ragged, ordered)
         got = l_h[b, h, i * 64:(i + 1) * 64]
         assert np.array_equal(np.isneginf(got), ~live), what
         assert not live.any() or np.abs(got[live] - ref_l[live]).max() <= 2e-2, what
+
+
+@pytest.mark.parametrize("B,Hh,nb,d,kmax,raster", [
+    (1, 4, 390, 128, 60, False),   # later lists start inside
+    (1, 8, 700, 128, 50, False),   # the deeper ring, several rounds (a head beyond the L2)
+    (2, 14, 200, 64, 30, False),   # d = 64
+    (1, 4, 600, 128, 60, True),    # raster order
+    (1, 7, 800, 64, 40, True),     # ... d = 64
+])
+def test_what_a_large_launch_promises(usv, B, Hh, nb, d, kmax, raster):
+    """The same call gives the same bits (nothing in the hand-counted waits of the request ring depends on timing), and calls
+    whose lists start elsewhere (other work orders, another slot of the launch, another kmax) differ by the rounding of the
+    weights to bf16: 2^-8 of a weight in either, so 2^-7 of the row sum between the two and 2^-7 of a mean of |v - out|, which is at
+    most twice the largest |v|; and 2e-3 of the 2-norm, twice what such inputs show."""
+    Nv = nb * 64 - (0 if raster else 37)
+    gen = torch.Generator(device=gu.DEV).manual_seed(nb + kmax)
+    def tensor():
+        x = torch.randn((B, Hh, nb, 64, d), device=gu.DEV, generator=gen) + 2 * torch.randn((B, Hh, nb, 1, d), device=gu.DEV, generator=gen)
+        return x.view(B, Hh, nb * 64, d).to(torch.bfloat16)
+    q, k, v = tensor(), tensor(), tensor()
+    idx = torch.rand((B, Hh, nb, nb), device=gu.DEV, generator=gen).topk(kmax, dim=-1).indices.sort(-1).values.int()
+    cnt = torch.full((B, Hh, nb), kmax, dtype=torch.int32, device=gu.DEV)
+    order = torch.randperm(nb * 64, device=gu.DEV, generator=gen).int()
+
+    def run(wo=None, i=idx, c=cnt, qkv=(q, k, v)):
+        if raster:
+            return usv.block_sparse_attn_raster(*qkv, order, i, c, out_dtype=torch.float32, return_lse=True, work_order=wo)
+        return usv.block_sparse_attn(*qkv, i, c, seq_valid=Nv, out_dtype=torch.float32, return_lse=True, work_order=wo)
+
+    sorted_order = usv.attn_work_order(cnt, kmax, idx=idx)
+    shuffled = torch.rand((B, Hh, nb), device=gu.DEV, generator=gen).argsort(-1).int()
+    plain, plain_lse = run()
+    for wo in (None, sorted_order, shuffled):
+        first, first_lse = run(wo)
+        for _ in range(4):
+            again, again_lse = run(wo)
+            assert torch.equal(again.view(torch.int32), first.view(torch.int32))
+            assert torch.equal(again_lse.view(torch.int32), first_lse.view(torch.int32))
+
+    def close(out, lse, what):
+        diff = (out - plain).double()
+        assert diff.abs().max() <= 2.0 ** -6 * v.abs().max(), what
+        assert diff.norm() <= 2e-3 * plain.double().norm(), (what, float(diff.norm() / plain.double().norm()))
+        live = torch.isfinite(plain_lse)
+        assert torch.equal(live, torch.isfinite(lse)), what
+        assert (lse - plain_lse)[live].abs().max() <= 2.0 ** -7 * 1.01, what
+
+    close(*run(sorted_order), "sorted work order")
+    close(*run(shuffled), "random work order")
+    # the same heads in another slot of the launch
+    rolled = [t.roll(1, dims=1) for t in (q, k, v)]
+    out, lse = run(None, idx.roll(1, dims=1), cnt, rolled)
+    close(out.roll(-1, dims=1), lse.roll(-1, dims=1), "another head slot")
+    # the same lists in rows of another length (past the sixth of the blocks up to which lists start inside)
+    long = torch.full((B, Hh, nb, nb // 5), -1, dtype=torch.int32, device=gu.DEV)
+    long[..., :kmax] = idx
+    close(*run(None, long, cnt), "another kmax")
 
 
 # Grids that fill the chip and stay with the kernel for small ones all the same: its sweeps start at the first entry, so the
