@@ -35,15 +35,10 @@ _BINDING_NAMES = (
 )
 
 
-_binding = None
-
-
 def __getattr__(name):
-    global _binding
     if name in _BINDING_NAMES:
-        if _binding is None:  # (kept: an import statement on every call costs more than the rest of the lookup)
-            from . import binding
+        from . import binding
 
-            _binding = binding
-        return getattr(_binding, name)
+        value = globals()[name] = getattr(binding, name)  # kept: binding passes on what replaces it later
+        return value
     raise AttributeError(name)
