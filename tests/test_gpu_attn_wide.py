@@ -61,6 +61,82 @@ def test_wide_grids_against_the_oracle(usv, B, Hh, nb, d, kmax, ragged, ordered)
         assert not live.any() or np.abs(got[live] - ref_l[live]).max() <= 2e-2, what
 
 
+@pytest.mark.parametrize("B,Hh,nb,d,mode", [
+    (1, 13, 120, 128, "cube"),      # 1560 query blocks
+    (2, 23, 120, 64, "cube"),       # 5520
+    (1, 18, 120, 128, "raster"),    # 2160
+    (2, 23, 120, 64, "raster"),
+    (1, 18, 120, 128, "cubes"),     # one cube per block, cut cubes padded
+    (1, 45, 121, 64, "cubes"),
+])
+@pytest.mark.parametrize("gates", ["both", "fine", "coarse", "none"])
+def test_second_branch_of_a_large_launch(usv, B, Hh, nb, d, mode, gates):
+    """out = gate_fine * attention + gate_coarse * coarse[cube] in the store of the kernel for large grids: both gates, one, none (an
+    absent gate is 1); fp32 and bf16 output; a partial last block, cut cubes; projection layout, with a work order and without."""
+    kmax, raster = 7, mode != "cube"
+    rng = np.random.default_rng(nb + d + len(mode))
+    valid = rng.integers(1, 65, size=nb).astype(np.int32) if mode == "cubes" else np.full(nb, 64, np.int32)
+    if mode != "cubes":
+        valid[-1] = 64 - 27
+    Nv = int(valid.sum())
+    rows = Nv if raster else nb * 64
+    gen = torch.Generator(device=gu.DEV).manual_seed(nb * d)
+
+    def tensor(scale=1.0):
+        x = torch.randn((B, rows, Hh, d) if raster else (B, Hh, rows, d), device=gu.DEV, generator=gen) * scale
+        x = x.to(torch.bfloat16)
+        return x.transpose(1, 2) if raster else x  # raster: as a projection leaves it
+
+    q, k, v = tensor(1.5), tensor(1.5), tensor()
+    gf = tensor() if gates in ("both", "fine") else None
+    gc = tensor() if gates in ("both", "coarse") else None
+    coarse = torch.randn((B, Hh, nb, d), device=gu.DEV, generator=gen)
+    cnt = rng.integers(0, kmax + 1, size=(B, Hh, nb)).astype(np.int32)
+    idx = np.sort(np.argsort(rng.random((B, Hh, nb, nb)), axis=-1)[..., :kmax], axis=-1).astype(np.int32)
+    i_g, c_g = gu.up(idx), gu.up(cnt)
+    # position -> raster row (padding positions: 0, a valid token, as the order kernels write it)
+    order = np.zeros((nb, 64), np.int32)
+    order[np.arange(64)[None, :] < valid[:, None]] = rng.permutation(Nv) if raster else np.arange(Nv)
+    kw = dict(coarse=coarse, gate_fine=gf, gate_coarse=gc, return_lse=True)
+    outs = {}
+    if raster:
+        o_g = gu.up(order.reshape(-1))
+        for wo in (None, usv.attn_work_order(c_g, kmax, idx=i_g)):
+            for odt in (torch.float32, torch.bfloat16):
+                outs[wo is not None, odt] = usv.block_sparse_attn_raster(
+                    q, k, v, o_g, i_g, c_g, out_dtype=odt, work_order=wo, block_valid=gu.up(valid) if mode == "cubes" else None, **kw)
+    else:
+        for odt in (torch.float32, torch.bfloat16):
+            outs[False, odt] = usv.block_sparse_attn(q, k, v, i_g, c_g, seq_valid=Nv, out_dtype=odt, **kw)
+    for f in [int(x) for x in np.linspace(0, B * Hh * nb - 1, 13)]:
+        b, h, i = f // (Hh * nb), f // nb % Hh, f % nb
+        pick = lambda t, p: gu.down(t[b, h][torch.from_numpy(p).to(gu.DEV).long()]).astype(np.float64)
+        mine = order[i, :valid[i]]
+        keys = np.concatenate([order[j, :valid[j]] for j in idx[b, h, i, :cnt[b, h, i]]]) if cnt[b, h, i] else np.zeros(0, int)
+        attn, lse = np.zeros((valid[i], d)), np.full(valid[i], -np.inf)
+        if len(keys):
+            S = pick(q, mine) @ pick(k, keys).T / np.sqrt(d)
+            m = S.max(axis=1, keepdims=True)
+            P = np.exp(S - m)
+            attn, lse = P @ pick(v, keys) / P.sum(axis=1, keepdims=True), m[:, 0] + np.log(P.sum(axis=1))
+        g1 = pick(gf, mine) if gf is not None else np.ones((valid[i], d))
+        g2 = pick(gc, mine) if gc is not None else np.ones((valid[i], d))
+        want = g1 * attn + g2 * gu.down(coarse[b, h, i]).astype(np.float64)
+        for (ordered, odt), (out, out_lse) in outs.items():
+            if odt != torch.float32:
+                continue
+            what = f"{gates} head {b},{h} block {i} ({cnt[b, h, i]} listed) ordered {ordered}"
+            err = np.abs(pick(out, mine) - want)  # (the gate scales the attention's error)
+            assert (err <= gu.BF16_MAX_ABS * np.maximum(1.0, np.abs(g1))).all(), (what, err.max())
+            got = pick(out_lse[..., None], mine)[:, 0]
+            assert np.array_equal(np.isneginf(got), np.isneginf(lse)), what
+            assert not len(keys) or np.abs(got - lse).max() <= 2e-2, what
+    for ordered in {o for o, _ in outs}:
+        gu.assert_bf16_store_is_rne(outs[ordered, torch.bfloat16][0], outs[ordered, torch.float32][0], f"{mode} {gates}")
+    if not raster:  # padded rows are written as 0
+        assert not gu.down(outs[False, torch.float32][0])[:, :, Nv:].any()
+
+
 @pytest.mark.parametrize("B,Hh,nb,d,kmax,raster", [
     (1, 4, 390, 128, 60, False),   # later lists start inside
     (1, 8, 700, 128, 50, False),   # the deeper ring, several rounds (a head beyond the L2)

@@ -487,7 +487,8 @@ def expected_work_order(idx, cnt, kmax):
 
 def test_work_order_is_the_documented_sort_and_does_not_change_the_result(usv):
     """usv_attn_work_order: per head the query blocks sorted by (list length descending, where the list lies, index);
-    usv_block_sparse_attn_ordered: the same bits as usv_block_sparse_attn whatever permutation it is given."""
+    usv_block_sparse_attn_ordered: on a grid of this size (240 query blocks) the same bits as usv_block_sparse_attn whatever
+    permutation it is given (what large launches promise is tested in test_gpu_attn_wide.py)."""
     w = Workload("ragged_small", 2, 3, 40 * 64 - 17, 128, "bf16", 2.0, 0, budget_lo=0, budget_hi=24, seed=77)
     Q, K, V = synth.gen_qkv(w)
     q, k, v = gu.up(Q), gu.up(K), gu.up(V)
