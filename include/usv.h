@@ -456,7 +456,8 @@ usv_status usv_block_sparse_attn_raster_fused(const void* q, const void* k, cons
  */
 
 /* Bytes of device scratch usv_merge_similarity needs (descriptors and their
- * squared norms: B * T*H*W * (d + 1) * 4).  Returns 0 for invalid arguments. */
+ * squared norms: B * T*H*W * (d + 1) * 4).  Returns 0 for invalid arguments.
+ * (For 2x2x2 merge blocks it is asked for all the same, but not used.) */
 size_t usv_merge_workspace_bytes(const usv_shape* shape, const usv_grid* grid);
 
 /* k   : [B, Hh, T*H*W, d] of shape->dtype, raster order (device, read only)

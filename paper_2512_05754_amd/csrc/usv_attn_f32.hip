@@ -314,7 +314,8 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
   __shared__ int redo[4 * KH];
   __shared__ unsigned v_top[CH];  // largest |V| that was staged, per 8 channels (bits of the float)
-  __shared__ int subnormal_v;
+  __shared__ unsigned zero_at;    // groups of eight channels with a result of 0 beside other values
+  __shared__ int subnormal_v;     // ... and V is not 0 there
 
   const int work = xcd_contiguous_id(blockIdx.x, per_xcd);  // neighbouring query blocks share K and V in an XCD's L2
   if (work >= total) return;  // whole workgroup leaves before any barrier
@@ -380,7 +381,7 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
   const unsigned char* const ks = smem;
   const unsigned char* const vs = smem + 3 * kPlane;
   if (tid < CH) v_top[tid] = 0;  // (the barriers of the loop stand between this and the first maximum)
-  if (tid == 0) subnormal_v = 0;
+  if (tid == 0) zero_at = 0, subnormal_v = 0;
 
   constexpr int kSteps = 2 / KH;  // steps per listed block
   for (int st = 0; st < kSteps * n_list; ++st) {
@@ -539,7 +540,7 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
   const bool live = mine && lt > 0.f;  // lt == 0: every listed key is padding
   const float inv = live ? 1.f / lt : 0.f;
   bool bad = (mine && (!(lt < INFINITY) || q_top >= qk_limit)) || k_top >= qk_limit;
-  bool small = false, zero = false;
+  bool small = false;
   float finite = 0.f;  // NaN as soon as a result is not finite
   float* stage = rows + (qw * 16 + c16) * LD;
   auto least = [&](float top) { return fmaxf(kTiny, top * kTiny); };
@@ -558,27 +559,37 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
   if (__any(live && small)) {
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
-      const float top = __uint_as_float(v_top[2 * dt + (G >> 1)]);
+      const int ch = 2 * dt + (G >> 1);
+      const float top = __uint_as_float(v_top[ch]);
+      bool zero = false;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float a = fabsf(o[dt][r] * inv);
         bad |= live && a < least(top) && (a > 0.f || (top > 0.f && top < kTiny));
         zero |= live && a == 0.f && top > 0.f;
       }
+      if (zero) atomicOr(&zero_at, 1u << ch);
     }
   }
-  const int any_bad = __any(bad), any_zero = __any(zero);
-  if (lane == 0) redo[wave] = any_bad | any_zero << 1;
+  const int any_bad = __any(bad);
+  if (lane == 0) redo[wave] = any_bad;
   __syncthreads();
   int again = 0;
 #pragma unroll
   for (int w = 0; w < 4 * KH; ++w) again |= redo[w];
-  if (again == 2) {  // a result of 0 beside other values: is V 0 there, or too small to be split?
+  if (!again && zero_at) {  // results of 0 beside other values: is V 0 there, or too small to be split?
     bool sub = false;
-    for (int n = 0; n < n_list; ++n) {
-      const int jn = block_at(n), rows_n = min(kBlock, Nv - jn * kBlock);
-      const unsigned* vn = reinterpret_cast<const unsigned*>(v + head_off + (long long)jn * kBlock * D);
-      for (int e = tid; e < rows_n * D; e += kThreads) sub |= (vn[e] & 0x7fffffffu) - 1u < 0x007fffffu;
+    auto is_sub = [](unsigned x) { return (x & 0x7fffffffu) - 1u < 0x007fffffu; };
+    for (unsigned left = zero_at; left; left &= left - 1) {
+      const int ch = __ffs(left) - 1;
+#pragma unroll 4
+      for (int e = tid; e < n_list * kBlock; e += kThreads) {  // a row of these eight channels each
+        const int jn = block_at(e / kBlock), row = jn * kBlock + e % kBlock;
+        const uint4* at = reinterpret_cast<const uint4*>(v + head_off + (long long)min(row, Nv - 1) * D + ch * 8);
+        const uint4 x = at[0], y = at[1];
+        const bool any = is_sub(x.x) | is_sub(x.y) | is_sub(x.z) | is_sub(x.w) | is_sub(y.x) | is_sub(y.y) | is_sub(y.z) | is_sub(y.w);
+        sub |= any && row < Nv;
+      }
     }
     if (__any(sub) && lane == 0) subnormal_v = 1;
     __syncthreads();

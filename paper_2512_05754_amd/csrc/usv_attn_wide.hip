@@ -190,7 +190,8 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
   // can be expected to be: the k-th of the sweep_wgs that make up round m = rank / sweep_wgs starts about k / sweep_wgs of
   // the rounds' spread behind the first, the spread grows like sqrt(m) (independent delays) up to one whole sweep, and the
   // list is walked from the first block at or past that point, around the end, back to it.  A pure function of the launch:
-  // same bits every time.  Measured (start at 0 -> here): 480p / 51 of 512 blocks 0.80 -> 0.712 ms, 25 blocks 0.487 ->
+  // same bits every time; but the first tile sets the reference that a row's weights are rounded to bf16 against, so in another
+  // slot of a launch (or with another kmax) the same list may give a result that differs by that rounding.  Measured (start at 0 -> here): 480p / 51 of 512 blocks 0.80 -> 0.712 ms, 25 blocks 0.487 ->
   // 0.401, 720p / 59 of 1182 10.8 -> 7.65 ms; spread 0.3 / 0.4 / 0.5 / 0.6 / 0.8 sqrt(m): 0.722 / 0.713 / 0.712 / 0.717 /
   // 0.727 ms.
   int first = 0;  // entry the sweep starts with
