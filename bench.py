@@ -549,7 +549,7 @@ def main():
         "stage_hbm_gbs": {"block_scores": bytes_scores / (avg[0] * 1e-3) / 1e9,
                           "select_topk": bytes_topk / (avg[1] * 1e-3) / 1e9},
         "roofline": {
-            "kernel": "usv_block_sparse_attn (attn_bf16)" if w.dtype == "bf16" else "usv_block_sparse_attn (attn_f32)",
+            "kernel": "usv_block_sparse_attn (attn_wide; few query blocks: attn_bf16)" if w.dtype == "bf16" else "usv_block_sparse_attn (attn_f32)",
             "bound": "mfma",  # bf16 matrix cores for bf16 inputs, fp32 matrix cores (v_mfma_f32_32x32x2_f32) for fp32 inputs
             "achieved": flop / (avg[2] * 1e-3) / 1e12,
             "peak": PEAK_BF16_TFLOPS if w.dtype == "bf16" else 157.3,
@@ -570,7 +570,7 @@ def main():
         result["config"]["step"] = ("usv_block_scores_raster + usv_select_topk + usv_block_sparse_attn_raster" if not two_branch else
                                     "usv_block_scores_raster + usv_select_topk_ex + usv_coarse_attn_raster + "
                                     "usv_block_sparse_attn_raster_fused + usv_attn_entropy")
-        result["roofline"]["kernel"] = "usv_block_sparse_attn_raster (attn_bf16, raster addressing)"
+        result["roofline"]["kernel"] = "usv_block_sparse_attn_raster (attn_wide, raster addressing)"
         result["roofline"].update(measured_traffic(("cubes:" if cubes else "raster:") + w.name))
     if cubes:
         result["config"]["path"] = "raster_cubes"

@@ -88,7 +88,7 @@ struct AttnBf16Args {
   RasterArgs ras;
   const int32_t* work_order;
 };
-hipError_t launch_attn_bf16(const AttnBf16Args& a, bool out_f32, hipStream_t st);  // picks the kernel by the grid's size
+hipError_t launch_attn_bf16(const AttnBf16Args& a, bool out_f32, hipStream_t st);  // picks the kernel (the rule stands there)
 hipError_t launch_attn_wide(const AttnBf16Args& a, bool out_f32, hipStream_t st);  // the one for grids that fill the chip
 hipError_t launch_attn_work_order(const int32_t* idx, const int32_t* cnt, const Dims& s, int kmax, int32_t* work_order,
                                   hipStream_t st);  // idx == nullptr: by list length only
