@@ -550,11 +550,11 @@ def main():
                           "select_topk": bytes_topk / (avg[1] * 1e-3) / 1e9},
         "roofline": {
             "kernel": "usv_block_sparse_attn (attn_wide; few query blocks: attn_bf16)" if w.dtype == "bf16" else "usv_block_sparse_attn (attn_f32)",
-            "bound": "mfma",  # bf16 matrix cores for bf16 inputs, fp32 matrix cores (v_mfma_f32_32x32x2_f32) for fp32 inputs
+            "bound": "mfma",  # bf16 matrix cores; a product of fp32 inputs is six of bf16 parts
             "achieved": flop / (avg[2] * 1e-3) / 1e12,
-            "peak": PEAK_BF16_TFLOPS if w.dtype == "bf16" else 157.3,
+            "peak": PEAK_BF16_TFLOPS if w.dtype == "bf16" else PEAK_BF16_TFLOPS / 6,
             "unit": "TFLOP/s",
-            "frac": flop / (avg[2] * 1e-3) / 1e12 / (PEAK_BF16_TFLOPS if w.dtype == "bf16" else 157.3),
+            "frac": flop / (avg[2] * 1e-3) / 1e12 / (PEAK_BF16_TFLOPS if w.dtype == "bf16" else PEAK_BF16_TFLOPS / 6),
             **measured_traffic(w.name),
             "avg_launch_ms": float(avg[2]),
         },

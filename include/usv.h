@@ -193,11 +193,11 @@ usv_status usv_block_sparse_attn(const void* q, const void* k, const void* v,
  * launch is made of the shortest lists.  "Where the list lies" = its entries at
  * 1/4, 1/2 and 3/4 of its length, each reduced to one of 64 equal buckets of
  * the block range, compared lexicographically.  Measured on MI355X: per-row
- * budgets uniform in 8..64 at the merged 480p shape 12 % faster than index
+ * budgets uniform in 8..64 at the merged 480p shape 25 % faster than index
  * order; uniform budgets at the 720p shape (59 of 1182 blocks, where a head's
- * K and V are ten times the L2) 8 % faster; uniform budgets at the 480p shape
- * 1 % (there the sort costs what it gains).  It pays when the lists are ragged
- * or when a head's K and V are many times the L2.
+ * K and V are ten times the L2) 7 % faster; uniform budgets at the 480p shape
+ * 0 to 3 % (there the sort costs what it gains).  It pays when the lists are
+ * ragged or when a head's K and V are many times the L2.
  *
  *   usv_attn_work_order   work_order[b,h,s] = the query block that slot s of head
  *                         (b,h) takes; deterministic.  idx == NULL: by list

@@ -643,7 +643,8 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
   }
 }
 
-// Which kernel takes a launch.  All times this kernel / wide.
+// Which kernel takes a launch.  All times this kernel / wide.  (Raster order plays no part: the raster entry points give the bits that
+// gathered tensors give.  The wide kernel's address arithmetic is the longer one there: 2048 query blocks, 26 listed 152 / 162 us.)
 inline bool wide_is_faster(const AttnBf16Args& a) {
   const Dims& s = a.s;
   const long long total = s.bh() * s.nb;
@@ -655,7 +656,6 @@ inline bool wide_is_faster(const AttnBf16Args& a) {
   //   d = 64 (half the matrix work per fetched byte and per exponential), 25 listed: 1024 blocks 41.4 / 42.0 us, 1536: 57.7 /
   //   58.0, 2048: 74 / 85, 2560: 92 / 100, 5120: 213 / 213 (128: 747 / 774), 6144 (51 listed): 408 / 385; heads of more than 640 blocks
   //   gain from the start of the sweep: 1182 blocks x 4, 71 listed 537 / 447
-  //   raster order (the wide kernel's address arithmetic is the longer one): 2048 query blocks, 26 listed 152 / 162
   // Heads beyond the L2 of an XCD (below: from 17.5 MiB of K and V on): twice as many sweeps run together in the wide kernel, and
   // from some list length on they drift apart further than the start of a sweep can foresee (its rule is in usv_attn_wide.hip).
   // Times in ms; k = kmax.
@@ -665,7 +665,7 @@ inline bool wide_is_faster(const AttnBf16Args& a) {
     const bool drifts = nb > 1280 && 4 * k < nb && (a.work_order ? 10 : 6) * k > nb;
     return total > (nb > 640 ? 4608 : 5376) && !drifts;
   }
-  if (total <= 768 || (total > 1024 && total <= (a.ras.order ? 2048 : 1536))) return false;
+  if (total <= 768 || (total > 1024 && total <= 1536)) return false;
   // In its single full round every list runs at once, half as fast: a work order puts the longest lists of a short head on the
   // same CUs (8 heads x 128 blocks, lists of 16..128 blocks 165 / 183 us, 24 x 40, 5..40: 65 / 73; 2 x 512, 64..512: 916 / 810).
   if (total <= 1024 && a.work_order && nb <= 128) return false;

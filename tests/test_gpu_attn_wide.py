@@ -194,6 +194,21 @@ def test_what_a_large_launch_promises(usv, B, Hh, nb, d, kmax, raster):
     close(*run(None, long, cnt), "another kmax")
 
 
+@pytest.mark.parametrize("Hh,nb,d,kmax", [(13, 125, 128, 9), (4, 650, 128, 100), (10, 700, 128, 40), (45, 125, 64, 9)])
+def test_raster_order_gives_the_bits_of_gathered_tensors(usv, Hh, nb, d, kmax):
+    """On both sides of the rule between the kernels and with the deeper ring (which raster order has not got)."""
+    gen = torch.Generator(device=gu.DEV).manual_seed(nb)
+    q, k, v = (torch.randn((1, Hh, nb * 64, d), device=gu.DEV, generator=gen).to(torch.bfloat16) for _ in range(3))
+    idx = torch.rand((1, Hh, nb, nb), device=gu.DEV, generator=gen).topk(kmax, dim=-1).indices.sort(-1).values.int()
+    cnt = torch.full((1, Hh, nb), kmax, dtype=torch.int32, device=gu.DEV)
+    order = torch.randperm(nb * 64, device=gu.DEV, generator=gen)
+    out, lse = usv.block_sparse_attn_raster(q, k, v, order.int(), idx, cnt, out_dtype=torch.float32, return_lse=True)
+    want, want_lse = usv.block_sparse_attn(*(t[:, :, order].contiguous() for t in (q, k, v)), idx, cnt, out_dtype=torch.float32,
+                                           return_lse=True)
+    assert torch.equal(out[:, :, order].view(torch.int32), want.view(torch.int32))
+    assert torch.equal(lse[:, :, order].view(torch.int32), want_lse.view(torch.int32))
+
+
 # Grids that fill the chip and stay with the kernel for small ones all the same: its sweeps start at the first entry, so the
 # result does not depend on the order the query blocks are walked in, bit for bit.
 @pytest.mark.parametrize("B,Hh,nb,d,kmax", [
