@@ -676,13 +676,19 @@ def block_sparse_attn_raster(q, k, v, order, idx, cnt, scale=0.0, out=None, out_
 
 class _Binding(types.ModuleType):
     """This module.  The package keeps the names it has looked up (a module __getattr__ is 0.4 us of a 20 us pass); replacing
-    one here replaces it there."""
+    one here, or all of them by reloading the module, replaces it there."""
 
     def __setattr__(self, name, value):
         super().__setattr__(name, value)
-        package = vars(sys.modules[__package__])
-        if name in package and name in package["_BINDING_NAMES"]:
-            package[name] = value
+        _pass_on(name, value)
+
+
+def _pass_on(name, value):
+    package = vars(sys.modules[__package__])
+    if name in package and name in package["_BINDING_NAMES"]:
+        package[name] = value
 
 
 sys.modules[__name__].__class__ = _Binding
+for _name, _value in list(globals().items()):
+    _pass_on(_name, _value)

@@ -42,7 +42,11 @@ def test_header_is_plain_c(tmp_path):
 
 
 def test_package_names_follow_the_binding_module(monkeypatch):
-    """paper_2512_05754_amd.f is binding.f at the time of the call, also after an earlier use (a replaced function is seen)."""
+    """paper_2512_05754_amd.f is binding.f at the time of the call, also after an earlier use (a replaced function is seen, and a
+    reloaded module, which runs in a process of its own here)."""
+    import subprocess
+    import sys
+
     import paper_2512_05754_amd as usv
 
     assert usv.block_scores is binding.block_scores
@@ -50,6 +54,9 @@ def test_package_names_follow_the_binding_module(monkeypatch):
     assert usv.block_scores() == "replaced"
     monkeypatch.undo()
     assert usv.block_scores is binding.block_scores
+    code = ("import importlib, paper_2512_05754_amd as usv; f = usv.block_scores; from paper_2512_05754_amd import binding; "
+            "importlib.reload(binding); assert usv.block_scores is binding.block_scores is not f")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
 
 
 def shape(**kw):
