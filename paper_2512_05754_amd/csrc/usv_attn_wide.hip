@@ -88,12 +88,13 @@ __device__ __forceinline__ void wait_lds() {
 }
 
 // WPS: waves per SIMD the register budget is sized for.  DEEP: one more ring slot (requests half a tile further ahead), for
-// heads whose K and V are far beyond the L2.
+// heads whose K and V are far beyond the L2.  SWEEP: the lists start where the other workgroups are expected ("where the list
+// starts" below), and the waves of a SIMD take turns.
 // RASTER: Q, K, V and the output are in raster token order (any strides); `ras.order[p]` gives the raster index of
 // cube-major position p.  Every wave fetches the 32 order entries of a half tile one step ahead of its K/V requests (one
 // more 4-byte-per-lane DMA per step, into a small LDS ring that only this wave reads) and turns them into the per-lane
 // global offsets of its DMA instructions; the epilogue stores each row at its raster position.
-template <int D, bool OUT_F32, int WPS, bool RASTER, bool DEEP>
+template <int D, bool OUT_F32, int WPS, bool RASTER, bool DEEP, bool SWEEP>
 __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                           const uint16_t* __restrict__ v, const int32_t* __restrict__ idx,
                                                           const int32_t* __restrict__ cnt, void* __restrict__ out,
@@ -185,24 +186,29 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
   // ---- where the list starts -------------------------------------------------------------------
   // The workgroups of an XCD that run together share fetched tiles through its L2 as long as their sweeps over the
   // head's keys stay together.  Starting every list at its first entry keeps them together in the first round only: later
-  // workgroups start whenever a slot frees, and within a few rounds the starts are spread over a whole sweep (measured at
-  // 12 heads, 512 blocks, 51 listed: half of the requests miss the L2).  So a workgroup starts its sweep where the others
-  // can be expected to be: the k-th of the sweep_wgs that make up round m = rank / sweep_wgs starts about k / sweep_wgs of
-  // the rounds' spread behind the first, the spread grows like sqrt(m) (independent delays) up to one whole sweep, and the
-  // list is walked from the first block at or past that point, around the end, back to it.  A pure function of the launch:
-  // same bits every time; but the first tile sets the reference that a row's weights are rounded to bf16 against, so in another
-  // slot of a launch (or with another kmax) the same list may give a result that differs by that rounding.  Measured (start at 0 -> here): 480p / 51 of 512 blocks 0.80 -> 0.712 ms, 25 blocks 0.487 ->
-  // 0.401, 720p / 59 of 1182 10.8 -> 7.65 ms; spread 0.3 / 0.4 / 0.5 / 0.6 / 0.8 sqrt(m): 0.722 / 0.713 / 0.712 / 0.717 /
-  // 0.727 ms.
+  // workgroups start whenever a slot frees, and those times spread from round to round (measured at 12 heads, 512 blocks, 51
+  // listed, as a share of one sweep: 0.18 in round 1, 0.28, 0.37, 0.47, 0.54 in round 5; 40 heads of 1182 blocks 0.19 to 0.8
+  // in round 6, where it stays).  So a workgroup starts its sweep where the others can be expected to be at its time.  The
+  // k-th of the sweep_wgs of round m = rank / sweep_wgs starts before or after the round's middle by its share of that
+  // spread, and the middles of all rounds meet the same place of the sweep: the list is walked from the first block at or past
+  // nb * width(m) * (k / sweep_wgs - 1/2), modulo nb, around the end, back to it.  A pure function of the launch: same bits
+  // every time; but the first tile sets the reference that a row's weights are rounded to bf16 against, so in another
+  // slot of a launch (or with another kmax) the same list may give a result that differs by that rounding.
+  // Measured, with "taking turns" below (start at 0 -> spread 0.5 sqrt(m) behind the first of a round, nobody taking turns -> here): 512 blocks x
+  // 12, 51 listed 800 -> 699 -> 661 us, 25 listed 487 -> 400 -> 385, 624 x 12, 62 listed 1078 -> 1006, 800 x 12, 64 listed 1635
+  // -> 1396, 1182 x 40, 59 listed 10.8 -> 7.70 -> 6.99 ms.  A width of 0.25 / 0.3 / 0.35 sqrt(m): 673 / 673 / 678 us, 398 / 385 / 383,
+  // 993 / 1006 / 1024, 1374 / 1396 / 1449, 7.25 / 7.00 / 6.92 ms.
   int first = 0;  // entry the sweep starts with
   int list_v;     // lane t: block of step 64 (n / 64) + t
   {
     const int raw = lane < kmax ? list[lane] : 0;  // (whatever the count says: this load does not wait for the count's)
     int pos = 0;
-    if (sweep_wgs > 0 && (rotate_short || n_list == kmax)) {
+    if (SWEEP && (rotate_short || n_list == kmax)) {
       const int rank = blockIdx.x / kNumXcd, m = rank / sweep_wgs;
-      const float spread = fminf(1.0f, 0.5f * __builtin_amdgcn_sqrtf((float)m));
-      pos = (int)(spread * (float)nb * (float)(rank - m * sweep_wgs) / (float)sweep_wgs);
+      const float width = fminf(1.0f, 0.3f * __builtin_amdgcn_sqrtf((float)m));
+      float at = width * ((float)(rank - m * sweep_wgs) / (float)sweep_wgs - 0.5f);
+      if (at < 0.f) at += 1.0f;
+      pos = (int)(at * (float)nb);
     }
     pos = __builtin_amdgcn_readfirstlane(pos);
     if (pos > 0 && n_list > 0) {  // entries below pos, of an ascending list (of any other list: some entry)
@@ -515,8 +521,22 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
     }
   };
   {
+    // Taking turns: between equals the SIMD issues from its oldest wave first, so of the WPS waves that share one the oldest runs
+    // ahead (measured at d = 128: 85 us a list against 110) and the sweeps of an XCD part already in the first round.  Where
+    // their staying together counts, a wave's priority goes round with its steps, counted from its slot: whoever is ahead is
+    // overtaken.  (Durations in the first round 120 +- 13 -> 113 +- 6 us.  Where the L2 serves the tiles anyway the old order
+    // is the better one, as it keeps prologues and epilogues apart: all 512 blocks listed 5.73 / 5.93 ms.)
+    unsigned turn = SWEEP ? __builtin_amdgcn_s_getreg(4 | (3 << 11)) : 0;  // HW_ID, bits 0..3: the wave's slot of its SIMD
+    if (WPS == 3) turn %= 3;
     int n = 0;
     for (; n + 1 < n_list; ++n) {
+      if constexpr (SWEEP) {
+        if (WPS == 2 ? turn & 1 : turn == 1) __builtin_amdgcn_s_setprio(1);
+        else if (WPS == 3 && turn == 2) __builtin_amdgcn_s_setprio(2);
+        else __builtin_amdgcn_s_setprio(0);
+        ++turn;
+        if (WPS == 3 && turn == 3) turn = 0;
+      }
       step(std::false_type{}, n);
       if constexpr (DEEP) {  // item x + 1 of the next step went where item x of this one was
         const int spare = ring[SLOTS - 1];
@@ -663,26 +683,28 @@ hipError_t run(const AttnBf16Args& a, hipStream_t st) {
   constexpr int WPS = D == 128 ? 2 : 3;                          // waves per SIMD the registers allow
   constexpr int kSweepWgs = 256 / kNumXcd * (WPS * 4 / NW);      // workgroups of an XCD (32 CUs) that run together
   const long long kv_head = 4LL * s.nb * kBlock * D;             // bytes of one head's K and V
-  // Lists that keep more than a sixth of the blocks stay together by themselves (whoever is ahead misses the L2 and is held
-  // up): start at the expected place / at the first entry: 26 of 256 blocks 632 / 656 us, 40 of 256 895 / 917, 80 of 512
-  // 3480 / 3603, 110 of 512 4705 / 4575, 128 of 512 1658 / 1617.
-  const int sweep_wgs = 6LL * a.kmax <= s.nb ? kSweepWgs : 0;
+  // Lists that keep more than a fifth of the blocks stay together by themselves (whoever is ahead misses the L2 and is held
+  // up): start at the expected place and take turns / start at the first entry: 43 of 256 blocks 553 / 568 us, 51 of 256 639 / 650, 64 of 256
+  // 789 / 783, 85 of 512 1037 / 1140, 102 of 512 1245 / 1260, 128 of 512 1558 / 1535, 170 of 512 2051 / 1980.
+  const bool sweep = 5LL * a.kmax <= s.nb;
   // Lists of different lengths sweep at different speeds.  In index order they gain as the others do (40 of 512 at most:
   // 492 / 521 us); a work order brings equal lengths together, which keeps them together as long as a head is not much
   // beyond the L2: 16.8 MB 2480 / 2078 us, but 38.7 MB 7270 / 8050 us and (d = 64) 19.4 MB 2809 / 3235 us.
   const int rotate_short = !a.work_order || kv_head > (18LL << 20);
-  auto launch = [&](auto deep_c) {
-    attn_wide<D, OUT_F32, WPS, RASTER, decltype(deep_c)::value><<<(unsigned)per_xcd * kNumXcd, 64 * NW, 0, st>>>(
+  auto launch = [&](auto deep_c, auto sweep_c) {
+    attn_wide<D, OUT_F32, WPS, RASTER, decltype(deep_c)::value, decltype(sweep_c)::value><<<(unsigned)per_xcd * kNumXcd, 64 * NW, 0, st>>>(
         static_cast<const uint16_t*>(a.q), static_cast<const uint16_t*>(a.k), static_cast<const uint16_t*>(a.v), a.idx,
         a.cnt, a.out, a.lse, s.nb, s.Nv, a.kmax, a.scale * kLog2e, probability_shift(a.kmax), (int)total, per_xcd, a.fuse,
-        a.ras, a.work_order, stream_output(s), sweep_wgs, rotate_short);
+        a.ras, a.work_order, stream_output(s), kSweepWgs, rotate_short);
   };
   // The extra slot costs a rotation of the ring offsets, 1.3 % where the L2 serves the requests (480p 709 -> 718 us), and
   // pays where it does not: 49152 tokens (25 MB) 1870 -> 1815 us, 75600 (38.7 MB) 8.09 -> 7.83 ms, 7.26 -> 7.21 with a work
   // order.  (At d = 64 it changes nothing; raster mode has no LDS left for it.)
   constexpr bool kCanDeep = D == 128 && !RASTER;
-  if (kCanDeep && kv_head > (24LL << 20)) launch(std::integral_constant<bool, kCanDeep>{});
-  else launch(std::false_type{});
+  using Deep = std::integral_constant<bool, kCanDeep>;
+  const bool deep = kCanDeep && kv_head > (24LL << 20);
+  if (sweep) deep ? launch(Deep{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
+  else deep ? launch(Deep{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
   return hipGetLastError();
 }
 
