@@ -656,14 +656,19 @@ inline bool wide_is_faster(const AttnBf16Args& a) {
   //   d = 64 (half the matrix work per fetched byte and per exponential), 25 listed: 1024 blocks 41.4 / 42.0 us, 1536: 57.7 /
   //   58.0, 2048: 74 / 85, 2560: 92 / 100, 5120: 213 / 213 (128: 747 / 774), 6144 (51 listed): 408 / 385; heads of more than 640 blocks
   //   gain from the start of the sweep: 1182 blocks x 4, 71 listed 537 / 447
-  // Heads beyond the L2 of an XCD (below: from 17.5 MiB of K and V on): twice as many sweeps run together in the wide kernel, and
-  // from some list length on they drift apart further than the start of a sweep can foresee (its rule is in usv_attn_wide.hip).
-  // Times in ms; k = kmax.
+  // Longer heads share fetched tiles as long as the sweeps of an XCD stay together: twice as many run together in the wide
+  // kernel, which starts lists of up to a fifth of the blocks where the others are (in index order up to two fifths; the rule is in
+  // usv_attn_wide.hip).  Times in ms; k = kmax; measured over 3 and 12 heads of 560 to 2400 blocks, 3 % to all of them listed.
   const long long k = a.kmax, nb = s.nb;
   if (s.d == 64) {
-    // 1700 blocks x 6 heads: k = 272 4.75 / 3.57, 340 4.09 / 4.62; with a work order 136 2.35 / 1.79, 204 2.45 / 2.64, 340 3.92 / 3.99
-    const bool drifts = nb > 1280 && 4 * k < nb && (a.work_order ? 10 : 6) * k > nb;
-    return total > (nb > 640 ? 4608 : 5376) && !drifts;
+    // Lists that start at their first entry: 560 x 12, k = 224 0.973, 900 x 12, 360 0.981, 1182 x 12, 295 0.969 of the wide kernel's
+    // time.  Others: 640 x 12, 80 1.03, 900 x 12, 45 1.22, 1182 x 12, 94 1.32 (189: 1.03), 1500 x 12, 240 1.31; below three rounds only
+    // long heads with short lists, which share most: 900 x 3, 180 1.00, 1024 x 3, 81 1.10, 1182 x 3, 94 1.15 but 147 0.98, 1500 x 3, 120 1.36.
+    // A work order keeps equal lists together in both kernels: 1182 x 12, 147 1.01, 1500 x 12, 240 0.985, 1900 x 12, 152
+    // 1.46 but 237 0.99, 1182 x 3, 59 1.07 but 94 0.97.
+    if (5 * k > nb) return false;
+    if (total > (nb > 640 ? 4608 : 5376)) return !a.work_order || nb <= 1280 || 8 * k <= nb;
+    return nb >= 1000 && total > 2560 && (a.work_order ? 16 * k <= nb : nb >= 1400 || 10 * k <= nb);
   }
   if (total <= 768 || (total > 1024 && total <= 1536)) return false;
   // In its single full round every list runs at once, half as fast: a work order puts the longest lists of a short head on the
@@ -671,15 +676,15 @@ inline bool wide_is_faster(const AttnBf16Args& a) {
   if (total <= 1024 && a.work_order && nb <= 128) return false;
   if (nb <= 560) return true;
   if (a.work_order) {
-    // 600 blocks x 40 heads, k = 96 5.43 / 4.99; 680 x 40, 109 6.75 / 8.40; 768 x 12, 61 1.38 / 1.48, 123 2.48 / 2.86; 1182 x 3, 59
-    // 0.62 / 0.68 but x 40, 59 8.06 / 7.62; 1182 x 4, 95 1.12 / 1.35; 768 x 12, 154 3.05 / 2.83; 1182 x 6, 236 3.60 / 4.54, 390 5.72 / 5.74
-    if (6 * k <= nb) return nb <= 640 || (k <= 64 && (24 * k <= nb || (16 * k <= nb && total > 12000)));
+    // 640 x 12, k = 102 1.07 of the wide kernel's time, 700 x 12, 112 1.09, 1182 x 12, 147 1.12, 189 1.09; 3 heads: 700, 56 0.99, 112
+    // 1.02, 1024, 163 1.005, 1182, 94 0.995, 236 0.97.  1500 x 3, 120 1.18 but 187 0.89; 2400 x 3, 192 1.14 but 384 0.68.
+    // Lists that start at their first entry: 768 x 12, 154 3.05 / 2.83, 1024 x 12, 256 1.05; 1182 x 12, 248 0.945, x 6, 236 3.60 / 4.54, 390 5.72 / 5.74
+    if (5 * k <= nb) return nb <= 640 || 12 * k <= nb || (nb <= 1280 && total > 4096);
     return nb <= 1024 || 3 * k >= nb;
   }
-  // 600 x 24, 96 3.85 / 3.13; 680 x 40, 82 6.63 / 6.08; 768 x 12, 61 1.83 / 1.49, 92 1.99 / 2.17, 154 3.11 / 4.11, 253 4.86 / 4.59;
-  // 1182 x 4, 142 2.30 / 2.02 but x 12, 142 5.11 / 5.95; 1182 x 6, 236 3.71 / 4.98; 1700 x 2, 714 5.41 / 6.25
-  if (5 * k >= 2 * nb) return nb <= 1280;
-  return 6 * k <= nb && (nb <= 640 || k <= 84 || (nb > 1024 && total <= 7168));
+  // 700 x 12, k = 56 1.18, 112 1.09, 231 1.04; 900 x 12, 112 1.09, 225 1.04; 1182 x 12, 59 1.19, 189 1.12, 248 1.06; x 3, 59 1.10, 236 1.01,
+  // 295 0.98, 472 1.05; beyond: 1500 x 3, 300 1.33 but 375 0.87; 1900 x 12, 95 1.04, x 3, 380 1.24 but 627 0.72
+  return nb <= 1280 || 5 * k <= nb;
 }
 
 template <int D, bool OUT_F32, bool RASTER>

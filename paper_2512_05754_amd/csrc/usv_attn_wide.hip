@@ -88,13 +88,13 @@ __device__ __forceinline__ void wait_lds() {
 }
 
 // WPS: waves per SIMD the register budget is sized for.  DEEP: one more ring slot (requests half a tile further ahead), for
-// heads whose K and V are far beyond the L2.  SWEEP: the lists start where the other workgroups are expected ("where the list
-// starts" below), and the waves of a SIMD take turns.
+// heads whose K and V are far beyond the L2.  TURNS: the waves of a SIMD
+// take turns ("taking turns" below).
 // RASTER: Q, K, V and the output are in raster token order (any strides); `ras.order[p]` gives the raster index of
 // cube-major position p.  Every wave fetches the 32 order entries of a half tile one step ahead of its K/V requests (one
 // more 4-byte-per-lane DMA per step, into a small LDS ring that only this wave reads) and turns them into the per-lane
 // global offsets of its DMA instructions; the epilogue stores each row at its raster position.
-template <int D, bool OUT_F32, int WPS, bool RASTER, bool DEEP, bool SWEEP>
+template <int D, bool OUT_F32, int WPS, bool RASTER, bool DEEP, bool TURNS>
 __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                           const uint16_t* __restrict__ v, const int32_t* __restrict__ idx,
                                                           const int32_t* __restrict__ cnt, void* __restrict__ out,
@@ -186,27 +186,29 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
   // ---- where the list starts -------------------------------------------------------------------
   // The workgroups of an XCD that run together share fetched tiles through its L2 as long as their sweeps over the
   // head's keys stay together.  Starting every list at its first entry keeps them together in the first round only: later
-  // workgroups start whenever a slot frees, and those times spread from round to round (measured at 12 heads, 512 blocks, 51
+  // workgroups start whenever a slot frees, and those times spread from round to round (measured with TURNS at 12 heads, 512 blocks, 51
   // listed, as a share of one sweep: 0.18 in round 1, 0.28, 0.37, 0.47, 0.54 in round 5; 40 heads of 1182 blocks 0.19 to 0.8
   // in round 6, where it stays).  So a workgroup starts its sweep where the others can be expected to be at its time.  The
   // k-th of the sweep_wgs of round m = rank / sweep_wgs starts before or after the round's middle by its share of that
   // spread, and the middles of all rounds meet the same place of the sweep: the list is walked from the first block at or past
-  // nb * width(m) * (k / sweep_wgs - 1/2), modulo nb, around the end, back to it.  A pure function of the launch: same bits
-  // every time; but the first tile sets the reference that a row's weights are rounded to bf16 against, so in another
-  // slot of a launch (or with another kmax) the same list may give a result that differs by that rounding.
-  // Measured, with "taking turns" below (start at 0 -> spread 0.5 sqrt(m) behind the first of a round, nobody taking turns -> here): 512 blocks x
-  // 12, 51 listed 800 -> 699 -> 661 us, 25 listed 487 -> 400 -> 385, 624 x 12, 62 listed 1078 -> 1006, 800 x 12, 64 listed 1635
-  // -> 1396, 1182 x 40, 59 listed 10.8 -> 7.70 -> 6.99 ms.  A width of 0.25 / 0.3 / 0.35 sqrt(m): 673 / 673 / 678 us, 398 / 385 / 383,
-  // 993 / 1006 / 1024, 1374 / 1396 / 1449, 7.25 / 7.00 / 6.92 ms.
+  // nb * width(m) * (k / sweep_wgs - 1/2), modulo nb, around the end, back to it.  Without turns the oldest wave of a SIMD runs ahead, the first
+  // quarter of a round starts far ahead of the rest, and a place counted from the round's first start is the better guess.
+  // A pure function of the launch: same bits every time; but the first tile sets the reference that a row's weights are
+  // rounded to bf16 against, so in another slot of a launch (or with another kmax) the same list may give a result that
+  // differs by that rounding.
+  // Measured (start at 0 -> without turns -> with): 512 blocks x 12, 51 listed 800 -> 699 -> 661 us, 25 listed 487 -> 400 -> 385, 624 x 12,
+  // 62 listed 1078 -> 1006, 800 x 12, 64 listed 1635 -> 1396, 1182 x 40, 59 listed 10.8 -> 7.70 -> 6.99 ms.  A width of 0.25 / 0.3 / 0.35 sqrt(m):
+  // 673 / 673 / 678 us, 398 / 385 / 383, 993 / 1006 / 1024, 1374 / 1396 / 1449, 7.25 / 7.00 / 6.92 ms; without turns spread 0.3 / 0.4 / 0.5 / 0.6
+  // / 0.8 sqrt(m) from the first start: 722 / 713 / 712 / 717 / 727 us.
   int first = 0;  // entry the sweep starts with
   int list_v;     // lane t: block of step 64 (n / 64) + t
   {
     const int raw = lane < kmax ? list[lane] : 0;  // (whatever the count says: this load does not wait for the count's)
     int pos = 0;
-    if (SWEEP && (rotate_short || n_list == kmax)) {
+    if (sweep_wgs > 0 && (rotate_short || n_list == kmax)) {
       const int rank = blockIdx.x / kNumXcd, m = rank / sweep_wgs;
-      const float width = fminf(1.0f, 0.3f * __builtin_amdgcn_sqrtf((float)m));
-      float at = width * ((float)(rank - m * sweep_wgs) / (float)sweep_wgs - 0.5f);
+      const float width = fminf(1.0f, (TURNS ? 0.3f : 0.5f) * __builtin_amdgcn_sqrtf((float)m));
+      float at = width * ((float)(rank - m * sweep_wgs) / (float)sweep_wgs - (TURNS ? 0.5f : 0.f));
       if (at < 0.f) at += 1.0f;
       pos = (int)(at * (float)nb);
     }
@@ -526,11 +528,11 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
     // their staying together counts, a wave's priority goes round with its steps, counted from its slot: whoever is ahead is
     // overtaken.  (Durations in the first round 120 +- 13 -> 113 +- 6 us.  Where the L2 serves the tiles anyway the old order
     // is the better one, as it keeps prologues and epilogues apart: all 512 blocks listed 5.73 / 5.93 ms.)
-    unsigned turn = SWEEP ? __builtin_amdgcn_s_getreg(4 | (3 << 11)) : 0;  // HW_ID, bits 0..3: the wave's slot of its SIMD
+    unsigned turn = TURNS ? __builtin_amdgcn_s_getreg(4 | (3 << 11)) : 0;  // HW_ID, bits 0..3: the wave's slot of its SIMD
     if (WPS == 3) turn %= 3;
     int n = 0;
     for (; n + 1 < n_list; ++n) {
-      if constexpr (SWEEP) {
+      if constexpr (TURNS) {
         if (WPS == 2 ? turn & 1 : turn == 1) __builtin_amdgcn_s_setprio(1);
         else if (WPS == 3 && turn == 2) __builtin_amdgcn_s_setprio(2);
         else __builtin_amdgcn_s_setprio(0);
@@ -684,18 +686,26 @@ hipError_t run(const AttnBf16Args& a, hipStream_t st) {
   constexpr int kSweepWgs = 256 / kNumXcd * (WPS * 4 / NW);      // workgroups of an XCD (32 CUs) that run together
   const long long kv_head = 4LL * s.nb * kBlock * D;             // bytes of one head's K and V
   // Lists that keep more than a fifth of the blocks stay together by themselves (whoever is ahead misses the L2 and is held
-  // up): start at the expected place and take turns / start at the first entry: 43 of 256 blocks 553 / 568 us, 51 of 256 639 / 650, 64 of 256
-  // 789 / 783, 85 of 512 1037 / 1140, 102 of 512 1245 / 1260, 128 of 512 1558 / 1535, 170 of 512 2051 / 1980.
-  const bool sweep = 5LL * a.kmax <= s.nb;
+  // up): start at the expected place / start at the first entry: 43 of 256 blocks 553 / 568 us, 51 of 256 639 / 650, 64 of 256
+  // 789 / 783, 85 of 512 1037 / 1140, 102 of 512 1245 / 1260, 128 of 512 1558 / 1535, 170 of 512 2051 / 1980.  In index order, heads
+  // beyond the L2 need more to stay together: 12 heads of 700 blocks, 175 listed 0.78 of the time, 800, 168 0.75, 900, 225
+  // 0.71, 1182, 248 0.73, 900 x 3, 297 0.93; 40 % listed: 800 x 12 1.04, 900 x 3 0.97, 1182 x 3 1.08.
+  const bool sweep = 5LL * a.kmax <= s.nb || (!a.work_order && s.nb > 512 && s.nb <= 1280 && 5LL * a.kmax < 2LL * s.nb);
+  // Taking turns keeps sweeps together, and it lets all workgroups of a round end at once: a part of a round behind them runs
+  // alone.  So it pays on long heads, and on many rounds.  Time with turns, as a multiple of the time without; d = 128, 4 % / 8 / 14 / 19.5 of the
+  // blocks listed: 160 blocks x 28 1.05 / 1.03 / 1.02 / 1.03, x 45 1.02 / 1.02 / 1.00 / 1.00; 230 x 10 0.98 / 1.02 / 1.05 / 1.07; 300 x 8 1.01 / 1.04 / 1.06 / 1.10, x 24 1.00 / 1.00 / 1.01 / 1.01; 512 x 4 0.95 / 1.06 / 1.09 / 1.09, x 9 0.94 / 0.93 / 0.99 / 1.00, x 14 0.97 /
+  // 0.98 / 0.98 / 0.98; 620 x 3 0.93 / 0.88 / 0.93 / 0.92, x 12 0.97 / 0.91 / 0.93 / 0.90.  d = 64: 512 x 21 1.02 / 1.02 / 1.04 / 1.03, 620 x 17
+  // 1.02 / 1.04 / 1.02 / 1.02, 1182 x 8, 100 listed 0.98.
+  const bool turns = sweep && (D == 64 ? s.nb > 800 : s.nb > 560 || (s.nb > 256 && total > 4096));
   // Lists of different lengths sweep at different speeds.  In index order they gain as the others do (40 of 512 at most:
   // 492 / 521 us); a work order brings equal lengths together, which keeps them together as long as a head is not much
   // beyond the L2: 16.8 MB 2480 / 2078 us, but 38.7 MB 7270 / 8050 us and (d = 64) 19.4 MB 2809 / 3235 us.
   const int rotate_short = !a.work_order || kv_head > (18LL << 20);
-  auto launch = [&](auto deep_c, auto sweep_c) {
-    attn_wide<D, OUT_F32, WPS, RASTER, decltype(deep_c)::value, decltype(sweep_c)::value><<<(unsigned)per_xcd * kNumXcd, 64 * NW, 0, st>>>(
+  auto launch = [&](auto deep_c, auto turns_c) {
+    attn_wide<D, OUT_F32, WPS, RASTER, decltype(deep_c)::value, decltype(turns_c)::value><<<(unsigned)per_xcd * kNumXcd, 64 * NW, 0, st>>>(
         static_cast<const uint16_t*>(a.q), static_cast<const uint16_t*>(a.k), static_cast<const uint16_t*>(a.v), a.idx,
         a.cnt, a.out, a.lse, s.nb, s.Nv, a.kmax, a.scale * kLog2e, probability_shift(a.kmax), (int)total, per_xcd, a.fuse,
-        a.ras, a.work_order, stream_output(s), kSweepWgs, rotate_short);
+        a.ras, a.work_order, stream_output(s), sweep ? kSweepWgs : 0, rotate_short);
   };
   // The extra slot costs a rotation of the ring offsets, 1.3 % where the L2 serves the requests (480p 709 -> 718 us), and
   // pays where it does not: 49152 tokens (25 MB) 1870 -> 1815 us, 75600 (38.7 MB) 8.09 -> 7.83 ms, 7.26 -> 7.21 with a work
@@ -703,7 +713,7 @@ hipError_t run(const AttnBf16Args& a, hipStream_t st) {
   constexpr bool kCanDeep = D == 128 && !RASTER;
   using Deep = std::integral_constant<bool, kCanDeep>;
   const bool deep = kCanDeep && kv_head > (24LL << 20);
-  if (sweep) deep ? launch(Deep{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
+  if (turns) deep ? launch(Deep{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
   else deep ? launch(Deep{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
   return hipGetLastError();
 }

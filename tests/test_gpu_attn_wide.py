@@ -263,3 +263,39 @@ def test_hugely_negative_logits_are_still_a_softmax(usv, d, Hh):
             # equal weights are exact in bf16: what is left is the fp32 sum of 192 values
             np.testing.assert_allclose(o[0, h, rows], want, rtol=0, atol=192 * 2.0 ** -24 * 4)
             np.testing.assert_allclose(l[0, h, rows], logit, rtol=1e-6)
+
+
+# Both sides of the lines at which lists start inside, waves take turns and long heads change kernels.
+@pytest.mark.parametrize("Hh,nb,d,kmax", [
+    (16, 257, 128, 51),    # just past four rounds and 256 blocks: turns; a fifth of the blocks
+    (16, 256, 128, 51),    # no turns
+    (3, 561, 128, 30),     # turns on a long head, under two rounds
+    (3, 561, 128, 130),    # past a fifth: starts inside in index order only
+    (3, 561, 128, 225),    # past two fifths: at the first entry
+    (2, 1281, 128, 256),   # beyond 1280 blocks a fifth is the line for the kernel, too
+    (2, 1281, 128, 257),
+    (7, 801, 64, 80),      # d = 64: three waves of a SIMD take turns
+    (7, 800, 64, 80),      # ... none do
+    (3, 1000, 64, 100),    # two rounds of a long head with short lists
+    (3, 1000, 64, 101),
+])
+def test_lines_of_the_rules_for_large_launches(usv, Hh, nb, d, kmax):
+    """Against a 64-bit evaluation of sampled blocks, within the bf16 bound, and three times the same bits."""
+    Nv = nb * 64 - 17
+    gen = torch.Generator(device=gu.DEV).manual_seed(nb + kmax)
+    q, k, v = ((torch.randn((1, Hh, nb, 64, d), device=gu.DEV, generator=gen) + 2 * torch.randn((1, Hh, nb, 1, d), device=gu.DEV, generator=gen))
+               .view(1, Hh, nb * 64, d).to(torch.bfloat16) for _ in range(3))
+    idx = torch.rand((1, Hh, nb, nb), device=gu.DEV, generator=gen).topk(kmax, dim=-1).indices.sort(-1).values.int()
+    cnt = torch.full((1, Hh, nb), kmax, dtype=torch.int32, device=gu.DEV)
+    for wo in (None, usv.attn_work_order(cnt, kmax, idx=idx)):
+        runs = [usv.block_sparse_attn(q, k, v, idx, cnt, seq_valid=Nv, out_dtype=torch.float32, return_lse=True, work_order=wo) for _ in range(3)]
+        assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for r in runs[1:] for a, b in zip(r, runs[0]))
+        for f in np.linspace(0, Hh * nb - 1, 11).astype(int):
+            h, i = f // nb, f % nb
+            keys = (idx[0, h, i].long()[:, None] * 64 + torch.arange(64, device=gu.DEV)).view(-1)
+            keys = keys[keys < Nv]
+            rows = slice(i * 64, min(i * 64 + 64, Nv))
+            S = q[0, h, rows].double() @ k[0, h][keys].double().T / d ** 0.5
+            what = f"head {h} block {i} ordered {wo is not None}"
+            gu.assert_attn_close(gu.down(runs[0][0][0, h, rows]), (S.softmax(-1) @ v[0, h][keys].double()).cpu().numpy(), "bf16", what)
+            assert (runs[0][1][0, h, rows] - S.logsumexp(-1)).abs().max() <= 2e-2, what
