@@ -63,19 +63,18 @@ __device__ __forceinline__ void dma_item(unsigned lds, const void* base, int eve
       : "s"(lds), "v"(even), "v"(odd), "s"(base)
       : "memory");
 }
-__device__ __forceinline__ void dma_item(unsigned lds, const void* base, int v0, int v1, int v2, int v3) {  // rows anywhere
+// Half an item, rows anywhere: instructions 2 HALF and 2 HALF + 1.  Offset of instruction r from base: its rows' plus kBack - 1024 r
+// (the instruction's own offset goes to both addresses).  Halves, so that two address registers do.
+constexpr int kBack = 3072;
+template <int HALF>
+__device__ __forceinline__ void dma_half(unsigned lds, const void* base, unsigned v0, unsigned v1) {
   asm volatile(
       "s_mov_b32 m0, %0\n\t"
-      "global_load_lds_dwordx4 %1, %5\n\t"
-      "s_add_u32 m0, m0, 0x400\n\t"
-      "global_load_lds_dwordx4 %2, %5\n\t"
-      "s_add_u32 m0, m0, 0x400\n\t"
-      "global_load_lds_dwordx4 %3, %5\n\t"
-      "s_add_u32 m0, m0, 0x400\n\t"
-      "global_load_lds_dwordx4 %4, %5"
+      "global_load_lds_dwordx4 %1, %3 offset:%4\n\t"
+      "global_load_lds_dwordx4 %2, %3 offset:%5"
       :
-      : "s"(lds), "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(base)
-      : "memory", "scc");
+      : "s"(lds), "v"(v0), "v"(v1), "s"(static_cast<const unsigned char*>(base) - kBack), "n"(2048 * HALF), "n"(2048 * HALF + 1024)
+      : "memory");
 }
 
 template <int N>
@@ -87,13 +86,23 @@ __device__ __forceinline__ void wait_lds() {
   asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// The lane number, formed anew where it is asked for: a value that is kept ahead of the loop is a register raster mode has not got.
+__device__ __forceinline__ int lane_again() {
+  unsigned all = ~0u;
+  asm volatile("" : "+s"(all));
+  return __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+}
+
 // WPS: waves per SIMD the register budget is sized for.  DEEP: one more ring slot (requests half a tile further ahead), for
 // heads whose K and V are far beyond the L2.  TURNS: the waves of a SIMD
 // take turns ("taking turns" below).
 // RASTER: Q, K, V and the output are in raster token order (any strides); `ras.order[p]` gives the raster index of
 // cube-major position p.  Every wave fetches the 32 order entries of a half tile one step ahead of its K/V requests (one
-// more 4-byte-per-lane DMA per step, into a small LDS ring that only this wave reads) and turns them into the per-lane
-// global offsets of its DMA instructions; the epilogue stores each row at its raster position.
+// more 4-byte-per-lane DMA per step, into a small LDS ring that only this wave reads), turns them into byte offsets where they
+// lie, once per step, and adds them to the per-lane offsets of its DMA instructions; the epilogue stores each row at its raster position.
+// (The entries read and multiplied anew for each of a step's sixteen DMA instructions, in front of the MFMAs, took 24 % more clocks than
+// the kernel for cube-major tensors; and the order entries of Q and of the output rows were loaded one after the other, 2.5 + 4.4 us a
+// workgroup.  12 heads, 51 of 512 blocks 764 -> 734 us, cubes 62 of 624 1056 -> 1014; cube-major 667.)
 template <int D, bool OUT_F32, int WPS, bool RASTER, bool DEEP, bool TURNS>
 __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                           const uint16_t* __restrict__ v, const int32_t* __restrict__ idx,
@@ -152,6 +161,21 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
   const int vofs = (RASTER ? 0 : drow * kRowBytes) + (((lane & 7) ^ (((lane >> 4) & 3) << 1)) << 4);
   const unsigned wave_lds = lds_address(smem) + wave * kWaveBytes;
   int* const my_ord = ord_ring + (RASTER ? wave * 64 : 0);
+  // raster mode: byte offsets of the rows this lane fetches in its DMA instructions for step n (the same rows of K and of V)
+  unsigned row_at[RASTER ? 4 : 1];
+  auto read_order = [&](int n) {
+    if constexpr (RASTER) {
+      const int* p = my_ord + (n & 1) * 32 + drow;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) row_at[r] = p[r * (D == 128 ? 4 : 8)];
+    }
+  };
+  auto scale_order = [&]() {
+    if constexpr (RASTER) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) row_at[r] *= (unsigned)ras.tok;
+    }
+  };
   // item x of tile j (step n): x < LINES: line x of K, else line x - LINES of V
   auto dma = [&](auto x_c, int j, int n, unsigned at) {
     constexpr int x = decltype(x_c)::value;
@@ -159,10 +183,9 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
     const unsigned char* base = (x < LINES ? kbase : vbase) + (x % LINES) * 128;
     if constexpr (x < LINES) asm volatile("" : "+v"(kofs));  // (the odd half is one XOR here, not a register)
     if constexpr (RASTER) {
-      const int even = x < LINES ? kofs : vofs, odd = x < LINES ? kofs ^ 64 : vofs, tok = (int)ras.tok;
-      const int* p = my_ord + (n & 1) * 32 + drow;
-      constexpr int R = D == 128 ? 4 : 8;
-      dma_item(lds, base, p[0] * tok + even, p[R] * tok + odd, p[2 * R] * tok + even, p[3 * R] * tok + odd);
+      const unsigned even = x < LINES ? kofs : vofs, odd = x < LINES ? kofs ^ 64 : vofs;
+      dma_half<0>(lds, base, row_at[0] + even + kBack, row_at[1] + odd + (kBack - 1024));
+      dma_half<1>(lds, base, row_at[2] + even + (kBack - 2048), row_at[3] + odd + (kBack - 3072));
     } else {
       base += (long long)j * (kBlock * kRowBytes);
       if constexpr (x < LINES) dma_item(lds, base, kofs, kofs ^ 64);
@@ -172,8 +195,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
   // raster mode: the 32 order entries of this wave's half of tile j, step n -> slot n % 2 of its ring
   auto request_order = [&](int j, int n) {
     if constexpr (RASTER) {
-      int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-      asm volatile("" : "+v"(ln));
+      const int ln = lane_again();
       if (ln < 32) {
         const unsigned dst = lds_address(my_ord) + (n & 1) * 128;
         const int32_t* src = ras.order + (long long)j * kBlock + wave * 32;
@@ -182,6 +204,13 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
       }
     }
   };
+
+  // raster mode: where this lane's four query rows lie
+  int q_order[RASTER ? 4 : 1];
+  if constexpr (RASTER) {
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) q_order[nt] = ras.order[i * kBlock + 16 * nt + c16];
+  }
 
   // ---- where the list starts -------------------------------------------------------------------
   // The workgroups of an XCD that run together share fetched tiles through its L2 as long as their sweeps over the
@@ -255,6 +284,8 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
       request_order(id_of(j0), 0);
       if (n_list > 1) request_order(id_of(j1), 1);
       wait_vm<0>();
+      read_order(0);
+      scale_order();
     }
     dma(I0{}, j0, 0, 0 * kItem);
     dma(I1{}, j0, 0, 1 * kItem);
@@ -274,17 +305,22 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
     const uint16_t* qp = q + head_off + (long long)qrow * D + G * 8;
     if constexpr (RASTER)
       qp = reinterpret_cast<const uint16_t*>(reinterpret_cast<const unsigned char*>(q) + ras_off +
-                                             (long long)ras.order[qrow] * ras.tok) + G * 8;
+                                             (long long)q_order[nt] * ras.tok) + G * 8;
 #pragma unroll
     for (int t = 0; t < KS; ++t) qf[nt][t] = *reinterpret_cast<const bf16x8*>(qp + t * 32);
-    if constexpr (RASTER) {
-      // padding positions have no token: their query rows are zero, as in a gathered copy (their lanes
-      // take part in the wave-wide rescale decisions, so what they hold is not quite without effect)
-      if (16 * nt + c16 >= nq) {
+  }
+  if constexpr (RASTER) {
+    // padding positions have no token: their query rows are zero, as in a gathered copy (their lanes
+    // take part in the wave-wide rescale decisions, so what they hold is not quite without effect)
+    if (nq < kBlock) {  // (after all the loads: a branch between them would wait for each)
 #pragma unroll
-        for (int t = 0; t < KS; ++t)
+      for (int nt = 0; nt < 4; ++nt) {
+        const unsigned keep = 16 * nt + c16 < nq ? ~0u : 0u;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) qf[nt][t][e] = (__bf16)0.0f;
+        for (int t = 0; t < KS; ++t) {
+          typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
+          qf[nt][t] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, qf[nt][t]) & u32x4{keep, keep, keep, keep});
+        }
       }
     }
   }
@@ -361,17 +397,19 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
     // ---- S^T = K Q^T: s[mt], quarter nt = tile (mt, nt) ----
     f32x16 s[2];
     asm volatile("" : "+v"(kl), "+v"(vl));  // keeps the XORs in the loop (hoisted, they are registers this kernel has not got)
-    bf16x8 kf[KF];
+    bf16x8 kf[KF], ql[QL > 0 ? QL : 1];
     auto read_k = [&](int f) {  // fragment f = 2 t + mt
       kf[f % KF] = *reinterpret_cast<const bf16x8*>(smem + ((kl + ring[f >> 2]) ^ (((f >> 1) & 1) << 6)) + (f & 1) * 2048);
     };
     await(I0{});
+    if constexpr (!LAST) read_order(n + 1);  // (asked for before this step's first item was: they are there)
 #pragma unroll
     for (int f = 0; f < KF - 1; ++f) read_k(f);
 #pragma unroll
     for (int f = 0; f < 2 * KS; ++f) {
       if (LINES == 2 && f + KF - 1 == 4) await(I1{});
       if (f + KF - 1 < 2 * KS) read_k(f + KF - 1);
+      if (f == 1 && !LAST) scale_order();
       if (f == 3) {
         wait_lds<(LINES == 2 ? KF - 1 : 0)>();  // (LDS reads return in order)
         refill(I0{});
@@ -380,10 +418,8 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
         wait_lds<0>();
         refill(I1{});
       }
-      bf16x8 ql[QL > 0 ? QL : 1];
-      if (QL > 0 && f >= 2 * KS - 2) {
-        unsigned ql_at = lane * 16;
-        asm volatile("" : "+v"(ql_at));
+      if (QL > 0 && f == 2 * KS - 2) {  // (for the last two fragments)
+        const unsigned ql_at = lane_again() * 16;
 #pragma unroll
         for (int e = 0; e < QL; ++e) ql[e] = *reinterpret_cast<const bf16x8*>(q_tail + ql_at + e * 1024);
       }
@@ -401,7 +437,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
 
     // s[mt][4 nt + r] of lane (c16, G) is stored row 16 mt + 4 G + r, query 16 nt + c16
     if (RASTER ? (j0 >> 16) < kBlock : j0 >= first_padded_j) {
-      int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+      int ln = RASTER ? lane_again() : __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
       float ninf = -INFINITY;
       asm volatile("" : "+v"(ln), "+v"(ninf));  // formed here, on the rare path, instead of kept in registers
       const int g = ln >> 4;
@@ -507,7 +543,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
       j0 = j1;
       j1 = j2;
       if (((n + 3) & 63) == 0) {  // the next 64 entries; awaited right here (once in 64 steps) so that the hot path
-        int t = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));  // carries no vector-memory wait
+        int t = RASTER ? lane_again() : __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));  // carries no vector-memory wait
         asm volatile("" : "+v"(t));
         t += n + 3;
         int e = t + first;
@@ -556,6 +592,8 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
   float l_row[4];
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt) l_row[nt] = sum_over_groups(l[nt]);
+  int my_order = 0;  // raster mode: lane r holds where the wave's row r % 32 lies; asked for here, used behind the exchange
+  if constexpr (RASTER) my_order = ras.order[i * kBlock + 32 * wave + (lane & 31)];
   auto give = [&](auto first_c) {
     constexpr int F = decltype(first_c)::value;
     float* dst = reinterpret_cast<float*>(smem + wave * kWaveBytes) + lane;
@@ -622,7 +660,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
   // rows this wave staged itself: no barrier)
   auto out_row = [&](int row) -> unsigned char* {
     if constexpr (RASTER)
-      return static_cast<unsigned char*>(out) + ras_out + (long long)ras.order[i * kBlock + row] * ras.o_tok;
+      return static_cast<unsigned char*>(out) + ras_out + (long long)__shfl(my_order, row & 31) * ras.o_tok;
     else
       return static_cast<unsigned char*>(out) + (blk_off + row * D) * (OUT_F32 ? 4 : 2);
   };
@@ -640,7 +678,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
       const int row = 32 * wave + (it * 64 + lane) / (D / 8);
       long long at = blk_off + row * D + c8;  // (padded rows are there to be read; a padding position's order entry is a valid token)
       if constexpr (RASTER)  // the gates are raster tensors laid out like q
-        at = (ras_off + (long long)ras.order[i * kBlock + row] * ras.tok) / 2 + c8;
+        at = (ras_off + (long long)__shfl(my_order, row & 31) * ras.tok) / 2 + c8;
       constexpr unsigned kOnes = 0x3f803f80u;  // an absent gate is 1
       gf[it] = gc[it] = gate8{kOnes, kOnes, kOnes, kOnes};
       if (fuse.gate_fine) gf[it] = __builtin_nontemporal_load(reinterpret_cast<const gate8*>(fuse.gate_fine + at));
@@ -655,6 +693,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
 #pragma unroll
     for (int it = 0; it < PIECES8; ++it) {
       const int rr = (it * 64 + lane) / (D / 8), row = 32 * wave + rr;
+      unsigned char* const dst = out_row(row) + c8 * (OUT_F32 ? 4 : 2);  // (ahead of the branch: it reads other lanes)
       if (RASTER && row >= nq) continue;  // the raster tensor has no padded rows
       float4 val[2];
 #pragma unroll
@@ -662,7 +701,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
         val[e] = *reinterpret_cast<const float4*>(other + rr * OSTRIDE + c8 + 4 * e);
         if (row < nq) fuse4(val[e], bf16_pair(gf[it][2 * e], gf[it][2 * e + 1]), bf16_pair(gc[it][2 * e], gc[it][2 * e + 1]), cz[e]);
       }
-      store8<OUT_F32>(out_row(row) + c8 * (OUT_F32 ? 4 : 2), val, stream_out);
+      store8<OUT_F32>(dst, val, stream_out);
     }
   } else {
     constexpr int PIECES = 32 * D / 4;
@@ -670,9 +709,10 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
     for (int it = 0; it < PIECES / 64; ++it) {
       const int id = it * 64 + lane;
       const int rr = id / (D / 4), row = 32 * wave + rr, c4 = (id % (D / 4)) * 4;
+      unsigned char* const dst = out_row(row) + c4 * (OUT_F32 ? 4 : 2);
       if (RASTER && row >= nq) continue;
       const float4 val = *reinterpret_cast<const float4*>(other + rr * OSTRIDE + c4);
-      store4<OUT_F32>(out_row(row) + c4 * (OUT_F32 ? 4 : 2), val, stream_out);
+      store4<OUT_F32>(dst, val, stream_out);
     }
   }
 }

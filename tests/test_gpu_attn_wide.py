@@ -299,3 +299,22 @@ def test_lines_of_the_rules_for_large_launches(usv, Hh, nb, d, kmax):
             what = f"head {h} block {i} ordered {wo is not None}"
             gu.assert_attn_close(gu.down(runs[0][0][0, h, rows]), (S.softmax(-1) @ v[0, h][keys].double()).cpu().numpy(), "bf16", what)
             assert (runs[0][1][0, h, rows] - S.logsumexp(-1)).abs().max() <= 2e-2, what
+
+
+@pytest.mark.parametrize("Hh,nb,d,packed", [(13, 130, 128, True), (13, 130, 128, False), (43, 130, 64, True)])
+def test_raster_rows_far_apart(usv, Hh, nb, d, packed):
+    """Row offsets of a raster launch: tokens far apart (other columns of a wider projection lie between them), in random order, against the
+    same tensors gathered; lists of 0, 1, 2 and more entries (the steps whose order entries are requested before the loop)."""
+    gen = torch.Generator(device=gu.DEV).manual_seed(nb + d)
+    N = nb * 64
+    def tensor():
+        x = torch.randn((1, N, Hh, d) if packed else (1, Hh, N, 3 * d), device=gu.DEV, generator=gen).to(torch.bfloat16)
+        return x.transpose(1, 2) if packed else x[..., d:2 * d]
+    q, k, v = tensor(), tensor(), tensor()
+    idx = torch.rand((1, Hh, nb, nb), device=gu.DEV, generator=gen).topk(5, dim=-1).indices.sort(-1).values.int()
+    cnt = torch.randint(0, 6, (1, Hh, nb), device=gu.DEV, generator=gen, dtype=torch.int32)
+    order = torch.randperm(N, device=gu.DEV, generator=gen)
+    out, lse = usv.block_sparse_attn_raster(q, k, v, order.int(), idx, cnt, out_dtype=torch.float32, return_lse=True)
+    want, want_lse = usv.block_sparse_attn(*(t[:, :, order].contiguous() for t in (q, k, v)), idx, cnt, out_dtype=torch.float32, return_lse=True)
+    assert torch.equal(out[:, :, order].view(torch.int32), want.view(torch.int32))
+    assert torch.equal(lse[:, :, order].view(torch.int32), want_lse.view(torch.int32))
