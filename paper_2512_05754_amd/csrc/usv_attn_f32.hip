@@ -18,6 +18,7 @@
 // Splitting the V rows between the MFMAs of the first product and the next K rows between those of the second took as many
 // clocks and more power (645 us): the second workgroup already fills those gaps.
 //
+// attn_f32_few: 16 query rows to a workgroup, for launches of few query blocks; the same products and the same bounds on what a split can carry.
 // attn_f32: one workgroup = 4 KH wavefronts = one 64-row query block; wave w owns query rows 16 (w % 4) .. + 15.  KH = 1: 32 keys
 // (half a listed block) per step, every wave sees them all and nothing is merged at the end.  KH = 2 (small grids, see the
 // launcher): a whole block per step, waves 0..3 take its first half and waves 4..7 its second, merged once through LDS.  K and V rows are fetched into
@@ -56,7 +57,7 @@ template <int D>  // (inlined: a call would need scratch memory)
 __device__ __forceinline__ void fp32_block(unsigned char* smem, const float* __restrict__ q, const float* __restrict__ k,
                            const float* __restrict__ v, const int32_t* __restrict__ idx, int n_list,
                            float* __restrict__ out, float* __restrict__ lse, long long blk, int nb, int Nv, int kmax,
-                           float scale_log2e) {
+                           float scale_log2e, int row_lo = 0, int row_hi = kBlock) {  // writes rows row_lo .. row_hi - 1
   constexpr int LD = D + 4;      // LDS row stride in floats: 16-byte reads of consecutive rows spread over the banks
   constexpr int DSUB = D / 32;   // 32-wide d sub-tiles of the output
   constexpr int HALF = D / 2;    // channels per lane half in the first product
@@ -229,7 +230,9 @@ __device__ __forceinline__ void fp32_block(unsigned char* smem, const float* __r
         val.w = live ? o[ds][rq * 4 + 3] * w0 + src[(ds * 16 + rq * 4 + 3) * 64] * w1 : 0.f;
         *reinterpret_cast<float4*>(stage + 32 * ds + 8 * rq + 4 * g) = val;
       }
-    if (lse && g == 0) lse[head * (long long)nb * kBlock + token] = live ? (mm + __log2f(lt)) * kLn2 : -INFINITY;
+    const int row = qh * 32 + col;
+    if (lse && g == 0 && row >= row_lo && row < row_hi)
+      lse[head * (long long)nb * kBlock + token] = live ? (mm + __log2f(lt)) * kLn2 : -INFINITY;
   }
   __syncthreads();
   {
@@ -238,6 +241,7 @@ __device__ __forceinline__ void fp32_block(unsigned char* smem, const float* __r
 #pragma unroll
     for (int e = tid; e < kBlock * (D / 4); e += 256) {
       const int row = e / (D / 4), c = (e % (D / 4)) * 4;
+      if (row < row_lo || row >= row_hi) continue;
       *reinterpret_cast<float4*>(ob + row * D + c) = *reinterpret_cast<const float4*>(Vs + row * LD + c);
     }
   }
@@ -608,6 +612,238 @@ __global__ __launch_bounds__(256 * KH, 2) void attn_f32(const float* __restrict_
   }
 }
 
+// Few query blocks: one workgroup of eight waves = 16 query rows, so that four times as many CUs have work, and the waves share out
+// the 32-key halves of the listed blocks instead of staging them together: a wave fetches its half straight into the lanes that
+// need it (V by single channels, which is the transpose the second product wants), splits it there, and meets the others once, at
+// the end, through LDS.  The loop has no barrier and no LDS.  What is paid for it: every half is split by four workgroups
+// instead of one.  Bound by latency: launch, list, one round trip for the operands, the splits, the store (times at the
+// launcher's rule).
+template <int D>
+__global__ __launch_bounds__(512, 2) void attn_f32_few(const float* __restrict__ q, const float* __restrict__ k,
+                                                       const float* __restrict__ v, const int32_t* __restrict__ idx,
+                                                       const int32_t* __restrict__ cnt, float* __restrict__ out,
+                                                       float* __restrict__ lse, int nb, int Nv, int kmax, float scale_log2e,
+                                                       float qk_limit, int total, int per_xcd) {
+  constexpr int KS = D / 32, DT = D / 16, CH = D / 8, W = 8, ROWS = 16;
+  constexpr bool kEarlyV = D == 64;   // registers for K and V of a half at once
+  constexpr int LD = D + 4;           // row stride of a wave's part of O
+  constexpr int VE = ROWS * D / 512;  // channels of a row that a thread finishes
+  constexpr int kParts = W * (ROWS * LD + 2 * ROWS) * (int)sizeof(float);
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kF32Lds<D> > kParts ? kF32Lds<D> : kParts];
+  __shared__ float v_tops[W][CH];  // largest |V| that a wave has split, per 8 channels
+  __shared__ int redo[W];
+  __shared__ int redo_any, subnormal_v;
+  __shared__ unsigned zero_at;
+
+  const int work = xcd_contiguous_id(blockIdx.x, per_xcd);
+  if (work >= total) return;  // whole workgroup leaves before any barrier
+  const long long blk = work >> 2;
+  const int rg = work & 3, i = (int)(blk % nb);
+  const long long head_off = (blk / nb) * (long long)nb * kBlock * D;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c16 = lane & 15, G = lane >> 4;
+  const int32_t* list = idx + blk * kmax;
+  auto block_at = [&](int n) { return min(max(list[n], 0), nb - 1); };  // device contents are not trusted with addresses
+
+  // half h of block j: K fragment (mt, t): key 16 mt + c16, channels 32 t + 8 G .. + 8; V^T fragment dt: channel 16 dt + c16, keys 16 (e / 4) + 4 G + e % 4
+  float4 kraw[2 * KS][2];
+  float vraw[DT][8];
+  auto fetch_k = [&](int j, int half) {
+    const float* p = k + head_off + ((long long)j * kBlock + half * 32 + c16) * D + 8 * G;
+#pragma unroll
+    for (int f = 0; f < 2 * KS; ++f)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) kraw[f][e] = reinterpret_cast<const float4*>(p + 16 * (f & 1) * D + 32 * (f >> 1))[e];
+  };
+  auto fetch_v = [&](int j, int half) {
+    const float* p = v + head_off + ((long long)j * kBlock + half * 32 + 4 * G) * D + c16;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) vraw[dt][e] = p[(16 * (e >> 2) + (e & 3)) * D + 16 * dt];
+  };
+  // the wave's first half: asked for before the list's length is known (the entry is there to be read, whatever it says)
+  int j = block_at(min(wave >> 1, kmax - 1));
+  fetch_k(j, wave & 1);
+  Split qf[KS];
+  float q_top = 0.f, k_top = 0.f, v_max[DT];
+  {
+    const float* qp = q + head_off + ((long long)i * kBlock + rg * ROWS + c16) * D + G * 8;
+    float4 raw[KS][2];
+#pragma unroll
+    for (int t = 0; t < KS; ++t) raw[t][0] = reinterpret_cast<const float4*>(qp + 32 * t)[0], raw[t][1] = reinterpret_cast<const float4*>(qp + 32 * t)[1];
+    if (kEarlyV) fetch_v(j, wave & 1);
+#pragma unroll
+    for (int t = 0; t < KS; ++t) {
+      float x[8];
+      *reinterpret_cast<float4*>(x) = raw[t][0];
+      *reinterpret_cast<float4*>(x + 4) = raw[t][1];
+      largest8(q_top, x);
+      qf[t] = split8(x);
+    }
+  }
+  const int n_list = min(max(cnt[blk], 0), kmax);
+  f32x4 o[DT], o5[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) o[dt] = o5[dt] = f32x4{0.f, 0.f, 0.f, 0.f}, v_max[dt] = 0.f;
+  float m = -INFINITY, m_ref = 0.f, l = 0.f;
+
+  for (int c = wave; c < 2 * n_list; c += W) {
+    const int nkeys = Nv - j * kBlock - (c & 1) * 32;  // valid keys of this half (below 32 only at the end of the sequence)
+    const int jn = block_at(min((c + W) >> 1, n_list - 1));
+    f32x4 s[2], t5[2];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) s[mt] = t5[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int f = 0; f < 2 * KS; ++f) {
+      float x[8];
+      *reinterpret_cast<float4*>(x) = kraw[f][0];
+      *reinterpret_cast<float4*>(x + 4) = kraw[f][1];
+      largest8(k_top, x);
+      const Split a = split8(x);
+      const bf16x8(&y)[3] = qf[f >> 1].p;
+      f32x4& big = s[f & 1];
+      f32x4& small = t5[f & 1];
+      small = mfma(a.p[2], y[0], small);
+      small = mfma(a.p[0], y[2], small);
+      small = mfma(a.p[1], y[1], small);
+      small = mfma(a.p[1], y[0], small);
+      small = mfma(a.p[0], y[1], small);
+      big = mfma(a.p[0], y[0], big);
+    }
+    if (!kEarlyV) fetch_v(j, c & 1);
+    else if (c + W < 2 * n_list) fetch_k(jn, c & 1);
+    float x[8];  // key 16 (e / 4) + 4 G + e % 4 of the half, query c16
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = s[e >> 2][e & 3] + t5[e >> 2][e & 3];
+    if (nkeys < 32) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = 16 * (e >> 2) + 4 * G + (e & 3) < nkeys ? x[e] : -INFINITY;
+    }
+    // online softmax, as in attn_f32
+    float mx = x[0];
+#pragma unroll
+    for (int e = 1; e < 8; ++e) mx = fmaxf(mx, x[e]);
+    if (__any(mx * scale_log2e - m > kRescaleSlack)) {
+      const float m_new = fmaxf(m, max_over_groups(mx) * scale_log2e);
+      m_ref = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = fast_exp2(m - m_ref);
+      m = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[dt][r] *= alpha, o5[dt][r] *= alpha;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      x[e] = fast_exp2(fmaf(x[e], scale_log2e, -m_ref));
+      l += x[e];
+    }
+    const Split pf = split8(x);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      if (nkeys < 32) {  // padded rows may hold any finite value, also one that rounds to infinity: their p is 0
+#pragma unroll
+        for (int e = 0; e < 8; ++e) vraw[dt][e] = 16 * (e >> 2) + 4 * G + (e & 3) < nkeys ? vraw[dt][e] : 0.f;
+      }
+      largest8(v_max[dt], vraw[dt]);
+      const Split y = split8(vraw[dt]);
+      o5[dt] = mfma(y.p[2], pf.p[0], o5[dt]);
+      o5[dt] = mfma(y.p[0], pf.p[2], o5[dt]);
+      o5[dt] = mfma(y.p[1], pf.p[1], o5[dt]);
+      o5[dt] = mfma(y.p[1], pf.p[0], o5[dt]);
+      o5[dt] = mfma(y.p[0], pf.p[1], o5[dt]);
+      o[dt] = mfma(y.p[0], pf.p[0], o[dt]);
+    }
+    if (c + W < 2 * n_list) {
+      if (kEarlyV) fetch_v(jn, c & 1);
+      else fetch_k(jn, c & 1);
+    }
+    j = jn;
+  }
+
+  // ---- the waves' parts meet: row c16's O, reference and sum of each ----
+  float* const part = reinterpret_cast<float*>(smem) + wave * ROWS * LD;
+  float* const stats = reinterpret_cast<float*>(smem) + W * ROWS * LD;  // [W][2][ROWS]
+  {
+    const float lt = sum_over_groups(l);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const f32x4 both = o[dt] + o5[dt];
+      *reinterpret_cast<f32x4*>(part + c16 * LD + 16 * dt + 4 * G) = both;
+      float top = max_over_groups(v_max[dt]);
+#pragma unroll
+      for (int d = 1; d < 8; d <<= 1) top = fmaxf(top, __shfl_xor(top, d));
+      if (G == 0 && (c16 & 7) == 0) v_tops[wave][2 * dt + (c16 >> 3)] = top;
+    }
+    if (G == 0) stats[2 * ROWS * wave + c16] = m, stats[2 * ROWS * wave + ROWS + c16] = lt;
+    const bool bad = (q_top >= qk_limit && i * kBlock + rg * ROWS + c16 < Nv && n_list > 0) || k_top >= qk_limit;
+    const int any_bad = __any(bad);
+    if (lane == 0) redo[wave] = any_bad;
+    if (tid == 0) redo_any = 0, zero_at = 0, subnormal_v = 0;
+  }
+  __syncthreads();
+  const int row = tid >> 5, ch = (tid & 31) * VE;  // 32 threads to a row
+  float mm = -INFINITY, lt = 0.f, top = 0.f, y[VE];
+  int again = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) mm = fmaxf(mm, stats[2 * ROWS * w + row]), top = fmaxf(top, v_tops[w][ch >> 3]), again |= redo[w];
+  const float ref = mm == -INFINITY ? 0.f : mm;
+#pragma unroll
+  for (int e = 0; e < VE; ++e) y[e] = 0.f;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    const float a = fast_exp2(stats[2 * ROWS * w + row] - ref);  // (a wave without keys: -inf, sum and O 0)
+    lt += stats[2 * ROWS * w + ROWS + row] * a;
+    const float* src = reinterpret_cast<const float*>(smem) + (w * ROWS + row) * LD + ch;
+#pragma unroll
+    for (int e = 0; e < VE; ++e) y[e] += src[e] * a;
+  }
+  const int token = i * kBlock + rg * ROWS + row;
+  const bool mine = token < Nv && n_list > 0, live = mine && lt > 0.f;  // lt == 0: every listed key is padding
+  const float inv = live ? 1.f / lt : 0.f, least = fmaxf(kTiny, top * kTiny);
+  bool bad = mine && !(lt < INFINITY), zero = false;
+#pragma unroll
+  for (int e = 0; e < VE; ++e) {
+    y[e] = live ? y[e] * inv : 0.f;
+    const float a = fabsf(y[e]);
+    bad |= !(a < INFINITY) || (live && a < least && (a > 0.f || (top > 0.f && top < kTiny)));
+    zero |= live && a == 0.f && top > 0.f;
+  }
+  if (zero) atomicOr(&zero_at, 1u << (ch >> 3));
+  if (bad) redo_any = 1;
+  __syncthreads();
+  again |= redo_any;
+  if (!again && zero_at) {  // results of 0 beside other values: is V 0 there, or too small to be split?
+    bool sub = false;
+    auto is_sub = [](unsigned x) { return (x & 0x7fffffffu) - 1u < 0x007fffffu; };
+    for (unsigned left = zero_at; left; left &= left - 1) {
+      const int c8 = __ffs(left) - 1;
+#pragma unroll 4
+      for (int e = tid; e < n_list * kBlock; e += 512) {  // a row of these eight channels each
+        const int r = block_at(e / kBlock) * kBlock + e % kBlock;
+        const uint4* at = reinterpret_cast<const uint4*>(v + head_off + (long long)min(r, Nv - 1) * D + c8 * 8);
+        const uint4 a = at[0], b = at[1];
+        const bool any = is_sub(a.x) | is_sub(a.y) | is_sub(a.z) | is_sub(a.w) | is_sub(b.x) | is_sub(b.y) | is_sub(b.z) | is_sub(b.w);
+        sub |= any && r < Nv;
+      }
+    }
+    if (__any(sub) && lane == 0) subnormal_v = 1;
+    __syncthreads();
+    again = subnormal_v;
+  }
+  if (again) {  // (these 16 rows only: the block's other rows are other workgroups')
+    fp32_block<D>(smem, q, k, v, idx, n_list, out, lse, blk, nb, Nv, kmax, scale_log2e, rg * ROWS, (rg + 1) * ROWS);
+    return;
+  }
+  if (lse && ch == 0) lse[(blk / nb) * (long long)nb * kBlock + token] = live ? (mm + __log2f(lt)) * kLn2 : -INFINITY;
+  float* dst = out + head_off + (long long)token * D + ch;
+  if constexpr (VE == 2) *reinterpret_cast<float2*>(dst) = make_float2(y[0], y[1]);
+  else *reinterpret_cast<float4*>(dst) = make_float4(y[0], y[1], y[2], y[3]);
+}
+
 }  // namespace
 
 hipError_t launch_attn_f32(const float* q, const float* k, const float* v, const Dims& s, const int32_t* idx,
@@ -626,6 +862,19 @@ hipError_t launch_attn_f32(const float* q, const float* k, const float* v, const
   // second workgroup to compute while one stages.  KH = 1 / 2, 20 listed: d = 64, 128 blocks 50.2 / 37.1 us, 256: 50.6 / 38.7, 320:
   // 68.6 / 70.6, 512: 72.8 / 73.7; d = 128, 128 blocks 87 / 64 us, 256: 88 / 69, 320: 117 / 126, 512: 127 / 135.
   const bool few = total <= 256;
+  // Up to 64 query blocks, four workgroups of 16 rows to a block still have a CU each.  attn_f32<D, 2> / attn_f32_few, lists of 1, 3, 6, 12, 16: d = 64,
+  // 64 blocks 8.7 / 8.4, 9.8 / 8.2, 14.8 / 9.7, 24.0 / 13.9, 30.2 / 16.8 us (8 us are the host's), 128 blocks 9.9 / 14.5 (3), 30.4 / 31.0 (16);
+  // d = 128, 64 blocks 9.6 / 10.3, 15.7 / 12.8, 24.2 / 16.2, 41.4 / 25.4, 52.8 / 31.9, 128 blocks 16.1 / 24.3, 53.4 / 60.2.
+  if (total <= 64 && (s.d == 64 || kmax > 1)) {
+    const int groups = 4 * total, per = (groups + kNumXcd - 1) / kNumXcd;
+    auto go = [&](auto d_c) {
+      attn_f32_few<decltype(d_c)::value><<<(unsigned)per * kNumXcd, 512, 0, st>>>(q, k, v, idx, cnt, out, lse, s.nb, s.Nv, kmax, sl2,
+                                                                              kQkLimit / fmaxf(scale, 1.f), groups, per);
+    };
+    if (s.d == 128) go(std::integral_constant<int, 128>{});
+    else go(std::integral_constant<int, 64>{});
+    return hipGetLastError();
+  }
   if (s.d == 128) few ? launch(std::integral_constant<int, 128>{}, I2{}) : launch(std::integral_constant<int, 128>{}, I1{});
   else few ? launch(std::integral_constant<int, 64>{}, I2{}) : launch(std::integral_constant<int, 64>{}, I1{});
   return hipGetLastError();

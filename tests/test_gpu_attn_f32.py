@@ -90,3 +90,32 @@ def test_f32_attention_special_values(usv, d, tail, what, Hh):
                     err[:, 5] = 0
                 # (values of 1e-36 leave results a few of whose last bits lie under the fp32 normal range)
                 assert (err <= 1e-5 * scale + 2.0 ** -126 * 1e-5 + 2.0 ** -149).all(), (what, h, i, (err / np.maximum(scale, 1e-45)).max())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hh,nb", [(1, 1), (3, 21), (2, 32), (5, 13)])  # 1, 63, 64 query blocks: sixteen rows to a workgroup; 65: a block
+@pytest.mark.parametrize("kmax", [1, 2, 4, 5, 13])  # halves of blocks for eight waves: fewer, just as many, one more round, several
+def test_f32_attention_few_blocks(usv, d, Hh, nb, kmax):
+    """Both sides of the rule for few query blocks against a 64-bit evaluation: ragged lists, empty ones, a partial last block."""
+    kmax, Nv = min(kmax, nb), nb * 64 - 37
+    rng = np.random.default_rng(nb * 100 + kmax)
+    Q, K, V = (rng.standard_normal((1, Hh, nb * 64, d), dtype=np.float32) for _ in range(3))
+    cnt = rng.integers(0, kmax + 1, size=(1, Hh, nb)).astype(np.int32)
+    idx = np.sort(np.argsort(rng.random((1, Hh, nb, nb)), axis=-1)[..., :kmax], axis=-1).astype(np.int32)
+    out, lse = usv.block_sparse_attn(gu.up(Q), gu.up(K), gu.up(V), gu.up(idx), gu.up(cnt), seq_valid=Nv, return_lse=True)
+    o, l = gu.down(out), gu.down(lse)
+    for h in range(Hh):
+        for i in range(nb):
+            rows = min(64, Nv - i * 64)
+            keys = [np.arange(j * 64, min(j * 64 + 64, Nv)) for j in idx[0, h, i, :cnt[0, h, i]]]
+            keys = np.concatenate(keys) if keys else np.zeros(0, int)
+            assert (o[0, h, i * 64 + rows:(i + 1) * 64] == 0).all() and np.isneginf(l[0, h, i * 64 + rows:(i + 1) * 64]).all()
+            got, got_l = o[0, h, i * 64:i * 64 + rows], l[0, h, i * 64:i * 64 + rows]
+            if not len(keys):
+                assert (got == 0).all() and np.isneginf(got_l).all()
+                continue
+            S = Q[0, h, i * 64:i * 64 + rows].astype(np.float64) @ K[0, h, keys].astype(np.float64).T / np.sqrt(d)
+            m = S.max(axis=1, keepdims=True)
+            P = np.exp(S - m)
+            gu.assert_f32_close(got, P @ V[0, h, keys].astype(np.float64) / P.sum(axis=1, keepdims=True), f"head {h} block {i}")
+            assert np.abs(got_l - (m[:, 0] + np.log(P.sum(axis=1)))).max() <= 1e-4
