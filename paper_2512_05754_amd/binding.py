@@ -7,6 +7,7 @@ There is no CPU fallback: a missing library or a CPU tensor raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
 import os
 import sys
 import types
@@ -92,11 +93,31 @@ def lib_path() -> str:
 
 
 _lib = None
+_calls = None  # the marshalling extension, once the library is loaded
+
+
+def calls_path() -> str:
+    """The marshalling extension; it is built against one torch and one interpreter, so their versions are in its name."""
+    return os.path.join(PKG_DIR, f"_calls-{torch.__version__}{importlib.machinery.EXTENSION_SUFFIXES[0]}")
+
+
+def _load_calls(L):
+    """csrc/usv_calls.cpp as built for this torch and interpreter, bound to the functions of L; None where there is none (the functions
+    here then marshal through ctypes, as they do for every call that the extension does not know)."""
+    path = calls_path()
+    if not os.path.exists(path):
+        return None
+    loader = importlib.machinery.ExtensionFileLoader("_calls", path)
+    calls = loader.create_module(importlib.machinery.ModuleSpec("_calls", loader, origin=path))
+    loader.exec_module(calls)
+    calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        L.usv_block_scores, L.usv_select_topk_ex, L.usv_attn_work_order, L.usv_block_sparse_attn, L.usv_block_sparse_attn_ordered)))
+    return calls
 
 
 def lib() -> ctypes.CDLL:
     """Loads libusv.so (building it first only if it has never been built)."""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
     path = lib_path()
@@ -149,7 +170,7 @@ def lib() -> ctypes.CDLL:
     L.usv_block_sparse_attn_raster_fused.argtypes = [vp, vp, vp, sp, rp, vp, vp, i32, f32, vp, vp, vp, i32, vp, vp, vp]
     L.usv_status_string.restype, L.usv_status_string.argtypes = ctypes.c_char_p, [i32]
     L.usv_last_error.restype, L.usv_last_error.argtypes = ctypes.c_char_p, []
-    _lib = L
+    _lib, _calls = L, _load_calls(L)
     return L
 
 
@@ -169,7 +190,8 @@ def _dev(t: torch.Tensor, name: str, dtype=None):
     return t.data_ptr()
 
 
-# A small call is a few microseconds of kernels, so the marshalling counts: the argument structs of a shape are built once
+# A small call is a few microseconds of kernels, so the marshalling counts.  The stages of a step on tensors that are all there go through
+# csrc/usv_calls.cpp; for the others the argument structs of a shape are built once
 # (plain values, never written afterwards), and the stream handle is read without building a torch.cuda.Stream (0.2 instead
 # of 3 us).  Together with module attributes that are looked up once: three stages on 1024 tokens 29 -> 19.5 us on the host.
 @lru_cache(maxsize=1024)
@@ -214,6 +236,12 @@ def workspace_bytes(batch, heads, seq_len, seq_valid, head_dim, dtype) -> int:
 
 def block_scores(q, k, seq_valid=None, out=None, workspace=None):
     """usv_block_scores: pooled block scores [B, Hh, nb, nb] fp32 of Q, K [B, Hh, N, d]."""
+    if _calls is not None and out is not None and workspace is not None:
+        status = _calls.block_scores(q, k, seq_valid, out, workspace)
+        if status is not None:
+            if status:
+                _check(status)
+            return out
     sh, shp = _shape_of(q, seq_valid)
     if k.shape != q.shape or k.dtype != q.dtype:
         raise ValueError("k must match q in shape and dtype")
@@ -251,6 +279,12 @@ def select_topk(scores, k=0, seq_valid=None, budgets=None, kmax=None, idx=None, 
     """usv_select_topk(_ex): scores [B, Hh, nb, nb] fp32 -> idx [B, Hh, nb, kmax] int32 (-1 padded), cnt [B, Hh, nb].
 
     force_local: USV_TOPK_FORCE_LOCAL, every row keeps its own cube."""
+    if _calls is not None and idx is not None and cnt is not None:
+        status = _calls.select_topk(scores, k, seq_valid, budgets, kmax, idx, cnt, force_local)
+        if status is not None:
+            if status:
+                _check(status)
+            return idx, cnt
     if scores.dim() != 4 or scores.shape[2] != scores.shape[3]:
         raise ValueError("scores must be [B, Hh, nb, nb]")
     B, Hh, nb, _ = scores.shape
@@ -275,6 +309,12 @@ def select_topk(scores, k=0, seq_valid=None, budgets=None, kmax=None, idx=None, 
 def attn_work_order(cnt, kmax, idx=None, out=None):
     """usv_attn_work_order: per head, the query blocks sorted by (list length descending, where the list lies
     [needs idx], block index) -> int32 [B, Hh, nb]."""
+    if _calls is not None and out is not None:
+        status = _calls.attn_work_order(cnt, kmax, idx, out)
+        if status is not None:
+            if status:
+                _check(status)
+            return out
     B, Hh, nb = cnt.shape
     shp = _shape(B, Hh, nb * BLOCK, nb * BLOCK, 0, USV_F32)[1]
     if out is None:
@@ -293,6 +333,12 @@ def block_sparse_attn(q, k, v, idx, cnt, seq_valid=None, scale=0.0, out=None, ls
     out_dtype: dtype of the result; defaults to q's dtype, torch.float32 is also allowed for bf16 inputs.
     coarse (+ optional gates): usv_block_sparse_attn_fused, out = gate_fine * attention + gate_coarse * coarse[cube].
     work_order (from attn_work_order): usv_block_sparse_attn_ordered, the launch walks the query blocks in that order."""
+    if _calls is not None and out is not None and not return_lse and coarse is None and gate_fine is None and gate_coarse is None:
+        status = _calls.block_sparse_attn(q, k, v, idx, cnt, seq_valid, scale, out, lse, work_order)
+        if status is not None:
+            if status:
+                _check(status)
+            return out
     sh, shp = _shape_of(q, seq_valid)
     for name, t in (("k", k), ("v", v)):
         if t.shape != q.shape or t.dtype != q.dtype:

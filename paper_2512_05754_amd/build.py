@@ -46,6 +46,31 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
     return LIB_PATH
 
 
+def build_calls(verbose: bool = True) -> str:
+    """Compiles csrc/usv_calls.cpp (host code only) against the installed torch."""
+    import sysconfig
+
+    import torch
+
+    from .binding import calls_path
+
+    t = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    out = calls_path()
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(t, "include"), "-I", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(rocm, "include"), os.path.join(CSRC, "usv_calls.cpp"), "-o", out + ".tmp",
+           "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout + res.stderr)
+    os.replace(out + ".tmp", out)
+    return out
+
+
 TOOLS_DIR = os.path.join(PKG_DIR, "tools")
 PEAK_TOOL = os.path.join(TOOLS_DIR, "mfma_peak")
 
@@ -83,5 +108,6 @@ def build_demo(verbose: bool = True) -> str:
 
 if __name__ == "__main__":
     print(build_library(extra_flags=tuple(sys.argv[1:])))
+    print(build_calls())
     print(build_tools())
     print(build_demo())
