@@ -478,11 +478,11 @@ usv_status usv_merge_similarity(const void* k, const usv_shape* shape, const usv
  * src_of : [B, N - r] int32 (device, written): the raster index of the token that
  *          owns each merged row
  * ws     : NULL, or device scratch of at least usv_merge_plan_workspace_bytes
- *          bytes (contents on return unspecified).  Without it one workgroup per
- *          batch element does the whole selection (fine for a few thousand
- *          tokens); with it the selection is a radix select spread over the chip
- *          (five short launches), which is what video-sized grids want.  The
- *          result is the same, bit for bit. */
+ *          bytes (contents on return unspecified).  It is used beyond 16384 tokens,
+ *          where the selection is then a radix select shared out over the chip (five
+ *          short launches); up to there, and without it, every workgroup of one launch
+ *          looks through all keys (beyond 81920 tokens without it: one workgroup per
+ *          batch element).  The result is the same, bit for bit. */
 size_t usv_merge_plan_workspace_bytes(const usv_shape* shape, const usv_grid* grid);
 usv_status usv_merge_plan(const float* u, const int32_t* blk, const usv_shape* shape,
                           const usv_grid* grid, int32_t* row_of, int32_t* src_of,

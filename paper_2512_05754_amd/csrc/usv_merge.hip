@@ -7,9 +7,11 @@
 //   merge_similarity   u[b,i] = cos(m_i, m_dst(i)); -inf at destinations; also blk[i], the rank of
 //                      token i's block among the destinations (bit 31 marks the destination)
 //   merge_similarity_2x2x2  both in one for 2x2x2 merge blocks
-//   merge_select       one workgroup per batch element: bit-by-bit search for the r-th largest
-//                      source key (keys in registers), then one ordered sweep that ranks ties by
-//                      index and assigns the rows of the merged sequence (scans, no atomics)
+//   merge_select_spread  the r largest source keys, ties by index, and the rows of the merged sequence: one launch whose
+//                      workgroups all find the threshold and assign 2048 tokens each
+//   rs_*               the same in five launches that share the keys out (large token counts, with a workspace)
+//   merge_select       the same in one workgroup per batch element (beyond 81920 tokens, without a workspace): bit-by-bit
+//                      search, then one ordered sweep (scans, no atomics)
 //   merge_rows         merged features: a destination row is the mean of itself and its merged
 //                      sources (found by scanning its own block), other rows are copies
 //   unmerge_rows       gather: token k reads row row_of[k]
@@ -329,22 +331,18 @@ __device__ __forceinline__ void block_exclusive_chunks(int (&v)[CH], int* wave_t
 // Keys: 0 = not a source (destination or past the end), sources >= 1 (a NaN similarity, the lowest
 // rank, maps to 1; every number maps above 0x007fffff).  The r-th largest key is found bit by bit
 // from the top; r <= number of sources keeps the key-0 entries out of the result.
-// CH > 0: all keys of up to 4096 * CH tokens stay in registers.  CH == 0: any N, keys are re-read
-// from memory in every pass.
-template <int CH>
+// For token counts beyond what merge_select_spread takes: keys are re-read from memory in every pass.
 __global__ __launch_bounds__(kSelThreads) void merge_select(const float* __restrict__ u, const int32_t* __restrict__ blk,
                                                             int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
                                                             int N, int n_dst, int r) {
-  constexpr bool kReg = CH > 0;
-  constexpr int C = kReg ? CH : 1;
   __shared__ int wave_cnt[2][kSelWaves];
-  __shared__ int wave_tot[C * kSelWaves + 1];
+  __shared__ int wave_tot[kSelWaves + 1];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* ub = u + (long long)b * N;
   int32_t* rob = row_of + (long long)b * N;
   int32_t* sob = src_of + (long long)b * (N - r);
   const int n_unmerged = N - n_dst - r;
-  const int chunks = kReg ? CH : (N + 4 * kSelThreads - 1) / (4 * kSelThreads);
+  const int chunks = (N + 4 * kSelThreads - 1) / (4 * kSelThreads);
   const bool vec_ok = (N & 3) == 0;  // then every batch element's row of u, blk, row_of is 16-byte aligned
 
   auto load_keys = [&](int c, uint32_t (&key)[4], int (&bk)[4]) {
@@ -368,27 +366,16 @@ __global__ __launch_bounds__(kSelThreads) void merge_select(const float* __restr
     }
   };
 
-  uint32_t key[C][4];
-  int bk[4];  // the partition words are only needed again at the very end: re-read there rather than kept
-  if (kReg) {
-#pragma unroll
-    for (int c = 0; c < C; ++c) load_keys(c, key[c], bk);
-  }
+  uint32_t key[4];
+  int bk[4];
 
   // count of keys >= cand over the workgroup; `buf` alternates so that one barrier per call is enough
   auto count_ge = [&](uint32_t cand, int buf) {
     int n = 0;
-    if (kReg) {
+    for (int c = 0; c < chunks; ++c) {
+      load_keys(c, key, bk);
 #pragma unroll
-      for (int c = 0; c < C; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) n += key[c][e] >= cand ? 1 : 0;
-    } else {
-      for (int c = 0; c < chunks; ++c) {
-        load_keys(c, key[0], bk);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) n += key[0][e] >= cand ? 1 : 0;
-      }
+      for (int e = 0; e < 4; ++e) n += key[e] >= cand ? 1 : 0;
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o);
@@ -421,64 +408,43 @@ __global__ __launch_bounds__(kSelThreads) void merge_select(const float* __restr
     __syncthreads();
   }
 
-  // ordered sweep.  Register version: all chunks at once (two scans in all); otherwise chunk by chunk.
+  // ordered sweep, chunk by chunk
   int eq_carry = 0, un_carry = 0;
-  for (int c0 = 0; c0 < chunks; c0 += C) {  // one trip when kReg
-    if (!kReg) load_keys(c0, key[0], bk);
-    int rank[C];
+  for (int c = 0; c < chunks; ++c) {
+    load_keys(c, key, bk);
+    int rank[1] = {0};
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      rank[c] = 0;
+    for (int e = 0; e < 4; ++e) rank[0] += key[e] == thr ? 1 : 0;
+    block_exclusive_chunks<1>(rank, wave_tot, &eq_carry);
+    int eq_rank = rank[0], un = 0;
+    unsigned merged_bits = 0u;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) rank[c] += key[c][e] == thr ? 1 : 0;
+    for (int e = 0; e < 4; ++e) {
+      const bool eq = key[e] == thr;
+      const bool merged = key[e] != 0u && (key[e] > thr || (eq && eq_rank < need_eq));
+      eq_rank += eq ? 1 : 0;
+      un += (key[e] != 0u && !merged) ? 1 : 0;
+      merged_bits |= merged ? 1u << e : 0u;
     }
-    block_exclusive_chunks<C>(rank, wave_tot, &eq_carry);
-    unsigned merged_bits[C];
+    rank[0] = un;
+    block_exclusive_chunks<1>(rank, wave_tot, &un_carry);
+    const int i0 = (c * kSelThreads + tid) * 4;
+    if (i0 >= N) continue;
+    int un_rank = rank[0];
+    int row[4];
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      int eq_rank = rank[c], un = 0;
-      merged_bits[c] = 0u;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool eq = key[c][e] == thr;
-        const bool merged = key[c][e] != 0u && (key[c][e] > thr || (eq && eq_rank < need_eq));
-        eq_rank += eq ? 1 : 0;
-        un += (key[c][e] != 0u && !merged) ? 1 : 0;
-        merged_bits[c] |= merged ? 1u << e : 0u;
-      }
-      rank[c] = un;
+    for (int e = 0; e < 4; ++e) {
+      const bool merged = (merged_bits >> e) & 1u;
+      // a destination's row, and the row a merged source reads back: the block's rank among the destinations
+      row[e] = (key[e] == 0u || merged) ? n_unmerged + (bk[e] & 0x7fffffff) : un_rank++;
+      if (i0 + e < N && !merged) sob[row[e]] = i0 + e;
     }
-    block_exclusive_chunks<C>(rank, wave_tot, &un_carry);
+    if (vec_ok && i0 + 3 < N) {
+      *reinterpret_cast<int4*>(rob + i0) = make_int4(row[0], row[1], row[2], row[3]);
+    } else {
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const int i0 = ((c0 + c) * kSelThreads + tid) * 4;
-      if (i0 >= N) continue;
-      if (kReg) {
-        if (vec_ok && i0 + 3 < N) {
-          const int4 k4 = *reinterpret_cast<const int4*>(blk + i0);
-          bk[0] = k4.x; bk[1] = k4.y; bk[2] = k4.z; bk[3] = k4.w;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (i0 + e < N) bk[e] = blk[i0 + e];
-        }
-      }
-      int un_rank = rank[c];
-      int row[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool merged = (merged_bits[c] >> e) & 1u;
-        // a destination's row, and the row a merged source reads back: the block's rank among the destinations
-        row[e] = (key[c][e] == 0u || merged) ? n_unmerged + (bk[e] & 0x7fffffff) : un_rank++;
-        if (i0 + e < N && !merged) sob[row[e]] = i0 + e;
-      }
-      if (vec_ok && i0 + 3 < N) {
-        *reinterpret_cast<int4*>(rob + i0) = make_int4(row[0], row[1], row[2], row[3]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (i0 + e < N) rob[i0 + e] = row[e];
-      }
+      for (int e = 0; e < 4; ++e)
+        if (i0 + e < N) rob[i0 + e] = row[e];
     }
   }
 }
@@ -750,6 +716,202 @@ __global__ __launch_bounds__(kRsThreads) void rs_assign(const float* __restrict_
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The same in one launch, for up to 81920 tokens: every workgroup finds the threshold by itself, from all keys of its batch element
+// in its registers (all of u and blk come out of the L2), and assigns the rows of its own 2048 tokens.  Nothing is exchanged
+// between workgroups and nothing is waited for; what each of them repeats takes as long once as sixteen times.
+//
+// Finding the r-th largest key: 4096 bins over [smallest, largest] key (a similarity's keys lie in a small part of the 32-bit
+// range, so bins over their own range spread them out: the LDS additions rarely meet, and the bin in question holds a handful of
+// keys, which are then ranked one against the other).  A bin that holds more than kSpList keys is divided again; twelve bits a
+// time, so at most three times.
+//
+// Bound by the instructions that every workgroup spends on every key (about thirty: 2.9 us per 8192 keys); times at the launcher's rule.
+constexpr int kSpThreads = 1024, kSpWaves = kSpThreads / 64, kSpBins = 4096, kSpSlice = 2 * kSpThreads, kSpList = 256;
+
+// Exclusive prefix of one int per thread over the workgroup.  `lds` holds kSpWaves ints; one barrier (the caller's next use of the
+// same array needs another in between: alternate two).
+__device__ __forceinline__ int sp_exclusive(int v, int* lds, int* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int inc = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(inc, o);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) lds[wave] = inc;
+  __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kSpWaves; ++w) {
+    before += w < wave ? lds[w] : 0;
+    all += lds[w];
+  }
+  *total = all;
+  return before + inc - v;
+}
+
+// grid = (ceil(N / kSpSlice), B).  CH: chunks of 8 * 1024 tokens, thread t of chunk c owns tokens 8 (1024 c + t) .. + 7.
+template <int CH>
+__global__ __launch_bounds__(kSpThreads) void merge_select_spread(const float* __restrict__ u, const int32_t* __restrict__ blk,
+                                                                  int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
+                                                                  int N, int n_dst, int r) {
+  __shared__ int h[kSpBins];
+  __shared__ int scan_a[kSpWaves], scan_b[kSpWaves], scan_c[kSpWaves], scan_d[kSpWaves];
+  __shared__ uint32_t low[kSpWaves], high[kSpWaves], cand[kSpList];
+  __shared__ uint32_t picked_key;
+  __shared__ int picked_bin, picked_rank, picked_count, n_cand;
+  const int b = blockIdx.y, g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float* ub = u + (long long)b * N;
+  uint32_t key[CH][kRsPer];
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    int bk[kRsPer];
+    rs_load(ub, blk, N, (c * kSpThreads + tid) * kRsPer, key[c], bk);
+  }
+  // this thread's two tokens of the slice
+  const int i0 = g * kSpSlice + 2 * tid;
+  uint32_t mine[2];
+  int bk[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const bool in = i0 + e < N;
+    bk[e] = in ? blk[i0 + e] : (int)0x80000000;
+    const uint32_t x = order_key(in ? ub[i0 + e] : 0.f);
+    mine[e] = bk[e] >= 0 ? (x ? x : 1u) : 0u;
+  }
+
+  uint32_t thr = 0xffffffffu;  // r == 0: nothing is merged (no key is that large)
+  int need_eq = 0;
+  if (r > 0) {  // uniform
+    uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int e = 0; e < kRsPer; ++e) lo = min(lo, key[c][e] - 1u), hi = max(hi, key[c][e]);  // (0 - 1 is the largest)
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) lo = min(lo, (uint32_t)__shfl_xor((int)lo, o)), hi = max(hi, (uint32_t)__shfl_xor((int)hi, o));
+    if (lane == 0) low[wave] = lo, high[wave] = hi;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSpWaves; ++w) lo = min(lo, low[w]), hi = max(hi, high[w]);
+    lo += 1u;  // (no source at all: lo = 0, hi = 0)
+    int rank = r;
+    for (int level = 0; level < 3; ++level) {  // at most: 20, 8, 0 bits are left
+      const uint32_t width = hi - lo;
+      const int shift = width < (uint32_t)kSpBins ? 0 : 20 - __clz((int)width);
+#pragma unroll
+      for (int k = 0; k < kSpBins / kSpThreads; ++k) h[k * kSpThreads + tid] = 0;
+      if (tid == 0) picked_bin = 0, picked_rank = 0, picked_count = 0, n_cand = 0;
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int e = 0; e < kRsPer; ++e) {
+          const bool in = key[c][e] != 0u && key[c][e] >= lo && key[c][e] <= hi;
+          const int bin = (int)((key[c][e] - lo) >> shift);
+          const unsigned long long all = __ballot(in);
+          if (all == 0) continue;
+          // (ties: a wave whose keys all fall into one bin adds them at once)
+          const int first = __builtin_amdgcn_readlane(bin, __ffsll(all) - 1);
+          if (__ballot(in && bin == first) == all) {
+            if (lane == 0) atomicAdd(&h[first], __popcll(all));
+          } else if (in) {
+            atomicAdd(&h[bin], 1);
+          }
+        }
+      __syncthreads();
+      {  // the bin that holds the rank-th largest: thread t owns four, highest first
+        constexpr int P = kSpBins / kSpThreads;
+        const int top = kSpBins - 1 - tid * P;
+        int own = 0, total;
+#pragma unroll
+        for (int p = 0; p < P; ++p) own += h[top - p];
+        int above = sp_exclusive(own, level & 1 ? scan_b : scan_a, &total);
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+          const int n = h[top - p];
+          if (above < rank && rank <= above + n) picked_bin = top - p, picked_rank = rank - above, picked_count = n;
+          above += n;
+        }
+      }
+      __syncthreads();
+      const int count = picked_count;
+      lo += (uint32_t)picked_bin << shift;
+      const uint32_t span = (1u << shift) - 1u;
+      hi = hi - lo < span ? hi : lo + span;
+      rank = picked_rank;
+      if (count == 0) {  // r beyond the sources (a partition that is not this grid's): all of them
+        lo = 0u, rank = 0, hi = 0u;
+        break;
+      }
+      if (shift == 0) break;
+      if (count <= kSpList) {
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+          for (int e = 0; e < kRsPer; ++e)
+            if (key[c][e] != 0u && key[c][e] >= lo && key[c][e] <= hi) cand[min(atomicAdd(&n_cand, 1), kSpList - 1)] = key[c][e];
+        __syncthreads();
+        if (tid < count) {
+          const uint32_t k = cand[tid];
+          int gt = 0, ge = 0;
+          for (int t = 0; t < count; ++t) gt += cand[t] > k ? 1 : 0, ge += cand[t] >= k ? 1 : 0;
+          if (gt < rank && rank <= ge) picked_key = k, picked_rank = rank - gt;  // (equal keys write the same)
+        }
+        __syncthreads();
+        lo = picked_key;
+        rank = picked_rank;
+        break;
+      }
+      __syncthreads();  // everyone has read what was picked
+    }
+    thr = lo;
+    need_eq = rank;
+  }
+
+  // ties and lower keys in the slices before this one
+  int eq = 0, lt = 0;
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+    if (c * kSpThreads + tid < g * (kSpSlice / kRsPer)) {
+#pragma unroll
+      for (int e = 0; e < kRsPer; ++e) eq += key[c][e] == thr ? 1 : 0, lt += (key[c][e] != 0u && key[c][e] < thr) ? 1 : 0;
+    }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) eq += __shfl_xor(eq, o), lt += __shfl_xor(lt, o);
+  if (lane == 0) scan_c[wave] = eq, scan_d[wave] = lt;
+  __syncthreads();
+  int eq_before = 0, lt_before = 0;
+#pragma unroll
+  for (int w = 0; w < kSpWaves; ++w) eq_before += scan_c[w], lt_before += scan_d[w];
+  const int un_before = lt_before + max(0, eq_before - need_eq);  // ties beyond the first need_eq stay unmerged
+  __syncthreads();  // (scan_a and scan_b are free since the search, scan_c and scan_d from here on)
+
+  int unused;
+  int eq_rank = eq_before + sp_exclusive((mine[0] == thr ? 1 : 0) + (mine[1] == thr ? 1 : 0), scan_c, &unused);
+  bool merged[2];
+  int un = 0;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const bool is_eq = mine[e] == thr;
+    merged[e] = mine[e] != 0u && (mine[e] > thr || (is_eq && eq_rank < need_eq));
+    eq_rank += is_eq ? 1 : 0;
+    un += (mine[e] != 0u && !merged[e]) ? 1 : 0;
+  }
+  int un_rank = un_before + sp_exclusive(un, scan_d, &unused);
+  const int n_unmerged = N - n_dst - r;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    if (i0 + e >= N) break;
+    // a destination's row, and the row a merged source reads back: the block's rank among the destinations
+    const int row = (mine[e] == 0u || merged[e]) ? n_unmerged + (bk[e] & 0x7fffffff) : un_rank++;
+    row_of[(long long)b * N + i0 + e] = row;
+    // (the bound holds by construction; it keeps a partition array that does not belong to this grid from writing past src_of)
+    if (!merged[e] && (unsigned)row < (unsigned)(N - r)) src_of[(long long)b * (N - r) + row] = i0 + e;
+  }
+}
+
 // grid = (dst_wgs + copy_wgs, Hh, B).  Nm = N - r valid merged rows, of which the last nT * nH * nW are the
 // destinations in ascending raster order and the others copies of token src_of[p]; rows Nm <= p < Np are padding.
 // A group of D / VEC lanes owns a row piece by piece (16 bytes per lane, kept as raw chunks while in flight).
@@ -927,6 +1089,18 @@ size_t merge_plan_workspace_bytes(int B, int N) {
 hipError_t launch_merge_select(const float* u, const int32_t* blk, const MergeGrid& g, int B, int N, int r, int32_t* row_of,
                                int32_t* src_of, void* ws, hipStream_t st) {
   const int n_dst = g.nT * g.nH * g.nW;
+  // One launch whose workgroups each look through all keys, or five that share them out.  With a workspace, spread / five launches, distinct similarities
+  // (18 distinct ones): 1105 x 2 tokens 9.1 / 26.6 us (12.6 / 26.5), 3510 11.3 / 30.4 (16.0 / 30.7), 17589 30.4 / 31.5 (42.7 / 31.9), 32760 21.7 / 23.7 (41.1 /
+  // 24.1), 75600 41.7 / 25.7.  Without one, against one workgroup per batch element: 32760 21.7 / 36.1, 75600 41.6 / 123.
+  constexpr int kChunk = kSpThreads * kRsPer;  // (keys of ten chunks fit a workgroup's registers)
+  if (N <= (ws ? 2 : 10) * kChunk) {
+    const dim3 grid((unsigned)((N + kSpSlice - 1) / kSpSlice), (unsigned)B);
+    if (N <= kChunk) merge_select_spread<1><<<grid, kSpThreads, 0, st>>>(u, blk, row_of, src_of, N, n_dst, r);
+    else if (N <= 2 * kChunk) merge_select_spread<2><<<grid, kSpThreads, 0, st>>>(u, blk, row_of, src_of, N, n_dst, r);
+    else if (N <= 4 * kChunk) merge_select_spread<4><<<grid, kSpThreads, 0, st>>>(u, blk, row_of, src_of, N, n_dst, r);
+    else merge_select_spread<10><<<grid, kSpThreads, 0, st>>>(u, blk, row_of, src_of, N, n_dst, r);
+    return hipGetLastError();
+  }
   if (ws) {
     const unsigned G = (unsigned)((N + kRsSlice - 1) / kRsSlice);
     RadixWs w;
@@ -945,12 +1119,7 @@ hipError_t launch_merge_select(const float* u, const int32_t* blk, const MergeGr
     rs_assign<<<grid, kRsThreads, 0, st>>>(u, blk, row_of, src_of, N, n_dst, r, w);
     return hipGetLastError();
   }
-  if (N <= kSelThreads * 4 * 8)
-    merge_select<8><<<(unsigned)B, kSelThreads, 0, st>>>(u, blk, row_of, src_of, N, n_dst, r);
-  else if (N <= kSelThreads * 4 * 20)
-    merge_select<20><<<(unsigned)B, kSelThreads, 0, st>>>(u, blk, row_of, src_of, N, n_dst, r);
-  else
-    merge_select<0><<<(unsigned)B, kSelThreads, 0, st>>>(u, blk, row_of, src_of, N, n_dst, r);
+  merge_select<<<(unsigned)B, kSelThreads, 0, st>>>(u, blk, row_of, src_of, N, n_dst, r);
   return hipGetLastError();
 }
 

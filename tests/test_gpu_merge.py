@@ -204,3 +204,27 @@ def test_similarity_of_2x2x2_blocks(usv, grid, d, dtype, Hh):
     assert np.array_equal(gu.down(blk), expected_blk(grid, (2, 2, 2)))
     ref = orc.merge_similarity(synth.as_f32(K), grid, (2, 2, 2))
     gu.assert_f32_close(gu.down(u), ref, f"{grid} d={d} {dtype} heads={Hh}")
+
+
+@pytest.mark.parametrize("grid,mb", [((1, 1, 2), (1, 1, 2)), ((1, 32, 64), (1, 2, 2)), ((1, 3, 683), (1, 1, 4)), ((2, 64, 64), (2, 2, 2)), ((1, 89, 93), (1, 4, 4)),
+                                     ((4, 64, 64), (2, 2, 2)), ((1, 129, 128), (1, 2, 2)), ((2, 127, 129), (2, 2, 2)), ((5, 128, 128), (1, 2, 2))], ids=str)
+@pytest.mark.parametrize("values", ["distinct", "narrow", "few", "wide"])
+def test_merge_plan_at_the_edges_of_its_kernels(usv, grid, mb, values):
+    """Token counts around a slice (2048) and around 8192, 16384, 32768 and 81920; keys that fall apart at the first level, that need all three,
+    ties past the list a bin may hold; two batch elements."""
+    N = grid[0] * grid[1] * grid[2]
+    rng = np.random.default_rng([11, N])
+    dst = orc.merge_partition(grid, mb)
+    u = rng.uniform(-1, 1, size=(2, N)).astype(np.float32)
+    if values == "narrow":  # one wide outlier and the rest within a few hundred neighbouring floats
+        u[:] = np.float32(0.75) + rng.integers(0, 300, size=(2, N)) * np.float32(2.0 ** -24)
+        u[:, N // 2] = -1
+    if values == "few": u = np.round(u * 3).astype(np.float32) / 3
+    if values == "wide": u = (u * 10.0 ** rng.integers(-38, 38, size=(2, N))).astype(np.float32)
+    u[:, dst == np.arange(N)] = -np.inf
+    n_src = int((dst != np.arange(N)).sum())
+    for r in sorted({0, 1, n_src // 2, n_src - 1, n_src} & set(range(n_src + 1))):
+        row_of, src_of = both_plans(usv, gu.up(u), gu.up(expected_blk(grid, mb)), grid, mb, r)
+        rr, rs = orc.merge_plan(u, grid, mb, r)
+        np.testing.assert_array_equal(row_of.cpu().numpy(), rr)
+        np.testing.assert_array_equal(src_of.cpu().numpy(), rs)
