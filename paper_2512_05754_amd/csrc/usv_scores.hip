@@ -2,9 +2,9 @@
 // paper Sections 2.2 and 3.2).  Two kernels:
 //   pool_means   HBM-bound: reads Q and K once with 16-byte coalesced loads, reduces each
 //                64-token cube to its fp32 mean over the valid tokens.
-//   score_gemm   S = Qm Km^T / sqrt(d) per head on the fp32 matrix cores (fp32 operands and
-//                accumulation: the scores keep fp32 accuracy; bf16 MFMA would not).
-#include "usv_internal.h"
+//   score_gemm   S = Qm Km^T / sqrt(d) per head to fp32 accuracy: operands in three bf16 parts each, on the
+//                bf16 matrix cores (usv_attn_f32.hip says how; where a split does not carry the operands, fp32 ones).
+#include "usv_split.h"
 
 namespace usv {
 namespace {
@@ -93,59 +93,47 @@ __global__ __launch_bounds__(kPoolThreads) void pool_means(const T* __restrict__
   }
 }
 
-// S[bh, i, j] = sum_c Qm[bh,i,c] Km[bh,j,c] * rsqrt_d on the fp32 matrix cores
-// (v_mfma_f32_32x32x2_f32: fp32 operands and accumulation, so the scores keep fp32 accuracy).
-// 64x64 output tile per workgroup, one 32x32 quadrant per wave; the pooled means are staged in LDS
+// S[bh, i, j] = sum_c Qm[bh,i,c] Km[bh,j,c] * rsqrt_d.  64x64 output tile per workgroup, one 32x32 quadrant per wave.
+//
+// A tile with fp32 operands on the fp32 matrix cores (v_mfma_f32_32x32x2_f32): the pooled means are staged in LDS
 // 64 channels at a time.  An MFMA step contracts 2 channels, one per 32-lane half; which channels a
 // step takes is free as long as both operands agree, so half g takes channels 32 g + t at step t
 // and every lane reads its operands as contiguous 16-byte pieces.
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-
+// For operands that three bf16 parts do not carry: infinities, and values so large that what a part loses beside them shows.
+constexpr int kTileLd = 64 + 4;  // row stride in floats: 16-byte reads of 32 consecutive rows spread over the banks
 template <int D>
-__global__ __launch_bounds__(256) void score_gemm(const float* __restrict__ qm, const float* __restrict__ km,
-                                                  float* __restrict__ scores, int nb, int nb_valid,
-                                                  float rsqrt_d) {
-  constexpr int KC = 64;        // channels staged per pass
-  constexpr int LD = KC + 4;    // row stride in floats: 16-byte reads of 32 consecutive rows spread over the banks
-  __shared__ __attribute__((aligned(16))) float As[64 * LD];
-  __shared__ __attribute__((aligned(16))) float Bs[64 * LD];
-  const int bh = blockIdx.z;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  const float* qbase = qm + (long long)bh * nb * D;
-  const float* kbase = km + (long long)bh * nb * D;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+__device__ __forceinline__ void fp32_tile(float* As, float* Bs, const float* __restrict__ qbase, const float* __restrict__ kbase,
+                                          float* __restrict__ out, int i0, int j0, int nb, int nb_valid, float rsqrt_d) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;  // this wave's quadrant
   const int r = lane & 31, g = lane >> 5;
   f32x16 acc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.f;
   // each thread stages 4 + 4 float4 per pass; the next pass's loads are issued before this pass's MFMAs
-  constexpr int PER = 64 * (KC / 4) / 256;
-  float4 ra[PER], rb[PER];
+  float4 ra[4], rb[4];
   auto fetch = [&](int kc) {
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int e = tid + u * 256, row = e / (KC / 4), c = (e % (KC / 4)) * 4;
-      ra[u] = make_float4(0.f, 0.f, 0.f, 0.f);  // zero rows beyond nb
-      rb[u] = ra[u];
+    for (int u = 0; u < 4; ++u) {
+      const int e = tid + u * 256, row = e / 16, c = (e % 16) * 4;
+      ra[u] = rb[u] = make_float4(0.f, 0.f, 0.f, 0.f);  // zero rows beyond nb
       if (i0 + row < nb) ra[u] = *reinterpret_cast<const float4*>(qbase + (long long)(i0 + row) * D + kc + c);
       if (j0 + row < nb) rb[u] = *reinterpret_cast<const float4*>(kbase + (long long)(j0 + row) * D + kc + c);
     }
   };
   fetch(0);
-  for (int kc = 0; kc < D; kc += KC) {
+  for (int kc = 0; kc < D; kc += 64) {
     if (kc) __syncthreads();
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int e = tid + u * 256, row = e / (KC / 4), c = (e % (KC / 4)) * 4;
-      *reinterpret_cast<float4*>(As + row * LD + c) = ra[u];
-      *reinterpret_cast<float4*>(Bs + row * LD + c) = rb[u];
+    for (int u = 0; u < 4; ++u) {
+      const int e = tid + u * 256, row = e / 16, c = (e % 16) * 4;
+      *reinterpret_cast<float4*>(As + row * kTileLd + c) = ra[u];
+      *reinterpret_cast<float4*>(Bs + row * kTileLd + c) = rb[u];
     }
     __syncthreads();
-    if (kc + KC < D) fetch(kc + KC);
-    const float* ap = As + (wi + r) * LD + 32 * g;
-    const float* bp = Bs + (wj + r) * LD + 32 * g;
+    if (kc + 64 < D) fetch(kc + 64);
+    const float* ap = As + (wi + r) * kTileLd + 32 * g;
+    const float* bp = Bs + (wj + r) * kTileLd + 32 * g;
 #pragma unroll
     for (int t = 0; t < 32; t += 4) {
       const float4 a = *reinterpret_cast<const float4*>(ap + t);
@@ -157,13 +145,117 @@ __global__ __launch_bounds__(256) void score_gemm(const float* __restrict__ qm, 
     }
   }
   // accumulator register e of lane (r, g): row wi + 8 (e/4) + 4 g + (e%4), column wj + r
-  float* out = scores + (long long)bh * nb * nb;
   const int j = j0 + wj + r;
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
     const int i = i0 + wi + 8 * (e >> 2) + 4 * g + (e & 3);
     if (i < nb && j < nb) out[(long long)i * nb + j] = (i < nb_valid && j < nb_valid) ? acc[e] * rsqrt_d : -INFINITY;
   }
+}
+
+// The products of three bf16 parts on v_mfma_f32_16x16x32_bf16 (lane = (c, G): rows / columns c of the operands, channels 8 G .. + 8), the
+// leading one and the five small ones in sums of their own; parts staged in LDS as planes, 64 channels at a time, the next pass's means
+// fetched meanwhile.  Six products at sixteen times the rate of the fp32 matrix pipe, which the fp32 form was bound by (5.8 of its 14 us at
+// 12 x 512 x 512, 110 of 200 us at 40 x 1182 x 1182).  What is left is the chain of load, split, barrier and product, and the store.
+constexpr float kScoreLimit = 0x1p80f;  // up to here an operand's error of 2^-125 leaves a score off by less than 2^-38
+template <int D>
+__global__ __launch_bounds__(256, 3) void score_gemm(const float* __restrict__ qm, const float* __restrict__ km,
+                                                  float* __restrict__ scores, int nb, int nb_valid,
+                                                  float rsqrt_d, int fp32) {
+  constexpr int KC = 64, kPlane = 64 * KC * 2;  // channels per pass; bytes of one part of 64 rows
+  static_assert(2 * 64 * kTileLd * 4 <= 6 * kPlane, "the fp32 tile's operands overlay the planes");
+  __shared__ __attribute__((aligned(16))) unsigned char smem[6 * kPlane];  // three planes of Q, three of K
+  const int bh = blockIdx.z;
+  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
+  const float* qbase = qm + (long long)bh * nb * D;
+  const float* kbase = km + (long long)bh * nb * D;
+  float* out = scores + (long long)bh * nb * nb;
+  auto with_fp32_operands = [&] {
+    fp32_tile<D>(reinterpret_cast<float*>(smem), reinterpret_cast<float*>(smem) + 64 * kTileLd, qbase, kbase, out, i0, j0, nb, nb_valid, rsqrt_d);
+  };
+  if (fp32) return with_fp32_operands();  // (the launcher's choice, the same for every workgroup)
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;  // this wave's quadrant
+  const int c16 = lane & 15, G = lane >> 4;
+  // a row's eight 16-byte chunks are stored at chunk ^ (row % 8): sixteen rows of a fragment spread over the banks
+  auto at = [](int row, int chunk) { return row * (KC * 2) + ((chunk ^ (row & 7)) << 4); };
+  // thread: two pieces of eight channels of either operand per pass
+  float4 raw[2][2][2];  // [operand][piece][half]
+  auto fetch = [&](int kc) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int e = tid + 256 * u, row = e >> 3, c = (e & 7) * 8;
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        raw[0][u][half] = raw[1][u][half] = make_float4(0.f, 0.f, 0.f, 0.f);  // zero rows beyond nb
+        if (i0 + row < nb) raw[0][u][half] = *reinterpret_cast<const float4*>(qbase + (long long)(i0 + row) * D + kc + c + 4 * half);
+        if (j0 + row < nb) raw[1][u][half] = *reinterpret_cast<const float4*>(kbase + (long long)(j0 + row) * D + kc + c + 4 * half);
+      }
+    }
+  };
+  f32x4 big[2][2], small[2][2];
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) big[mt][nt] = small[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float top = 0.f;  // largest magnitude this thread has split
+  fetch(0);
+  for (int kc = 0; kc < D; kc += KC) {
+    if (kc) __syncthreads();
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int e = tid + 256 * u;
+        float x[8];
+        *reinterpret_cast<float4*>(x) = raw[o][u][0];
+        *reinterpret_cast<float4*>(x + 4) = raw[o][u][1];
+        largest8(top, x);
+        const Split s = split8(x);
+#pragma unroll
+        for (int part = 0; part < 3; ++part)
+          *reinterpret_cast<bf16x8*>(smem + (3 * o + part) * kPlane + at(e >> 3, e & 7)) = s.p[part];
+      }
+    __syncthreads();
+    if (kc + KC < D) fetch(kc + KC);
+#pragma unroll
+    for (int t = 0; t < KC / 32; ++t) {
+      bf16x8 a[2][3], b[2][3];
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int part = 0; part < 3; ++part) {
+          a[x][part] = *reinterpret_cast<const bf16x8*>(smem + part * kPlane + at(wi + 16 * x + c16, 4 * t + G));
+          b[x][part] = *reinterpret_cast<const bf16x8*>(smem + (3 + part) * kPlane + at(wj + 16 * x + c16, 4 * t + G));
+        }
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+          f32x4& s = small[mt][nt];
+          s = mfma(a[mt][2], b[nt][0], s);
+          s = mfma(a[mt][0], b[nt][2], s);
+          s = mfma(a[mt][1], b[nt][1], s);
+          s = mfma(a[mt][1], b[nt][0], s);
+          s = mfma(a[mt][0], b[nt][1], s);
+          big[mt][nt] = mfma(a[mt][0], b[nt][0], big[mt][nt]);
+        }
+    }
+  }
+  if (__syncthreads_or(top >= kScoreLimit)) return with_fp32_operands();  // (a NaN stays a NaN either way)
+  // element r of tile (mt, nt): row wi + 16 mt + 4 G + r, column wj + 16 nt + c16
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+      const int j = j0 + wj + 16 * nt + c16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = i0 + wi + 16 * mt + 4 * G + r;
+        if (i < nb && j < nb)
+          out[(long long)i * nb + j] = (i < nb_valid && j < nb_valid) ? (big[mt][nt][r] + small[mt][nt][r]) * rsqrt_d : -INFINITY;
+      }
+    }
 }
 
 template <typename T, int D>
@@ -180,8 +272,12 @@ hipError_t run(const void* q, const void* k, const Dims& s, float* scores, float
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int tiles = (s.nb + 63) / 64;
+  // Up to two workgroups per CU the splits stand in the way and the fp32 products do not: stage 1 with fp32 operands / in parts, 12 heads x 55 blocks 7.2 /
+  // 7.5 us, 3 x 33 8.2 / 8.8, 24 x 256 44.0 / 43.8; 12 x 512 45.6 / 44.5, 12 x 624 60.6 / 56.2, 40 x 1182 415 / 384.  (Error against 64 bits, 2-norm:
+  // 2.06e-7 / 0.72e-7 at d = 128, 1.46e-7 / 0.5e-7 at d = 64.)
+  const int fp32 = (long long)tiles * tiles * s.bh() <= 512;
   score_gemm<D><<<dim3(tiles, tiles, (unsigned)s.bh()), 256, 0, st>>>(ws, ws + mean_elems, scores, s.nb,
-                                                                         s.nb_valid, 1.0f / sqrtf((float)D));
+                                                                         s.nb_valid, 1.0f / sqrtf((float)D), fp32);
   return hipGetLastError();
 }
 

@@ -532,3 +532,30 @@ def test_work_order_sizes(usv, nb, kmax):
     idx[0, 0, 0, :kmax] = np.sort(rng.choice(nb, size=kmax, replace=False))
     order = gu.down(usv.attn_work_order(gu.up(cnt), kmax, idx=gu.up(idx)))
     np.testing.assert_array_equal(order, expected_work_order(idx, cnt, kmax))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hh,nb", [(2, 1), (2, 33), (2, 64), (57, 130), (129, 65), (513, 64)])  # up to 512 tiles in fp32; more in parts: 513, 516
+@pytest.mark.parametrize("what", ["plain", "huge q, tiny k", "tiny q, huge k", "inf", "nan", "one huge block", "tiny"])
+def test_block_scores_operands_beyond_a_split(usv, d, Hh, nb, what):
+    """The score product takes its operands in three bf16 parts; what these do not carry it multiplies in fp32: scores against a 64-bit
+    evaluation at the fp32 bound, infinities and NaN where that has them."""
+    rng = np.random.default_rng(d + nb)
+    Q, K = (np.resize(rng.standard_normal((1, 2, nb * 64, d), dtype=np.float32), (1, Hh, nb * 64, d)) for _ in range(2))  # (every other head alike)
+    if what == "huge q, tiny k": Q, K = Q * np.float32(2.0 ** 117), K * np.float32(2.0 ** -117)
+    if what == "tiny q, huge k": Q, K = Q * np.float32(2.0 ** -117), K * np.float32(2.0 ** 117)
+    if what == "inf": Q[0, 0, 5, 3], K[0, 1, nb * 64 - 2, d - 1] = np.inf, -np.inf
+    if what == "nan": K[0, 0, 7, 1] = np.nan
+    if what == "one huge block": K[0, 1, -64:] *= np.float32(2.0 ** 110)
+    if what == "tiny": Q, K = Q * np.float32(2.0 ** -70), K * np.float32(2.0 ** -60)
+    got = gu.down(usv.block_scores(gu.up(Q), gu.up(K)))[:, :2].astype(np.float64)
+    with np.errstate(all="ignore"):
+        qm, km = (x.astype(np.float64).reshape(2, nb, 64, d).mean(axis=2) for x in (Q[0, :2], K[0, :2]))
+        terms = np.abs(qm[:, :, None, :] * km[:, None, :, :]).sum(axis=-1)  # what a score sums up
+        ref = (qm[:, :, None, :] * km[:, None, :, :]).sum(axis=-1) / np.sqrt(d)
+        fin = np.isfinite(ref)
+        assert np.array_equal(np.isnan(got[0]), np.isnan(ref)) and np.array_equal(np.isinf(got[0]), np.isinf(ref))
+        assert np.array_equal(got[0][np.isinf(ref)], ref[np.isinf(ref)])
+        # the means' fp32 sums of 64 values and the product's of d: a few 2^-24 each of the terms' sum
+        err = np.abs(np.where(fin, got[0] - ref, 0))
+        assert (err <= np.where(fin, 1e-5 * terms, 0) + 1e-37).all(), (what, (err / np.maximum(terms, 1e-300))[fin].max())
