@@ -644,7 +644,7 @@ __global__ __launch_bounds__(kThreads, WGS) void attn_bf16(const uint16_t* __res
 }
 
 // Which kernel takes a launch.  All times this kernel / wide.  (Raster order plays no part: the raster entry points give the bits that
-// gathered tensors give.  The wide kernel's address arithmetic is the longer one there: 2048 query blocks, 26 listed 152 / 162 us.)
+// gathered tensors give.)
 inline bool wide_is_faster(const AttnBf16Args& a) {
   const Dims& s = a.s;
   const long long total = s.bh() * s.nb;

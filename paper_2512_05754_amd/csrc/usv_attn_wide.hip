@@ -216,8 +216,8 @@ __global__ __launch_bounds__(64 * NW, WPS) void attn_wide(const uint16_t* __rest
   // The workgroups of an XCD that run together share fetched tiles through its L2 as long as their sweeps over the
   // head's keys stay together.  Starting every list at its first entry keeps them together in the first round only: later
   // workgroups start whenever a slot frees, and those times spread from round to round (measured with TURNS at 12 heads, 512 blocks, 51
-  // listed, as a share of one sweep: 0.18 in round 1, 0.28, 0.37, 0.47, 0.54 in round 5; 40 heads of 1182 blocks 0.19 to 0.8
-  // in round 6, where it stays).  So a workgroup starts its sweep where the others can be expected to be at its time.  The
+  // listed, as a share of one sweep: 0.18 at m = 1 (m as below), 0.28, 0.37, 0.47, 0.54 at m = 5; 40 heads of 1182 blocks 0.19 to 0.8
+  // at m = 6, where it stays).  So a workgroup starts its sweep where the others can be expected to be at its time.  The
   // k-th of the sweep_wgs of round m = rank / sweep_wgs starts before or after the round's middle by its share of that
   // spread, and the middles of all rounds meet the same place of the sweep: the list is walked from the first block at or past
   // nb * width(m) * (k / sweep_wgs - 1/2), modulo nb, around the end, back to it.  Without turns the oldest wave of a SIMD runs ahead, the first
