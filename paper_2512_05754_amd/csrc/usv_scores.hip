@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kPoolThreads) void pool_means(const T* __restrict__
 // 64 channels at a time.  An MFMA step contracts 2 channels, one per 32-lane half; which channels a
 // step takes is free as long as both operands agree, so half g takes channels 32 g + t at step t
 // and every lane reads its operands as contiguous 16-byte pieces.
-// For operands that three bf16 parts do not carry: infinities, and values so large that what a part loses beside them shows.
+// For operands that three bf16 parts do not carry: infinities, and values of which a lower part or a part's product runs out of exponent.
 constexpr int kTileLd = 64 + 4;  // row stride in floats: 16-byte reads of 32 consecutive rows spread over the banks
 template <int D>
 __device__ __forceinline__ void fp32_tile(float* As, float* Bs, const float* __restrict__ qbase, const float* __restrict__ kbase,
@@ -157,7 +157,10 @@ __device__ __forceinline__ void fp32_tile(float* As, float* Bs, const float* __r
 // leading one and the five small ones in sums of their own; parts staged in LDS as planes, 64 channels at a time, the next pass's means
 // fetched meanwhile.  Six products at sixteen times the rate of the fp32 matrix pipe, which the fp32 form was bound by (5.8 of its 14 us at
 // 12 x 512 x 512, 110 of 200 us at 40 x 1182 x 1182).  What is left is the chain of load, split, barrier and product, and the store.
-constexpr float kScoreLimit = 0x1p80f;  // up to here an operand's error of 2^-125 leaves a score off by less than 2^-38
+// Operands that are 0 or from 2^-50 to 2^80: such a value is its three parts exactly (from 2^-110 on it is), and the smallest of the six
+// products, 2^-16 of the leading one, stays above 2^-126.  (The look at the smallest: 389 -> 393 us for stage 1 at 40 x 1182 x 1182, 45.2 -> 45.3 at 12 x 512 x 512.)
+constexpr float kScoreMost = 0x1p80f;
+constexpr unsigned kScoreLeast = 77u << 23;  // (the bits of 2^-50)
 template <int D>
 __global__ __launch_bounds__(256, 3) void score_gemm(const float* __restrict__ qm, const float* __restrict__ km,
                                                   float* __restrict__ scores, int nb, int nb_valid,
@@ -198,7 +201,8 @@ __global__ __launch_bounds__(256, 3) void score_gemm(const float* __restrict__ q
   for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) big[mt][nt] = small[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float top = 0.f;  // largest magnitude this thread has split
+  float top = 0.f;         // largest magnitude this thread has split
+  unsigned least = ~0u;    // and the smallest that is not 0: twice its bits less 1, of which 0 makes the largest number
   fetch(0);
   for (int kc = 0; kc < D; kc += KC) {
     if (kc) __syncthreads();
@@ -211,6 +215,8 @@ __global__ __launch_bounds__(256, 3) void score_gemm(const float* __restrict__ q
         *reinterpret_cast<float4*>(x) = raw[o][u][0];
         *reinterpret_cast<float4*>(x + 4) = raw[o][u][1];
         largest8(top, x);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) least = min(least, 2u * __float_as_uint(x[i]) - 1u);
         const Split s = split8(x);
 #pragma unroll
         for (int part = 0; part < 3; ++part)
@@ -242,7 +248,7 @@ __global__ __launch_bounds__(256, 3) void score_gemm(const float* __restrict__ q
         }
     }
   }
-  if (__syncthreads_or(top >= kScoreLimit)) return with_fp32_operands();  // (a NaN stays a NaN either way)
+  if (__syncthreads_or(top >= kScoreMost || least < 2u * kScoreLeast - 1u)) return with_fp32_operands();  // (a NaN stays a NaN either way)
   // element r of tile (mt, nt): row wi + 16 mt + 4 G + r, column wj + 16 nt + c16
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt)
@@ -273,7 +279,7 @@ hipError_t run(const void* q, const void* k, const Dims& s, float* scores, float
   if (e != hipSuccess) return e;
   const int tiles = (s.nb + 63) / 64;
   // Up to two workgroups per CU the splits stand in the way and the fp32 products do not: stage 1 with fp32 operands / in parts, 12 heads x 55 blocks 7.2 /
-  // 7.5 us, 3 x 33 8.2 / 8.8, 24 x 256 44.0 / 43.8; 12 x 512 45.6 / 44.5, 12 x 624 60.6 / 56.2, 40 x 1182 415 / 384.  (Error against 64 bits, 2-norm:
+  // 7.5 us, 3 x 33 8.2 / 8.8, 24 x 256 44.0 / 43.8; 12 x 512 45.6 / 44.5, 12 x 624 60.6 / 56.2, 40 x 1182 415 / 388.  (Error against 64 bits, 2-norm:
   // 2.06e-7 / 0.72e-7 at d = 128, 1.46e-7 / 0.5e-7 at d = 64.)
   const int fp32 = (long long)tiles * tiles * s.bh() <= 512;
   score_gemm<D><<<dim3(tiles, tiles, (unsigned)s.bh()), 256, 0, st>>>(ws, ws + mean_elems, scores, s.nb,

@@ -536,7 +536,7 @@ def test_work_order_sizes(usv, nb, kmax):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Hh,nb", [(2, 1), (2, 33), (2, 64), (57, 130), (129, 65), (513, 64)])  # up to 512 tiles in fp32; more in parts: 513, 516
-@pytest.mark.parametrize("what", ["plain", "huge q, tiny k", "tiny q, huge k", "inf", "nan", "one huge block", "tiny"])
+@pytest.mark.parametrize("what", ["plain", "huge q, tiny k", "tiny q, huge k", "inf", "nan", "one huge block", "tiny", "tiny q, large k", "one tiny block"])
 def test_block_scores_operands_beyond_a_split(usv, d, Hh, nb, what):
     """The score product takes its operands in three bf16 parts; what these do not carry it multiplies in fp32: scores against a 64-bit
     evaluation at the fp32 bound, infinities and NaN where that has them."""
@@ -548,6 +548,8 @@ def test_block_scores_operands_beyond_a_split(usv, d, Hh, nb, what):
     if what == "nan": K[0, 0, 7, 1] = np.nan
     if what == "one huge block": K[0, 1, -64:] *= np.float32(2.0 ** 110)
     if what == "tiny": Q, K = Q * np.float32(2.0 ** -70), K * np.float32(2.0 ** -60)
+    if what == "tiny q, large k": Q, K = Q * np.float32(2.0 ** -122), K * np.float32(2.0 ** 40)  # (second parts of 2^-133)
+    if what == "one tiny block": Q, K[0, 1, -64:] = Q * np.float32(2.0 ** 40), K[0, 1, -64:] * np.float32(2.0 ** -122)
     got = gu.down(usv.block_scores(gu.up(Q), gu.up(K)))[:, :2].astype(np.float64)
     with np.errstate(all="ignore"):
         qm, km = (x.astype(np.float64).reshape(2, nb, 64, d).mean(axis=2) for x in (Q[0, :2], K[0, :2]))
