@@ -157,9 +157,11 @@ __device__ __forceinline__ void fp32_tile(float* As, float* Bs, const float* __r
 // leading one and the five small ones in sums of their own; parts staged in LDS as planes, 64 channels at a time, the next pass's means
 // fetched meanwhile.  Six products at sixteen times the rate of the fp32 matrix pipe, which the fp32 form was bound by (5.8 of its 14 us at
 // 12 x 512 x 512, 110 of 200 us at 40 x 1182 x 1182).  What is left is the chain of load, split, barrier and product, and the store.
-// Operands that are 0 or from 2^-50 to 2^80: such a value is its three parts exactly (from 2^-110 on it is), and the smallest of the six
-// products, 2^-16 of the leading one, stays above 2^-126.  (The look at the smallest: 389 -> 393 us for stage 1 at 40 x 1182 x 1182, 45.2 -> 45.3 at 12 x 512 x 512.)
-constexpr float kScoreMost = 0x1p80f;
+// Operands that are 0 or from 2^-50 to 2^59.  Below 2^59 no sum of 128 products overflows (beyond, the leading and the small sums could do so
+// with opposite signs, and a leading part rounded up could where the value does not).  From 2^-50 on such a value is its three parts exactly, each of
+// which is 0 or at least the value's last bit, 2^-73; of the six products only that of the two second parts may then fall below 2^-126, which is
+// 2^-26 of the leading one.  (The look at the smallest: 389 -> 393 us for stage 1 at 40 x 1182 x 1182, 45.2 -> 45.3 at 12 x 512 x 512.)
+constexpr float kScoreMost = 0x1p59f;
 constexpr unsigned kScoreLeast = 77u << 23;  // (the bits of 2^-50)
 template <int D>
 __global__ __launch_bounds__(256, 3) void score_gemm(const float* __restrict__ qm, const float* __restrict__ km,

@@ -561,3 +561,26 @@ def test_block_scores_operands_beyond_a_split(usv, d, Hh, nb, what):
         # the means' fp32 sums of 64 values and the product's of d: a few 2^-24 each of the terms' sum
         err = np.abs(np.where(fin, got[0] - ref, 0))
         assert (err <= np.where(fin, 1e-5 * terms, 0) + 1e-37).all(), (what, (err / np.maximum(terms, 1e-300))[fin].max())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hh,nb", [(1, 64), (2, 512), (9, 512)])  # one tile, tiles for half of the chip, and beyond
+@pytest.mark.parametrize("what", ["2^58", "2^60", "2^70", "2^79", "next to the largest"])
+def test_block_scores_large_operands(usv, d, Hh, nb, what):
+    """Both operands large: infinite where fp32 sums are, finite where those are, never NaN.  Block means of one sign, so that no
+    order of summing cancels; the tokens of a block are alike."""
+    rng = np.random.default_rng(d + nb)
+    if what == "next to the largest":  # products of -2^128 (1 - 2^-11): they fit into fp32, those of the operands rounded to bf16 do not
+        q, k = np.zeros((nb, d), np.float32), np.zeros((nb, d), np.float32)
+        q[:, 3], k[:, 3] = 2.0 ** 64 * (1 - 2.0 ** -12), -2.0 ** 64 * (1 - 2.0 ** -12)
+    else:
+        q, k = (np.abs(rng.standard_normal((nb, d))).astype(np.float32) * np.float32(2.0 ** int(what[2:])) for _ in range(2))
+    Q, K = (np.array(np.broadcast_to(np.repeat(x, 64, axis=0), (1, Hh, nb * 64, d))) for x in (q, k))
+    got = gu.down(usv.block_scores(gu.up(Q), gu.up(K)))[0].astype(np.float64)
+    sums = q.astype(np.float64) @ k.astype(np.float64).T  # the product ahead of its scaling is what overflows
+    largest = float(np.finfo(np.float32).max)
+    near = 1e-5 * largest  # (there a sum may go either way)
+    inf, fin = sums > largest + near, np.abs(sums) < largest - near
+    assert not np.isnan(got).any() and np.isposinf(got[:, inf]).all()
+    ref = sums / np.sqrt(d)
+    assert (np.abs(got[:, fin] - ref[fin]) <= 1e-5 * np.abs(ref[fin])).all()
