@@ -154,22 +154,29 @@ __device__ __forceinline__ void fp32_tile(float* As, float* Bs, const float* __r
 }
 
 // The products of three bf16 parts on v_mfma_f32_16x16x32_bf16 (lane = (c, G): rows / columns c of the operands, channels 8 G .. + 8), the
-// leading one and the five small ones in sums of their own; parts staged in LDS as planes, 64 channels at a time, the next pass's means
-// fetched meanwhile.  Six products at sixteen times the rate of the fp32 matrix pipe, which the fp32 form was bound by (5.8 of its 14 us at
+// leading one and the five small ones in sums of their own; parts staged in LDS as planes, 64 channels at a
+// time.  Six products at sixteen times the rate of the fp32 matrix pipe, which the fp32 form was bound by (5.8 of its 14 us at
 // 12 x 512 x 512, 110 of 200 us at 40 x 1182 x 1182).  What is left is the chain of load, split, barrier and product, and the store.
-// Operands that are 0 or from 2^-50 to 2^59.  Below 2^59 no sum of 128 products overflows (beyond, the leading and the small sums could do so
-// with opposite signs, and a leading part rounded up could where the value does not).  From 2^-50 on such a value is its three parts exactly, each of
-// which is 0 or at least the value's last bit, 2^-73; of the six products only that of the two second parts may then fall below 2^-126, which is
-// 2^-26 of the leading one.  (The look at the smallest: 389 -> 393 us for stage 1 at 40 x 1182 x 1182, 45.2 -> 45.3 at 12 x 512 x 512.)
+// Operands below 2^59 that are 0 or not below 2^-50 (2^-100 beside larger ones).  Below 2^59 no sum of 128 products overflows
+// (beyond, the leading and the small sums could do so with opposite signs, and a leading part rounded up could where the value does not).  A value
+// from 2^-100 on is its three parts exactly, each of which is 0 or at least the value's last bit; what is lost of a product is what falls below
+// 2^-126.  From 2^-50 on only the product of two second parts can, which is 2^-26 of the leading one.  A smaller value (of a channel that is nearly
+// dead) may stand beside larger ones, as long as every group of eight channels has one from 2^-40 on: all that a score's products lose there is
+// below 2^-116, which is less than its fp32 rounding if its terms add up to 2^-92.
+// The look at the operands comes ahead of the products, with the means of all passes requested at once for it.  (Behind them, a tile that fp32
+// operands were taken for was multiplied twice.)  Stage 1, look behind / ahead: 40 x 1182 x 1182 391 / 382 us, 12 x 512 x 512 44.7 / 44.8, d = 64 201.6 /
+// 203.8, 27.3 / 27.2; one channel nearly dead 525 / 391, 52.5 / 45.2, 265 / 206, 30.9 / 27.3; eight of them, which takes fp32 operands, 526 / 469, 53.4 / 50.4
+// (fp32 operands alone: 421, 46.9).
 constexpr float kScoreMost = 0x1p59f;
-constexpr unsigned kScoreLeast = 77u << 23;  // (the bits of 2^-50)
+constexpr unsigned below(int e) { return 2u * ((unsigned)(127 + e) << 23) - 1u; }  // twice the bits of 2^e less 1
 template <int D>
 __global__ __launch_bounds__(256, 3) void score_gemm(const float* __restrict__ qm, const float* __restrict__ km,
                                                   float* __restrict__ scores, int nb, int nb_valid,
                                                   float rsqrt_d, int fp32) {
-  constexpr int KC = 64, kPlane = 64 * KC * 2;  // channels per pass; bytes of one part of 64 rows
+  constexpr int KC = 64, P = D / KC, kPlane = 64 * KC * 2;  // channels per pass, passes; bytes of one part of 64 rows
   static_assert(2 * 64 * kTileLd * 4 <= 6 * kPlane, "the fp32 tile's operands overlay the planes");
   __shared__ __attribute__((aligned(16))) unsigned char smem[6 * kPlane];  // three planes of Q, three of K
+  __shared__ int refused[4];  // per wave: operands that parts do not carry
   const int bh = blockIdx.z;
   const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
   const float* qbase = qm + (long long)bh * nb * D;
@@ -184,48 +191,68 @@ __global__ __launch_bounds__(256, 3) void score_gemm(const float* __restrict__ q
   const int c16 = lane & 15, G = lane >> 4;
   // a row's eight 16-byte chunks are stored at chunk ^ (row % 8): sixteen rows of a fragment spread over the banks
   auto at = [](int row, int chunk) { return row * (KC * 2) + ((chunk ^ (row & 7)) << 4); };
-  // thread: two pieces of eight channels of either operand per pass
-  float4 raw[2][2][2];  // [operand][piece][half]
-  auto fetch = [&](int kc) {
+  // thread: two pieces of eight channels of either operand per pass, those of all passes requested at once
+  float4 raw[P][2][2][2];  // [pass][operand][piece][half]
+#pragma unroll
+  for (int p = 0; p < P; ++p)
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int e = tid + 256 * u, row = e >> 3, c = (e & 7) * 8;
+      const int e = tid + 256 * u, row = e >> 3, c = p * KC + (e & 7) * 8;
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
-        raw[0][u][half] = raw[1][u][half] = make_float4(0.f, 0.f, 0.f, 0.f);  // zero rows beyond nb
-        if (i0 + row < nb) raw[0][u][half] = *reinterpret_cast<const float4*>(qbase + (long long)(i0 + row) * D + kc + c + 4 * half);
-        if (j0 + row < nb) raw[1][u][half] = *reinterpret_cast<const float4*>(kbase + (long long)(j0 + row) * D + kc + c + 4 * half);
+        raw[p][0][u][half] = raw[p][1][u][half] = make_float4(0.f, 0.f, 0.f, 0.f);  // zero rows beyond nb
+        if (i0 + row < nb) raw[p][0][u][half] = *reinterpret_cast<const float4*>(qbase + (long long)(i0 + row) * D + c + 4 * half);
+        if (j0 + row < nb) raw[p][1][u][half] = *reinterpret_cast<const float4*>(kbase + (long long)(j0 + row) * D + c + 4 * half);
       }
     }
-  };
   f32x4 big[2][2], small[2][2];
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) big[mt][nt] = small[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float top = 0.f;         // largest magnitude this thread has split
-  unsigned least = ~0u;    // and the smallest that is not 0: twice its bits less 1, of which 0 makes the largest number
-  fetch(0);
-  for (int kc = 0; kc < D; kc += KC) {
-    if (kc) __syncthreads();
+  // do parts carry the operands of all passes?
+  float top = 0.f, least_top = INFINITY;  // largest magnitude; the smallest that is the largest of its piece
+  unsigned least = ~0u;                   // the smallest that is not 0: twice its bits less 1, of which 0 makes the largest number
+  auto look = [&](const float(&x)[8]) {
+    float t = 0.f;
+    largest8(t, x);
+    top = fmaxf(top, t), least_top = fminf(least_top, t);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) least = min(least, 2u * __float_as_uint(x[i]) - 1u);
+  };
+  auto bad = [&] {  // (a NaN stays a NaN either way)
+    return top >= kScoreMost || (least < below(-50) && (least_top < 0x1p-40f || least < below(-100)));
+  };
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    if (p) __syncthreads();
 #pragma unroll
     for (int o = 0; o < 2; ++o)
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int e = tid + 256 * u;
         float x[8];
-        *reinterpret_cast<float4*>(x) = raw[o][u][0];
-        *reinterpret_cast<float4*>(x + 4) = raw[o][u][1];
-        largest8(top, x);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) least = min(least, 2u * __float_as_uint(x[i]) - 1u);
+        *reinterpret_cast<float4*>(x) = raw[p][o][u][0];
+        *reinterpret_cast<float4*>(x + 4) = raw[p][o][u][1];
+        if (p == 0) look(x);
         const Split s = split8(x);
 #pragma unroll
         for (int part = 0; part < 3; ++part)
           *reinterpret_cast<bf16x8*>(smem + (3 * o + part) * kPlane + at(e >> 3, e & 7)) = s.p[part];
       }
+    if (p == 0) {
+#pragma unroll
+      for (int f = 4; f < 4 * P; ++f) {
+        float x[8];
+        *reinterpret_cast<float4*>(x) = raw[f >> 2][(f >> 1) & 1][f & 1][0];
+        *reinterpret_cast<float4*>(x + 4) = raw[f >> 2][(f >> 1) & 1][f & 1][1];
+        look(x);
+      }
+      const int any = __any(bad());
+      if (lane == 0) refused[wave] = any;
+    }
     __syncthreads();
-    if (kc + KC < D) fetch(kc + KC);
+    if (p == 0 && (refused[0] | refused[1] | refused[2] | refused[3])) return with_fp32_operands();
 #pragma unroll
     for (int t = 0; t < KC / 32; ++t) {
       bf16x8 a[2][3], b[2][3];
@@ -250,7 +277,6 @@ __global__ __launch_bounds__(256, 3) void score_gemm(const float* __restrict__ q
         }
     }
   }
-  if (__syncthreads_or(top >= kScoreMost || least < 2u * kScoreLeast - 1u)) return with_fp32_operands();  // (a NaN stays a NaN either way)
   // element r of tile (mt, nt): row wi + 16 mt + 4 G + r, column wj + 16 nt + c16
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt)

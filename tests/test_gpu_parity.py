@@ -584,3 +584,19 @@ def test_block_scores_large_operands(usv, d, Hh, nb, what):
     assert not np.isnan(got).any() and np.isposinf(got[:, inf]).all()
     ref = sums / np.sqrt(d)
     assert (np.abs(got[:, fin] - ref[fin]) <= 1e-5 * np.abs(ref[fin])).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nb", [512, 515])  # whole tiles; rows beyond the blocks, which read as zeros
+@pytest.mark.parametrize("what", ["one channel 2^-60", "one channel 2^-98", "one channel 2^-110", "a group 2^-60", "a group 0", "one channel 0"])
+def test_block_scores_dead_channels(usv, d, nb, what):
+    """Channels that are nearly dead, beside live ones (in parts) and in whole groups of eight (fp32 operands), against a 64-bit evaluation."""
+    rng = np.random.default_rng(d + nb)
+    Hh = 9
+    Q, K = (np.resize(rng.standard_normal((1, 1, nb * 64, d), dtype=np.float32), (1, Hh, nb * 64, d)) for _ in range(2))
+    K[..., 8:16 if what.startswith("a group") else 9] *= np.float32(0 if what.endswith(" 0") else 2.0 ** int(what.split("^")[1]))
+    got = gu.down(usv.block_scores(gu.up(Q), gu.up(K)))[0].astype(np.float64)
+    qm, km = (x[0, 0].astype(np.float64).reshape(nb, 64, d).mean(axis=1) for x in (Q, K))
+    terms = np.abs(qm) @ np.abs(km).T
+    # the means' fp32 sums of 64 values and the product's of d: a few 2^-24 each of the terms' sum
+    assert (np.abs(got - qm @ km.T / np.sqrt(d)) <= 1e-5 * terms).all()
