@@ -72,7 +72,8 @@ size_t usv_workspace_bytes(const usv_shape* shape);
  *
  * q, k   : [B, Hh, N, d] of shape->dtype (device, read only)
  * scores : [B, Hh, nb, nb] fp32 (device, written); rows and columns of blocks
- *          that hold no valid token are written as -inf
+ *          that hold no valid token are written as -inf.  A head's scores are the
+ *          same, bit for bit, whatever batch and heads it is launched with
  * ws     : device scratch of at least usv_workspace_bytes(shape) bytes; its
  *          contents on return are unspecified
  */

@@ -306,10 +306,12 @@ hipError_t run(const void* q, const void* k, const Dims& s, float* scores, float
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int tiles = (s.nb + 63) / 64;
-  // Up to two workgroups per CU the splits stand in the way and the fp32 products do not: stage 1 with fp32 operands / in parts, 12 heads x 55 blocks 7.2 /
-  // 7.5 us, 3 x 33 8.2 / 8.8, 24 x 256 44.0 / 43.8; 12 x 512 45.6 / 44.5, 12 x 624 60.6 / 56.2, 40 x 1182 415 / 388.  (Error against 64 bits, 2-norm:
-  // 2.06e-7 / 0.72e-7 at d = 128, 1.46e-7 / 0.5e-7 at d = 64.)
-  const int fp32 = (long long)tiles * tiles * s.bh() <= 512;
+  // Parts from 512 blocks on; from there a head's tiles fill the chip with a few heads.  Batch and heads have no part in this: a head has the same
+  // scores, to the bit, in any launch.  Stage 1 with fp32 operands / in parts, d = 128: 1 head x 512 blocks 8.9 / 9.9 us, 2 11.4 / 12.4, 6 27.4 / 27.5, 12
+  // 45.7 / 44.8, 40 146 / 137; 1 x 1182 18.0 / 18.0, 40 x 1182 421 / 382; d = 64 7.1 / 7.5 (1 x 512), 27.6 / 27.2 (12 x 512), 222 / 204 (40 x 1182).  Below:
+  // 12 x 55 9.9 / 11.0, 12 x 256 24.3 / 25.4, 12 x 448 43.0 / 42.8, 24 x 448 80.8 / 76.  (Error against 64 bits, 2-norm: 2.06e-7 / 0.72e-7 at d = 128,
+  // 1.46e-7 / 0.5e-7 at d = 64.)
+  const int fp32 = s.nb < 512;
   score_gemm<D><<<dim3(tiles, tiles, (unsigned)s.bh()), 256, 0, st>>>(ws, ws + mean_elems, scores, s.nb,
                                                                          s.nb_valid, 1.0f / sqrtf((float)D), fp32);
   return hipGetLastError();

@@ -535,7 +535,7 @@ def test_work_order_sizes(usv, nb, kmax):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("Hh,nb", [(2, 1), (2, 33), (2, 64), (57, 130), (129, 65), (513, 64)])  # up to 512 tiles in fp32; more in parts: 513, 516
+@pytest.mark.parametrize("Hh,nb", [(2, 33), (2, 511), (2, 512), (3, 577)])  # below 512 blocks in fp32, from there in parts
 @pytest.mark.parametrize("what", ["plain", "huge q, tiny k", "tiny q, huge k", "inf", "nan", "one huge block", "tiny", "tiny q, large k", "one tiny block"])
 def test_block_scores_operands_beyond_a_split(usv, d, Hh, nb, what):
     """The score product takes its operands in three bf16 parts; what these do not carry it multiplies in fp32: scores against a 64-bit
@@ -553,8 +553,8 @@ def test_block_scores_operands_beyond_a_split(usv, d, Hh, nb, what):
     got = gu.down(usv.block_scores(gu.up(Q), gu.up(K)))[:, :2].astype(np.float64)
     with np.errstate(all="ignore"):
         qm, km = (x.astype(np.float64).reshape(2, nb, 64, d).mean(axis=2) for x in (Q[0, :2], K[0, :2]))
-        terms = np.abs(qm[:, :, None, :] * km[:, None, :, :]).sum(axis=-1)  # what a score sums up
-        ref = (qm[:, :, None, :] * km[:, None, :, :]).sum(axis=-1) / np.sqrt(d)
+        terms = np.abs(qm) @ np.abs(km).transpose(0, 2, 1)  # what a score sums up
+        ref = qm @ km.transpose(0, 2, 1) / np.sqrt(d)
         fin = np.isfinite(ref)
         assert np.array_equal(np.isnan(got[0]), np.isnan(ref)) and np.array_equal(np.isinf(got[0]), np.isinf(ref))
         assert np.array_equal(got[0][np.isinf(ref)], ref[np.isinf(ref)])
@@ -564,7 +564,7 @@ def test_block_scores_operands_beyond_a_split(usv, d, Hh, nb, what):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("Hh,nb", [(1, 64), (2, 512), (9, 512)])  # one tile, tiles for half of the chip, and beyond
+@pytest.mark.parametrize("Hh,nb", [(1, 64), (2, 511), (2, 512)])  # fp32 operands, parts
 @pytest.mark.parametrize("what", ["2^58", "2^60", "2^70", "2^79", "next to the largest"])
 def test_block_scores_large_operands(usv, d, Hh, nb, what):
     """Both operands large: infinite where fp32 sums are, finite where those are, never NaN.  Block means of one sign, so that no
@@ -592,7 +592,7 @@ def test_block_scores_large_operands(usv, d, Hh, nb, what):
 def test_block_scores_dead_channels(usv, d, nb, what):
     """Channels that are nearly dead, beside live ones (in parts) and in whole groups of eight (fp32 operands), against a 64-bit evaluation."""
     rng = np.random.default_rng(d + nb)
-    Hh = 9
+    Hh = 2
     Q, K = (np.resize(rng.standard_normal((1, 1, nb * 64, d), dtype=np.float32), (1, Hh, nb * 64, d)) for _ in range(2))
     K[..., 8:16 if what.startswith("a group") else 9] *= np.float32(0 if what.endswith(" 0") else 2.0 ** int(what.split("^")[1]))
     got = gu.down(usv.block_scores(gu.up(Q), gu.up(K)))[0].astype(np.float64)
@@ -600,3 +600,15 @@ def test_block_scores_dead_channels(usv, d, nb, what):
     terms = np.abs(qm) @ np.abs(km).T
     # the means' fp32 sums of 64 values and the product's of d: a few 2^-24 each of the terms' sum
     assert (np.abs(got - qm @ km.T / np.sqrt(d)) <= 1e-5 * terms).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nb", [65, 300, 511, 512, 577])
+def test_block_scores_of_a_head_alone(usv, d, nb):
+    """A head's scores do not depend on what else the launch holds: alone, and among batch elements and heads, the same bits."""
+    gen = torch.Generator(device=gu.DEV).manual_seed(nb)
+    q, k = (torch.randn((2, 6, nb * 64, d), device=gu.DEV, generator=gen).to(torch.bfloat16) for _ in range(2))
+    s = usv.block_scores(q, k)
+    for b, h in ((0, 0), (1, 5)):
+        alone = usv.block_scores(q[b:b + 1, h:h + 1].contiguous(), k[b:b + 1, h:h + 1].contiguous())
+        assert torch.equal(alone[0, 0].view(torch.int32), s[b, h].view(torch.int32))
