@@ -756,7 +756,17 @@ template <int CH>
 __global__ __launch_bounds__(kSpThreads) void merge_select_spread(const float* __restrict__ u, const int32_t* __restrict__ blk,
                                                                   int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
                                                                   int N, int n_dst, int r) {
-  __shared__ int h[kSpBins];
+  // Similarities of few values meet in their bins.  16384 tokens, ten values: with a second copy of every bin for the odd lanes 23.2 instead of 25.8 us,
+  // where the five launches take 23.7 (all different: 14.3 / 14.3).  More tokens come here without a workspace only, where the other form is the slower
+  // one anyway, and copies cost what is usual more (four chunks 21.5 -> 21.7 us, ten 41.6 -> 44.1).
+  constexpr int COPIES = CH == 2 ? 2 : 1;
+  __shared__ int h[kSpBins * COPIES];
+  auto in_bin = [&](int bin) {
+    int n = 0;
+#pragma unroll
+    for (int c = 0; c < COPIES; ++c) n += h[bin * COPIES + c];
+    return n;
+  };
   __shared__ int scan_a[kSpWaves], scan_b[kSpWaves], scan_c[kSpWaves], scan_d[kSpWaves];
   __shared__ uint32_t low[kSpWaves], high[kSpWaves], cand[kSpList];
   __shared__ uint32_t picked_key;
@@ -801,7 +811,7 @@ __global__ __launch_bounds__(kSpThreads) void merge_select_spread(const float* _
       const uint32_t width = hi - lo;
       const int shift = width < (uint32_t)kSpBins ? 0 : 20 - __clz((int)width);
 #pragma unroll
-      for (int k = 0; k < kSpBins / kSpThreads; ++k) h[k * kSpThreads + tid] = 0;
+      for (int k = 0; k < kSpBins * COPIES / kSpThreads; ++k) h[k * kSpThreads + tid] = 0;
       if (tid == 0) picked_bin = 0, picked_rank = 0, picked_count = 0, n_cand = 0;
       __syncthreads();
 #pragma unroll
@@ -815,9 +825,9 @@ __global__ __launch_bounds__(kSpThreads) void merge_select_spread(const float* _
           // (ties: a wave whose keys all fall into one bin adds them at once)
           const int first = __builtin_amdgcn_readlane(bin, __ffsll(all) - 1);
           if (__ballot(in && bin == first) == all) {
-            if (lane == 0) atomicAdd(&h[first], __popcll(all));
+            if (lane == 0) atomicAdd(&h[first * COPIES], __popcll(all));
           } else if (in) {
-            atomicAdd(&h[bin], 1);
+            atomicAdd(&h[bin * COPIES + (lane & (COPIES - 1))], 1);
           }
         }
       __syncthreads();
@@ -826,11 +836,11 @@ __global__ __launch_bounds__(kSpThreads) void merge_select_spread(const float* _
         const int top = kSpBins - 1 - tid * P;
         int own = 0, total;
 #pragma unroll
-        for (int p = 0; p < P; ++p) own += h[top - p];
+        for (int p = 0; p < P; ++p) own += in_bin(top - p);
         int above = sp_exclusive(own, level & 1 ? scan_b : scan_a, &total);
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-          const int n = h[top - p];
+          const int n = in_bin(top - p);
           if (above < rank && rank <= above + n) picked_bin = top - p, picked_rank = rank - above, picked_count = n;
           above += n;
         }
@@ -1091,7 +1101,8 @@ hipError_t launch_merge_select(const float* u, const int32_t* blk, const MergeGr
   const int n_dst = g.nT * g.nH * g.nW;
   // One launch whose workgroups each look through all keys, or five that share them out.  With a workspace, spread / five launches, distinct similarities
   // (18 distinct ones): 1105 x 2 tokens 9.1 / 26.6 us (12.6 / 26.5), 3510 11.3 / 30.4 (16.0 / 30.7), 17589 30.4 / 31.5 (42.7 / 31.9), 32760 21.7 / 23.7 (41.1 /
-  // 24.1), 75600 41.7 / 25.7.  Without one, against one workgroup per batch element: 32760 21.7 / 36.1, 75600 41.6 / 123.
+  // 24.1), 75600 41.7 / 25.7.  Without one, against one workgroup per batch element: 32760 21.7 / 36.1 (ten distinct ones 41.3 /
+  // 46.6), 75600 41.6 / 118 (83.9 / 139).
   constexpr int kChunk = kSpThreads * kRsPer;  // (keys of ten chunks fit a workgroup's registers)
   if (N <= (ws ? 2 : 10) * kChunk) {
     const dim3 grid((unsigned)((N + kSpSlice - 1) / kSpSlice), (unsigned)B);
