@@ -153,6 +153,14 @@ __device__ __forceinline__ void store8(void* dst, const float4 (&val)[2], int st
 // runs at the limit of the fabric, which ordinary stores load more evenly).
 inline int stream_output(const Dims& s) { return 4LL * s.nb * kBlock * s.d <= (32LL << 20); }
 
+// Workgroups that the chip runs together in the wide kernel; and whether a launch of long heads makes two to four such rounds, give or take a
+// twenty-fourth of one.  Sweeps that are kept together end together, and what is left behind a round then runs by itself.
+inline long long wide_round(const Dims& s) { return s.d == 128 ? 1024 : 1536; }
+inline bool full_rounds(const Dims& s) {
+  const long long round = wide_round(s), past = s.bh() * s.nb + round / 24;
+  return s.nb > 640 && past >= 2 * round && past < 5 * round && 12 * (past % round) < round;
+}
+
 // Second branch folded into the store: gate_fine * attention + gate_coarse * cube-level row.
 __device__ __forceinline__ void fuse4(float4& val, const float4& gf, const float4& gc, const float4& cz) {
   val.x = fmaf(gf.x, val.x, gc.x * cz.x);

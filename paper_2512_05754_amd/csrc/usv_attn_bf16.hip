@@ -666,6 +666,7 @@ inline bool wide_is_faster(const AttnBf16Args& a) {
     // long heads with short lists, which share most: 900 x 3, 180 1.00, 1024 x 3, 81 1.10, 1182 x 3, 94 1.15 but 147 0.98, 1500 x 3, 120 1.36.
     // A work order keeps equal lists together in both kernels: 1182 x 12, 147 1.01, 1500 x 12, 240 0.985, 1900 x 12, 152
     // 1.46 but 237 0.99, 1182 x 3, 59 1.07 but 94 0.97.
+    // (Lists of more than a fifth in index order, 64 to 640 blocks, 4 to 20 rounds: 0.97 to 1.025, on average 1.00; ragged ones in a work order 0.96 to 0.98.)
     if (5 * k > nb) return false;
     if (total > (nb > 640 ? 4608 : 5376)) return !a.work_order || nb <= 1280 || 8 * k <= nb;
     return nb >= 1000 && total > 2560 && (a.work_order ? 16 * k <= nb : nb >= 1400 || 10 * k <= nb);
@@ -679,7 +680,9 @@ inline bool wide_is_faster(const AttnBf16Args& a) {
     // 640 x 12, k = 102 1.07 of the wide kernel's time, 700 x 12, 112 1.09, 1182 x 12, 147 1.12, 189 1.09; 3 heads: 700, 56 0.99, 112
     // 1.02, 1024, 163 1.005, 1182, 94 0.995, 236 0.97.  1500 x 3, 120 1.18 but 187 0.89; 2400 x 3, 192 1.14 but 384 0.68.
     // Lists that start at their first entry: 768 x 12, 154 3.05 / 2.83, 1024 x 12, 256 1.05; 1182 x 12, 248 0.945, x 6, 236 3.60 / 4.54, 390 5.72 / 5.74
-    if (5 * k <= nb) return nb <= 640 || 12 * k <= nb || (nb <= 1280 && total > 4096);
+    // Lists of 19 %, which start at their first entry in launches of full rounds (usv_attn_wide.hip): 800 x 1 1.17, 1024 x 1 1.17, 660 x 3 1.19,
+    // 800 x 3 1.03, 900 x 3 1.07, 1024 x 2 1.09, x 4 1.04, but 720 x 3 0.97, 1182 x 3 0.98; ragged ones 800 x 3 1.07, 1024 x 2 1.10.
+    if ((full_rounds(s) ? 6 : 5) * k <= nb) return nb <= 640 || 12 * k <= nb || (nb <= 1280 && total > 4096) || (6 * k > nb && nb <= 1024);
     return nb <= 1024 || 3 * k >= nb;
   }
   // 700 x 12, k = 56 1.18, 112 1.09, 231 1.04; 900 x 12, 112 1.09, 225 1.04; 1182 x 12, 59 1.19, 189 1.12, 248 1.06; x 3, 59 1.10, 236 1.01,

@@ -730,13 +730,26 @@ hipError_t run(const AttnBf16Args& a, hipStream_t st) {
   // 789 / 783, 85 of 512 1037 / 1140, 102 of 512 1245 / 1260, 128 of 512 1558 / 1535, 170 of 512 2051 / 1980.  In index order, heads
   // beyond the L2 need more to stay together: 12 heads of 700 blocks, 175 listed 0.78 of the time, 800, 168 0.75, 900, 225
   // 0.71, 1182, 248 0.73, 900 x 3, 297 0.93; 40 % listed: 800 x 12 1.04, 900 x 3 0.97, 1182 x 3 1.08.
-  const bool sweep = 5LL * a.kmax <= s.nb || (!a.work_order && s.nb > 512 && s.nb <= 1280 && 5LL * a.kmax < 2LL * s.nb);
+  // Time with starts and turns (below), as a multiple of that from the first entry, where a small rest follows two rounds, index order, 35 % listed:
+  // 600 x 4 1.05, 720 x 3 1.05, 800 x 3 1.02, 1024 x 2 1.07, but 1060 to 1230 x 2 0.83 to 0.98; in a work order, 19 %: lists of equal lengths 1024 x 2 1.15, x 3 1.10, x
+  // 4 1.04, ragged ones 0.84, 0.80; 900 x 3 0.93.
+  const long long k = a.kmax, nb = s.nb, round = wide_round(s);
+  const bool sweep = a.work_order ? (full_rounds(s) ? 6 : 5) * k <= nb
+                                  : 5 * k <= nb || (D == 128 && nb > 512 && nb <= 1280 && 5 * k < 2 * nb &&
+                                                    !(nb <= 1024 && total >= 2 * round && 5 * total < 12 * round));
   // Taking turns keeps sweeps together, and it lets all workgroups of a round end at once: a part of a round behind them runs
   // alone.  So it pays on long heads, and on many rounds.  Time with turns, as a multiple of the time without; d = 128, 4 % / 8 / 14 / 19.5 of the
   // blocks listed: 160 blocks x 28 1.05 / 1.03 / 1.02 / 1.03, x 45 1.02 / 1.02 / 1.00 / 1.00; 230 x 10 0.98 / 1.02 / 1.05 / 1.07; 300 x 8 1.01 / 1.04 / 1.06 / 1.10, x 24 1.00 / 1.00 / 1.01 / 1.01; 512 x 4 0.95 / 1.06 / 1.09 / 1.09, x 9 0.94 / 0.93 / 0.99 / 1.00, x 14 0.97 /
   // 0.98 / 0.98 / 0.98; 620 x 3 0.93 / 0.88 / 0.93 / 0.92, x 12 0.97 / 0.91 / 0.93 / 0.90.  d = 64: 512 x 21 1.02 / 1.02 / 1.04 / 1.03, 620 x 17
   // 1.02 / 1.04 / 1.02 / 1.02, 1182 x 8, 100 listed 0.98.
-  const bool turns = sweep && (D == 64 ? s.nb > 800 : s.nb > 560 || (s.nb > 256 && total > 4096));
+  // Up to 640 blocks it does not where half a round or less follows two full ones, on lists of more than an eighth (600 x 4, 13 % / 19 % listed 1.04 / 1.05, 630 x
+  // 4, 80 listed in a work order 1.06), nor up to 1024 where hardly anything follows, on lists of more than a sixth (712 x 3, 120 listed 1.03, 1024 x 2, 194 1.06; but 802 x
+  // 3, 145 0.975), nor on short lists in index order in a single round of up to 860 (800 x 1, 64 listed 1.02; 1024 x 1, 81 0.91).  (d = 64 from 800 blocks on: 820 x 6, 4 % to 19 %
+  // listed 1.01 to 1.03, but in a work order with ragged lists 831 x 6, 58 0.97, 847 x 51, 45 0.93.)
+  const long long behind_two = total - 2 * round;
+  const bool alone = behind_two >= 0 && ((nb <= 640 && 8 * k > nb && 2 * behind_two < round) || (nb <= 1024 && 6 * k > nb && 5 * behind_two < round));
+  const bool one_short = total <= round && nb <= 860 && 8 * k <= nb && !a.work_order;
+  const bool turns = sweep && !alone && !one_short && (D == 64 ? nb > 800 : nb > 560 || (nb > 256 && total > 4096));
   // Lists of different lengths sweep at different speeds.  In index order they gain as the others do (40 of 512 at most:
   // 492 / 521 us); a work order brings equal lengths together, which keeps them together as long as a head is not much
   // beyond the L2: 16.8 MB 2480 / 2078 us, but 38.7 MB 7270 / 8050 us and (d = 64) 19.4 MB 2809 / 3235 us.
