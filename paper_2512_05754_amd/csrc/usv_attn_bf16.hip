@@ -658,7 +658,7 @@ inline bool wide_is_faster(const AttnBf16Args& a) {
   //   gain from the start of the sweep: 1182 blocks x 4, 71 listed 537 / 447
   // Longer heads share fetched tiles as long as the sweeps of an XCD stay together: twice as many run together in the wide
   // kernel, which starts lists of up to a fifth of the blocks where the others are (in index order up to two fifths; the rule is in
-  // usv_attn_wide.hip).  Times in ms; k = kmax; measured over 3 and 12 heads of 560 to 2400 blocks, 3 % to all of them listed.
+  // usv_attn_wide.hip).  Times in ms; k = kmax; measured over 1 to 8 and 12 heads of 560 to 2400 blocks, 3 % to all of them listed.
   const long long k = a.kmax, nb = s.nb;
   if (s.d == 64) {
     // Lists that start at their first entry: 560 x 12, k = 224 0.973, 900 x 12, 360 0.981, 1182 x 12, 295 0.969 of the wide kernel's
