@@ -7,10 +7,12 @@ There is no CPU fallback: a missing library or a CPU tensor raises.
 from __future__ import annotations
 
 import ctypes
+import hashlib
 import importlib.machinery
 import os
 import sys
 import types
+import warnings
 from functools import lru_cache
 
 import torch
@@ -96,33 +98,53 @@ _lib = None
 _calls = None  # the marshalling extension, once the library is loaded
 
 
+_CALLS_SOURCES = (os.path.join(PKG_DIR, "csrc", "usv_calls.cpp"), os.path.join(os.path.dirname(PKG_DIR), "include", "usv.h"))
+
+
 def calls_path() -> str:
-    """The marshalling extension; it is built against one torch and one interpreter, so their versions are in its name."""
-    return os.path.join(PKG_DIR, f"_calls-{torch.__version__}{importlib.machinery.EXTENSION_SUFFIXES[0]}")
+    """The marshalling extension.  It is built against one torch, one interpreter and one version of its sources, so all three are in
+    its name: what is left of another one is not found."""
+    h = hashlib.sha256()
+    for name in _CALLS_SOURCES:
+        with open(name, "rb") as f:
+            h.update(f.read())
+    return os.path.join(PKG_DIR, f"_calls-{torch.__version__}-{h.hexdigest()[:12]}{importlib.machinery.EXTENSION_SUFFIXES[0]}")
 
 
 def _load_calls():
-    """csrc/usv_calls.cpp as built for this torch and interpreter; None where there is none (the functions here then marshal through
-    ctypes, as they do for every call that the extension does not know)."""
-    path = calls_path()
-    if not os.path.exists(path):
+    """csrc/usv_calls.cpp as built for this torch and interpreter; None where there is none or it does not load (the functions here then
+    marshal through ctypes, as they do for every call that the extension does not know)."""
+    try:
+        path = calls_path()
+        if not os.path.exists(path):
+            return None
+        loader = importlib.machinery.ExtensionFileLoader("_calls", path)
+        calls = loader.create_module(importlib.machinery.ModuleSpec("_calls", loader, origin=path))
+        loader.exec_module(calls)
+        return calls
+    except (ImportError, OSError) as e:
+        warnings.warn(f"the marshalling extension does not load, small calls take longer: {e}", RuntimeWarning, stacklevel=3)
         return None
-    loader = importlib.machinery.ExtensionFileLoader("_calls", path)
-    calls = loader.create_module(importlib.machinery.ModuleSpec("_calls", loader, origin=path))
-    loader.exec_module(calls)
-    return calls
+
+
+def _build_all():
+    from .build import build_calls, build_library
+
+    build_library(verbose=False)
+    try:
+        build_calls(verbose=False)
+    except (RuntimeError, OSError) as e:  # (no headers of torch or of the interpreter: ctypes does)
+        warnings.warn(f"the marshalling extension cannot be built, small calls take longer: {e}", RuntimeWarning, stacklevel=3)
 
 
 def lib() -> ctypes.CDLL:
-    """Loads libusv.so (building it first only if it has never been built)."""
+    """Loads libusv.so (building it and the marshalling extension first only if it has never been built)."""
     global _lib, _calls
     if _lib is not None:
         return _lib
     path = lib_path()
     if not os.path.exists(path):
-        from .build import build_library
-
-        build_library(verbose=False)
+        _build_all()
     calls = _load_calls()  # (ahead of the library: opened behind it, it slows torch's own calls down, 300 small ones 1.96 -> 2.22 ms)
     L = ctypes.CDLL(path)
     vp, i32, sz, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t, ctypes.c_float

@@ -1,6 +1,7 @@
 """Builds libusv.so (HIP kernels + C ABI) for gfx950 in-tree with hipcc.  `python -m paper_2512_05754_amd.build`."""
 from __future__ import annotations
 
+import glob
 import os
 import shutil
 import subprocess
@@ -47,7 +48,8 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
 
 
 def build_calls(verbose: bool = True) -> str:
-    """Compiles csrc/usv_calls.cpp (host code only) against the installed torch."""
+    """Compiles csrc/usv_calls.cpp (host code only) against the installed torch; what was built of other sources goes."""
+    import importlib.machinery
     import sysconfig
 
     import torch
@@ -68,6 +70,10 @@ def build_calls(verbose: bool = True) -> str:
     if res.returncode != 0:
         raise RuntimeError("g++ failed:\n" + res.stdout + res.stderr)
     os.replace(out + ".tmp", out)
+    suffix = importlib.machinery.EXTENSION_SUFFIXES[0]
+    for old in glob.glob(os.path.join(glob.escape(PKG_DIR), f"_calls-{glob.escape(torch.__version__)}*{suffix}")):
+        if old != out:
+            os.remove(old)
     return out
 
 

@@ -65,6 +65,62 @@ def shape(**kw):
     return binding.UsvShape(**base)
 
 
+@pytest.mark.parametrize("contents", [b"", b"\x7fELF" + bytes(60), None], ids=["empty", "truncated", "a folder"])
+def test_marshalling_extension_that_does_not_load_steps_aside(monkeypatch, tmp_path, contents):
+    """The library loads without the extension, and says so."""
+    path = tmp_path / "_calls.so"
+    path.mkdir() if contents is None else path.write_bytes(contents)
+    monkeypatch.setattr(binding, "calls_path", lambda: str(path))
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_calls", None)
+    with pytest.warns(RuntimeWarning, match="marshalling extension"):
+        L = binding.lib()
+    assert binding._calls is None and L.usv_workspace_bytes(ctypes.byref(shape())) > 0
+
+
+def test_marshalling_extension_belongs_to_its_sources(monkeypatch, tmp_path):
+    """One built of other sources, of the extension or of the C interface, is not opened."""
+    paths = [binding.calls_path()]
+    for i, name in enumerate(binding._CALLS_SOURCES):
+        changed = list(binding._CALLS_SOURCES)
+        changed[i] = str(tmp_path / os.path.basename(name))
+        with open(name) as f, open(changed[i], "w") as g:
+            g.write(f.read() + "\n")
+        monkeypatch.setattr(binding, "_CALLS_SOURCES", tuple(changed))
+        paths.append(binding.calls_path())
+        assert binding._load_calls() is None
+    assert len(set(paths)) == 3
+
+
+def test_first_use_builds_the_library_and_the_extension(monkeypatch, tmp_path):
+    """A library that was never built is built with its extension; an extension that cannot be built is no error."""
+    import shutil
+
+    from paper_2512_05754_amd import build
+
+    built, lib_path, target = [], binding.lib_path(), str(tmp_path / "libusv.so")
+    binding.lib()
+    monkeypatch.setattr(binding, "lib_path", lambda: target)
+    monkeypatch.setattr(build, "build_library", lambda verbose: (built.append("library"), shutil.copy(lib_path, target)))
+    for error in (None, RuntimeError("g++ failed")):
+        def build_calls(verbose):
+            built.append("extension")
+            if error:
+                raise error
+
+        monkeypatch.setattr(build, "build_calls", build_calls)
+        monkeypatch.setattr(binding, "_lib", None)
+        if os.path.exists(target):
+            os.remove(target)
+        if error:
+            with pytest.warns(RuntimeWarning, match="marshalling extension"):
+                binding.lib()
+        else:
+            binding.lib()
+        assert built == ["library", "extension"]
+        built.clear()
+
+
 def test_workspace_bytes():
     L = binding.lib()
     assert L.usv_workspace_bytes(ctypes.byref(shape())) == 2 * 2 * 16 * 64 * 4
