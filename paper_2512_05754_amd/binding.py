@@ -569,7 +569,7 @@ def merge_similarity(k, grid, mblock, out=None, blk=None, workspace=None):
     return out, blk
 
 
-MERGE_PLAN_WIDE_TOKENS = 8192  # from here on merge_plan brings a workspace by itself: the selection runs chip-wide
+MERGE_PLAN_WIDE_TOKENS = 16385  # from here on merge_plan brings a workspace by itself: with fewer tokens the library has no use for one
 
 
 def merge_plan_workspace_bytes(B, grid, mblock, r) -> int:
@@ -581,8 +581,9 @@ def merge_plan_workspace_bytes(B, grid, mblock, r) -> int:
 def merge_plan(u, blk, grid, mblock, r, row_of=None, src_of=None, workspace=None):
     """usv_merge_plan: u [B, T*H*W] fp32 and the partition blk -> row_of [B, T*H*W], src_of [B, T*H*W - r] (int32).
 
-    workspace: uint8 device tensor of merge_plan_workspace_bytes(...) -> the selection is spread over the chip; False ->
-    one workgroup per batch element; None -> a workspace is allocated from MERGE_PLAN_WIDE_TOKENS tokens on."""
+    workspace: uint8 device tensor of merge_plan_workspace_bytes(...) -> beyond 16384 tokens the selection is shared out over the chip;
+    False -> none (every workgroup looks through all keys, beyond 81920 tokens one workgroup per batch element does); None -> one is
+    allocated from MERGE_PLAN_WIDE_TOKENS tokens on."""
     B, N = u.shape
     shp = _merge_shape(B, 1, 64, torch.float32, grid, r)[1]
     g = _grid(grid, mblock)

@@ -42,8 +42,9 @@ def expected_blk(grid, mb):
 
 
 def both_plans(usv, u, blk, grid, mb, r):
-    """usv_merge_plan both ways: one workgroup per batch element (no workspace) and the radix select spread over the chip
-    (workspace, handed over full of garbage: nothing in it is assumed clear).  The two must agree bit for bit."""
+    """usv_merge_plan without a workspace and with one, handed over full of garbage (nothing in it is assumed clear).  The two must
+    agree bit for bit.  Beyond 16384 tokens they are different kernels (one launch whose workgroups each look through all keys, beyond
+    81920 tokens one workgroup per batch element; the radix select shared out over the chip); up to there the same one, which leaves the workspace alone."""
     one = usv.merge_plan(u, blk, grid, mb, r, workspace=False)
     ws = torch.full((usv.merge_plan_workspace_bytes(u.shape[0], grid, mb, r),), 0xA5, dtype=torch.uint8, device=u.device)
     wide = usv.merge_plan(u, blk, grid, mb, r, workspace=ws)
@@ -90,11 +91,12 @@ def test_merge_pipeline(usv, grid, mb, B, Hh, d, dtype):
         np.testing.assert_array_equal(gu.down(z), z_ref)
 
 
-def test_merge_plan_ties_and_special_values(usv):
+@pytest.mark.parametrize("grid", [(3, 20, 40), (3, 75, 75)], ids=["2400_tokens", "16875_tokens"])  # (odd: rows of u and blk without alignment)
+def test_merge_plan_ties_and_special_values(usv, grid):
     """Engineered similarities: many exact ties across the sweep boundary of the selection, signed zeros,
     NaN (ranks lowest), several batch elements with different values."""
-    grid, mb = (3, 20, 40), (1, 2, 2)
-    N = 2400
+    mb = (1, 2, 2)
+    N = grid[0] * grid[1] * grid[2]
     rng = np.random.default_rng(7)
     dst = orc.merge_partition(grid, mb)
     u = np.round(rng.standard_normal((3, N)) * 2).astype(np.float32) / 4  # heavy ties
