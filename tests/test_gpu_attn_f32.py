@@ -46,7 +46,7 @@ def edit(what, Q, K, V, Nv):
 @pytest.mark.parametrize("what", ["plain", "inf in v", "nan in v", "nan in q", "-inf logit", "beyond bf16", "tiny v",
                                   "tiny v, lower parts subnormal", "subnormal v", "zero v", "huge q, tiny k", "tiny q, huge k",
                                   "tiny weight, huge v", "huge padding"])
-@pytest.mark.parametrize("Hh", [2, 52])  # 10 query blocks: eight waves each; 260, just past one per CU: four waves each
+@pytest.mark.parametrize("Hh", [2, 14, 52])  # 10 query blocks: sixteen rows to a workgroup; 70: eight waves a block; 260, just past one per CU: four
 def test_f32_attention_special_values(usv, d, tail, what, Hh):
     nb, Nv = 5, 5 * 64 - tail
     rng = np.random.default_rng(d + tail)
