@@ -31,19 +31,35 @@ def run(s, nv, **change):
     return [t[n].clone() for n in ("scores", "idx", "cnt", "out", "lse")]
 
 
+class Recorded:
+    """The extension, and what each of its functions returned: a status, or None for what it leaves to the binding."""
+
+    def __init__(self, calls):
+        self.calls, self.returned = calls, {}
+
+    def __getattr__(self, name):
+        def call(*args):
+            status = getattr(self.calls, name)(*args)
+            self.returned[name] = status
+            return status
+
+        return call
+
+
 def both(monkeypatch, f):
-    """Result or error of f with the extension and without."""
+    """Result or error of f with the extension and without; what the extension returned."""
     got = []
     binding.lib()
     assert binding._calls is not None, "the build step builds the extension"
-    for calls in (binding._calls, None):
+    extension = Recorded(binding._calls)
+    for calls in (extension, None):
         with monkeypatch.context() as m:
             m.setattr(binding, "_calls", calls)
             try:
                 got.append(f())
             except Exception as e:
                 got.append((type(e), str(e)))
-    return got
+    return (*got, extension.returned)
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
@@ -53,8 +69,12 @@ def test_the_same_bits(usv, monkeypatch, dtype, nv):
     for change in ({}, {"local": True}, {"use_budgets": s["budgets"], "keep": 0, "kmax": 3}, {"scale": 0.3, "use_lse": s["lse"]},
                    {"ordered": dtype == torch.bfloat16}, {"scale": 1}):
         s["lse"].zero_()
-        a, b = both(monkeypatch, lambda: run(s, nv, **change))
+        a, b, returned = both(monkeypatch, lambda: run(s, nv, **change))
         assert isinstance(a, list) and isinstance(b, list), (a, b)
+        # the extension did it all, but for a scale that is not a float
+        taken = {"block_scores": 0, "select_topk": 0, "block_sparse_attn": None if "scale" in change and isinstance(change["scale"], int) else 0}
+        if change.get("ordered"): taken["attn_work_order"] = 0
+        assert returned == taken, change
         for x, y in zip(a, b):
             assert torch.equal(x.view(torch.int32), y.view(torch.int32)), change
 
@@ -87,5 +107,5 @@ def test_the_same_errors(usv, monkeypatch, what):
     if what == "lse not fp32": change["use_lse"] = s["lse"].half()
     if what == "not a tensor": change["q"] = [1.0]
     if what == "head dimension": change.update(q=q[..., :32].contiguous(), k=s["k"][..., :32].contiguous())
-    a, b = both(monkeypatch, lambda: run(s, nv, **change))
+    a, b, _ = both(monkeypatch, lambda: run(s, nv, **change))
     assert isinstance(a, tuple) and a == b, (a, b)
