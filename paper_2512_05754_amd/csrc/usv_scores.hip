@@ -99,39 +99,24 @@ __global__ __launch_bounds__(kPoolThreads) void pool_means(const T* __restrict__
 // 64 channels at a time.  An MFMA step contracts 2 channels, one per 32-lane half; which channels a
 // step takes is free as long as both operands agree, so half g takes channels 32 g + t at step t
 // and every lane reads its operands as contiguous 16-byte pieces.
-// For operands that three bf16 parts do not carry: infinities, and values of which a lower part or a part's product runs out of exponent.
+// For heads below 512 blocks (the launcher says why), and for operands that three bf16 parts do not carry: infinities, and values of which a lower
+// part or a part's product runs out of exponent.
 constexpr int kTileLd = 64 + 4;  // row stride in floats: 16-byte reads of 32 consecutive rows spread over the banks
-template <int D>
-__device__ __forceinline__ void fp32_tile(float* As, float* Bs, const float* __restrict__ qbase, const float* __restrict__ kbase,
-                                          float* __restrict__ out, int i0, int j0, int nb, int nb_valid, float rsqrt_d) {
+template <int D, typename Put, typename Ahead>  // put(p): stages pass p; ahead(p): what may be asked for while it is multiplied
+__device__ __forceinline__ void fp32_tile(float* As, float* Bs, Put put, Ahead ahead, float* __restrict__ out, int i0, int j0, int nb, int nb_valid,
+                                          float rsqrt_d) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;  // this wave's quadrant
   const int r = lane & 31, g = lane >> 5;
   f32x16 acc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  // each thread stages 4 + 4 float4 per pass; the next pass's loads are issued before this pass's MFMAs
-  float4 ra[4], rb[4];
-  auto fetch = [&](int kc) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + u * 256, row = e / 16, c = (e % 16) * 4;
-      ra[u] = rb[u] = make_float4(0.f, 0.f, 0.f, 0.f);  // zero rows beyond nb
-      if (i0 + row < nb) ra[u] = *reinterpret_cast<const float4*>(qbase + (long long)(i0 + row) * D + kc + c);
-      if (j0 + row < nb) rb[u] = *reinterpret_cast<const float4*>(kbase + (long long)(j0 + row) * D + kc + c);
-    }
-  };
-  fetch(0);
-  for (int kc = 0; kc < D; kc += 64) {
-    if (kc) __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + u * 256, row = e / 16, c = (e % 16) * 4;
-      *reinterpret_cast<float4*>(As + row * kTileLd + c) = ra[u];
-      *reinterpret_cast<float4*>(Bs + row * kTileLd + c) = rb[u];
-    }
+  for (int p = 0; p < D / 64; ++p) {
+    if (p) __syncthreads();
+    put(p);
     __syncthreads();
-    if (kc + 64 < D) fetch(kc + 64);
+    ahead(p);
     const float* ap = As + (wi + r) * kTileLd + 32 * g;
     const float* bp = Bs + (wj + r) * kTileLd + 32 * g;
 #pragma unroll
@@ -154,8 +139,8 @@ __device__ __forceinline__ void fp32_tile(float* As, float* Bs, const float* __r
 }
 
 // The products of three bf16 parts on v_mfma_f32_16x16x32_bf16 (lane = (c, G): rows / columns c of the operands, channels 8 G .. + 8), the
-// leading one and the five small ones in sums of their own; parts staged in LDS as planes, 64 channels at a
-// time.  Six products at sixteen times the rate of the fp32 matrix pipe, which the fp32 form was bound by (5.8 of its 14 us at
+// leading one and the five small ones in sums of their own; parts staged in LDS as planes, 64 channels at a time.
+// Six products at sixteen times the rate of the fp32 matrix pipe, which the fp32 form was bound by (5.8 of its 14 us at
 // 12 x 512 x 512, 110 of 200 us at 40 x 1182 x 1182).  What is left is the chain of load, split, barrier and product, and the store.
 // Operands below 2^59 that are 0 or not below 2^-50 (2^-100 beside larger ones).  Below 2^59 no sum of 128 products overflows
 // (beyond, the leading and the small sums could do so with opposite signs, and a leading part rounded up could where the value does not).  A value
@@ -165,8 +150,8 @@ __device__ __forceinline__ void fp32_tile(float* As, float* Bs, const float* __r
 // below 2^-116, which is less than its fp32 rounding if its terms add up to 2^-92.
 // The look at the operands comes ahead of the products, with the means of all passes requested at once for it.  (Behind them, a tile that fp32
 // operands were taken for was multiplied twice.)  Stage 1, look behind / ahead: 40 x 1182 x 1182 391 / 382 us, 12 x 512 x 512 44.7 / 44.8, d = 64 201.6 /
-// 203.8, 27.3 / 27.2; one channel nearly dead 525 / 391, 52.5 / 45.2, 265 / 206, 30.9 / 27.3; eight of them, which takes fp32 operands, 526 / 469, 53.4 / 50.4
-// (fp32 operands alone: 421, 46.9).
+// 203.8, 27.3 / 27.2; one channel nearly dead 525 / 391, 52.5 / 45.2, 265 / 206, 30.9 / 27.3; eight adjacent ones, which takes fp32 operands (from the registers they
+// were fetched into; fetched again 469, 50.4), 526 / 449, 53.4 / 48.5; fp32 operands alone 421, 46.9.
 constexpr float kScoreMost = 0x1p59f;
 constexpr unsigned below(int e) { return 2u * ((unsigned)(127 + e) << 23) - 1u; }  // twice the bits of 2^e less 1
 template <int D>
@@ -182,11 +167,32 @@ __global__ __launch_bounds__(256, 3) void score_gemm(const float* __restrict__ q
   const float* qbase = qm + (long long)bh * nb * D;
   const float* kbase = km + (long long)bh * nb * D;
   float* out = scores + (long long)bh * nb * nb;
-  auto with_fp32_operands = [&] {
-    fp32_tile<D>(reinterpret_cast<float*>(smem), reinterpret_cast<float*>(smem) + 64 * kTileLd, qbase, kbase, out, i0, j0, nb, nb_valid, rsqrt_d);
-  };
-  if (fp32) return with_fp32_operands();  // (the launcher's choice, the same for every workgroup)
+  float* const As = reinterpret_cast<float*>(smem);
+  float* const Bs = As + 64 * kTileLd;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (fp32) {  // (the launcher's choice, the same for every workgroup)
+    // each thread stages 4 + 4 float4 per pass; the next pass's loads are issued before this pass's MFMAs
+    float4 ra[4], rb[4];
+    auto fetch = [&](int p) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = tid + u * 256, row = e / 16, c = 64 * p + (e % 16) * 4;
+        ra[u] = rb[u] = make_float4(0.f, 0.f, 0.f, 0.f);  // zero rows beyond nb
+        if (i0 + row < nb) ra[u] = *reinterpret_cast<const float4*>(qbase + (long long)(i0 + row) * D + c);
+        if (j0 + row < nb) rb[u] = *reinterpret_cast<const float4*>(kbase + (long long)(j0 + row) * D + c);
+      }
+    };
+    fetch(0);
+    auto put = [&](int) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = tid + u * 256, row = e / 16, c = (e % 16) * 4;
+        *reinterpret_cast<float4*>(As + row * kTileLd + c) = ra[u];
+        *reinterpret_cast<float4*>(Bs + row * kTileLd + c) = rb[u];
+      }
+    };
+    return fp32_tile<D>(As, Bs, put, [&](int p) { if (p + 1 < P) fetch(p + 1); }, out, i0, j0, nb, nb_valid, rsqrt_d);
+  }
   const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;  // this wave's quadrant
   const int c16 = lane & 15, G = lane >> 4;
   // a row's eight 16-byte chunks are stored at chunk ^ (row % 8): sixteen rows of a fragment spread over the banks
@@ -252,7 +258,19 @@ __global__ __launch_bounds__(256, 3) void score_gemm(const float* __restrict__ q
       if (lane == 0) refused[wave] = any;
     }
     __syncthreads();
-    if (p == 0 && (refused[0] | refused[1] | refused[2] | refused[3])) return with_fp32_operands();
+    if (p == 0 && (refused[0] | refused[1] | refused[2] | refused[3])) {
+      auto put = [&](int of) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int half = 0; half < 2; ++half) {
+            const int e = tid + 256 * u, at = (e >> 3) * kTileLd + (e & 7) * 8 + 4 * half;
+            *reinterpret_cast<float4*>(As + at) = raw[of][0][u][half];
+            *reinterpret_cast<float4*>(Bs + at) = raw[of][1][u][half];
+          }
+      };
+      return fp32_tile<D>(As, Bs, put, [](int) {}, out, i0, j0, nb, nb_valid, rsqrt_d);
+    }
 #pragma unroll
     for (int t = 0; t < KC / 32; ++t) {
       bf16x8 a[2][3], b[2][3];
