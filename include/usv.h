@@ -172,11 +172,12 @@ usv_status usv_select_topk_ex(const float* scores, const usv_shape* shape, int32
  * slot, or under another kmax, may give a result that differs by that rounding:
  * each weight by at most 2^-7 of itself between the two, which is 2e-4 to 1e-3
  * of the result's 2-norm on video-like inputs, as much as the result's own
- * error.  Smaller launches and fp32 inputs begin at the first entry.
+ * error.  Smaller bf16 launches begin at the first entry.
  * fp32 inputs: both products to fp32 accuracy (operands in three bf16 parts,
  * the six leading products summed in fp32; on the fp32 matrix cores where a
  * part would run out of range), fp32 softmax: within 1e-5 relative of an fp64
- * evaluation.
+ * evaluation.  The order of the sums depends on the launch's size (up to 64, up
+ * to 256 and more query blocks), and with it the last bits.
  */
 usv_status usv_block_sparse_attn(const void* q, const void* k, const void* v,
                                  const usv_shape* shape, const int32_t* idx, const int32_t* cnt,
@@ -194,10 +195,10 @@ usv_status usv_block_sparse_attn(const void* q, const void* k, const void* v,
  * launch is made of the shortest lists.  "Where the list lies" = its entries at
  * 1/4, 1/2 and 3/4 of its length, each reduced to one of 64 equal buckets of
  * the block range, compared lexicographically.  Measured on MI355X: per-row
- * budgets uniform in 8..64 at the merged 480p shape 25 % faster than index
+ * budgets uniform in 8..64 at the merged 480p shape 23 % faster than index
  * order; uniform budgets at the 720p shape (59 of 1182 blocks, where a head's
- * K and V are ten times the L2) 7 % faster; uniform budgets at the 480p shape
- * 0 to 3 % (there the sort costs what it gains).  It pays when the lists are
+ * K and V are ten times the L2) 3 % faster; uniform budgets at the 480p shape
+ * 0 to 1 % (there the sort costs more than it gains).  It pays when the lists are
  * ragged or when a head's K and V are many times the L2.
  *
  *   usv_attn_work_order   work_order[b,h,s] = the query block that slot s of head
